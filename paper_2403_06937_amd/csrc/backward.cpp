@@ -76,10 +76,8 @@ void bwd_layout(Arena& ar, int64_t N, const tc_evolve_opts& o, BwdLayout* L) {
   L->Q0 = static_cast<c128*>(ar.take(NN * 16));
   L->Q1 = static_cast<c128*>(ar.take(NN * 16));
   L->scratch = static_cast<double*>(ar.take(8 * sizeof(double)));
-  // 8 slots per tile of the N x N product, at most 256, from 2 tile rows on
-  const int64_t t = (N + 127) / 128;
-  if (t >= 2) {
-    L->tail.bytes = size_t(std::min<int64_t>(256, 8 * t * t)) * 128 * 128 * 16;
+  if (tail_slots(N) > 0) {
+    L->tail.bytes = size_t(tail_slots(N)) * 128 * 128 * 16;
     L->tail.p = ar.take(L->tail.bytes);
   }
 }

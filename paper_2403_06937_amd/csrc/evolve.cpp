@@ -158,17 +158,18 @@ void plan_sectors(const tc_evolve_opts& o, Arena& ar, InstPlan* p) {
   }
 }
 
-// Slots for the partial sums of a dense product's last round split over K:
-// one 128 x 128 tile of complex elements per slot (16 B in FP64, 8 B as FP32
-// in the FP32 and split-BF16 products), 8 per tile of the N x N product and
-// at most 256 (64 MB in FP64); none for a single tile row, whose K is too
-// short to split.
+// Slots for the partial sums of a dense product's last round: one 128 x 128
+// tile of complex elements per slot (16 B in FP64, 8 B as FP32 in the FP32 and
+// split-BF16 products; at most 134 MB in FP64).  The split-BF16 product cuts
+// every tile of its last round into the same number of ranges, at most 256.
 size_t tail_bytes(const InstPlan& p, const tc_evolve_opts& o) {
   if (o.sectors) return 0;
-  const int64_t t = (p.N + 127) / 128;
-  if (t < 2) return 0;
   const size_t eb = o.gemm_mode == TC_GEMM_F64 ? 16 : 8;
-  return size_t(std::min<int64_t>(256, 8 * t * t)) * 128 * 128 * eb;
+  const int64_t t = (p.N + 127) / 128;
+  const int64_t slots = o.gemm_mode == TC_GEMM_SPLIT_BF16
+                            ? (t < 2 ? 0 : std::min<int64_t>(256, 8 * t * t))
+                            : tail_slots(p.N);
+  return size_t(slots) * 128 * 128 * eb;
 }
 
 // One region of slots for instances stepped one after another on one

@@ -37,6 +37,16 @@ struct GemmDesc {
   void* tail_ws = nullptr; size_t tail_ws_bytes = 0;
 };
 
+// Slots of one 128 x 128 tile that the partial sums of an N x N product's last
+// round take: one per range and one more per tile that a range ends in (at
+// most 256 ranges, of at least 4 K tiles each, over fewer than 256 tiles); none
+// for a single tile row, whose K is too short to split.
+inline int64_t tail_slots(int64_t N) {
+  const int64_t t = (N + 127) / 128;
+  if (t < 2) return 0;
+  return t >= 8 ? 511 : (2 * t * t * t + t * t < 511 ? 2 * t * t * t + t * t : 511);
+}
+
 int gemm_f64(const GemmDesc& d, hipStream_t s);   // elements double / cplx<double>
 int gemm_f32(const GemmDesc& d, hipStream_t s);   // elements float / cplx<float>
 

@@ -192,15 +192,15 @@ struct TileLds {
 // Modes of gemm_tile: the whole tile; PARTIAL: the K loop only, the raw
 // accumulators stored to part (16-byte chunk c of thread t at chunk c NT + t,
 // over the blocks' real then imaginary accumulators); FINISH: no K loop, the
-// accumulators are the in-order sum of nparts such slots from part, then the
-// epilogue.
+// accumulators of every wave's block row frow are the in-order sum of nparts
+// such slots from part, then the epilogue of that block row.
 enum TileMode { TILE_FULL = 0, TILE_PARTIAL = 1, TILE_FINISH = 2 };
 
 template <typename T, bool CPLX, bool AK, bool BK, bool CHECKED,
           int BM, int BN, int BKT, int WM, int WN, int PADB, int MODE = TILE_FULL>
 __device__ __forceinline__ void gemm_tile(const Params& p, int tm, int tn, bool mirror,
                                           typename elem<T, CPLX>::type* lds,
-                                          void* part = nullptr, int nparts = 0) {
+                                          void* part = nullptr, int nparts = 0, int frow = 0) {
   typedef typename elem<T, CPLX>::type E;
   typedef typename acc_t<T>::type A4;
   constexpr int WGN = BN / (16 * WN);
@@ -253,9 +253,10 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int tm, int tn, bool 
   const int64_t ska = AK ? int64_t(BKT) * lda : BKT;
   const int64_t skb = BK ? int64_t(BKT) * ldb : BKT;
 
-  A4 acc_re[WM][WN], acc_im[WM][WN];
+  constexpr int WMA = MODE == TILE_FINISH ? 1 : WM;   // block rows held
+  A4 acc_re[WMA][WN], acc_im[WMA][WN];
 #pragma unroll
-  for (int i = 0; i < WM; ++i)
+  for (int i = 0; i < WMA; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
       acc_re[i][j] = A4{0, 0, 0, 0};
@@ -325,29 +326,24 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int tm, int tn, bool 
   struct Chunks { u4 c[sizeof(A4) / 16]; };
   constexpr int NCH = int(sizeof(A4) / 16);
   if constexpr (MODE == TILE_FINISH) {
-    // one row of blocks at a time, the slots in order inside it, so that only
-    // that row's partial sums are live next to the accumulators
     constexpr int PER_ROW = (CPLX ? 2 : 1) * WN * NCH;          // chunks per row of blocks
     const size_t slot = size_t((CPLX ? 2 : 1) * WM * WN * NCH) * NT;
+#pragma unroll 2
+    for (int r = 0; r < nparts; ++r) {
+      const u4* src = static_cast<const u4*>(part) + size_t(r) * slot + size_t(frow) * PER_ROW * NT;
+      int c = 0;
 #pragma unroll
-    for (int i = 0; i < WM; ++i) {
-#pragma unroll 1
-      for (int r = 0; r < nparts; ++r) {
-        const u4* src = static_cast<const u4*>(part) + size_t(r) * slot + size_t(i) * PER_ROW * NT;
-        int c = 0;
+      for (int j = 0; j < WN; ++j) {
+        Chunks a, b;
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          Chunks a, b;
+        for (int h = 0; h < NCH; ++h) a.c[h] = gload(src + size_t(c + h) * NT + tid);
+        c += NCH;
+        acc_re[0][j] += __builtin_bit_cast(A4, a);
+        if constexpr (CPLX) {
 #pragma unroll
-          for (int h = 0; h < NCH; ++h) a.c[h] = gload(src + size_t(c + h) * NT + tid);
+          for (int h = 0; h < NCH; ++h) b.c[h] = gload(src + size_t(c + h) * NT + tid);
           c += NCH;
-          acc_re[i][j] += __builtin_bit_cast(A4, a);
-          if constexpr (CPLX) {
-#pragma unroll
-            for (int h = 0; h < NCH; ++h) b.c[h] = gload(src + size_t(c + h) * NT + tid);
-            c += NCH;
-            acc_im[i][j] += __builtin_bit_cast(A4, b);
-          }
+          acc_im[0][j] += __builtin_bit_cast(A4, b);
         }
       }
     }
@@ -442,10 +438,10 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int tm, int tn, bool 
   const bool use_beta = (Cin != nullptr) && (p.beta_re != 0.0 || p.beta_im != 0.0);
   // FP64 MFMA output r of lane l is row l/16 + 4r; FP32 is row 4(l/16) + r
   auto out_row = [&](int i, int r) -> int64_t {
-    return m0 + (wm * WM + i) * 16 + (sizeof(T) == 8 ? lrow + 4 * r : 4 * lrow + r);
+    return m0 + (wm * WM + i + frow) * 16 + (sizeof(T) == 8 ? lrow + 4 * r : 4 * lrow + r);
   };
 #pragma unroll
-  for (int i = 0; i < WM; ++i) {
+  for (int i = 0; i < WMA; ++i) {
     // beta's operand for this row of blocks, loaded before any of it is used
     // (addresses clamped into the matrix, so no branch): one wait per row of
     // blocks instead of one per element
@@ -512,14 +508,36 @@ gemm_kernel(const Params p) {
                                                                  lds);
 }
 
-// A product's last round split over K, as for the split-BF16 product: the
-// main launch runs the full rounds of one tile per CU (none for a product
-// with fewer tiles than half the CUs), gemm_tail_kernel runs
-// the remaining tiles' S K ranges (kc K tiles each) and stores their
-// accumulators to one slot each of part, and gemm_tail_finish_kernel adds
-// each tile's S slots in order and runs the epilogue (mirror included for a
-// Hermitian product).  Positions base .. base + tail - 1 of the launch's tile
+// A product's last, partial round of tiles spread evenly over the CUs.  The
+// main launch runs the full rounds of one tile per CU (none for a product with
+// fewer tiles than CUs); the remaining `tail` tiles' K tiles, tail x kt of them
+// laid end to end, are cut into G equal ranges, one workgroup each, so that
+// every CU does tail / G of a tile's work instead of tail CUs doing a whole
+// tile while the others idle.  A range (at most kt K tiles) touches at most
+// two tiles; each piece's accumulators go to slot w + i of part (workgroup w,
+// tile i: unique, and a tile's pieces are neighbours in K order), and
+// gemm_tail_finish_kernel adds each tile's slots in order and runs the epilogue
+// (mirror included for a Hermitian product), one workgroup per tile and row of
+// its waves' blocks.  Bound by the MFMA pipes like the tile loop; N = 2304 FP64
+// (324 tiles, one round and 68; the triangle 171) takes 2.21 ms a step against
+// 2.59 ms when each tile of a last round was cut into the same whole number of
+// ranges, which left the triangle's 171 tiles a whole tile each on two thirds
+// of the CUs; complex FP32 the same way (40-step gradient 301 -> 269 ms).
+// Positions base .. base + tail - 1 of the launch's tile
 // order are the tiles the main launch (grid base) leaves out.
+struct TailSplit {
+  int base, tail, G;
+  int64_t kt;
+  __host__ __device__ int64_t start(int64_t w) const { return w * (int64_t(tail) * kt) / G; }
+  // the workgroup whose range holds K tile x of the concatenation
+  __device__ int owner(int64_t x) const {
+    int w = int(x * G / (int64_t(tail) * kt));
+    while (w + 1 < G && start(w + 1) <= x) ++w;
+    while (start(w) > x) --w;
+    return w;
+  }
+};
+
 __device__ __forceinline__ void launch_tile(const Params& p, int pid, int& tm, int& tn) {
   if (p.herm)
     tri_coords(xcd_linear(pid, p.tiles_m * (p.tiles_m + 1) / 2), p.tiles_m, tm, tn);
@@ -530,33 +548,44 @@ __device__ __forceinline__ void launch_tile(const Params& p, int pid, int& tm, i
 template <typename T, bool CPLX, bool AK, bool BK, int BM, int BN, int BKT, int WM, int WN,
           int PADB>
 __global__ void __launch_bounds__(64 * (BM / (16 * WM)) * (BN / (16 * WN)), 1)
-gemm_tail_kernel(const Params p, int base, int S, int kc, void* part, size_t slot_bytes) {
+gemm_tail_kernel(const Params p, TailSplit ts, void* part, size_t slot_bytes) {
   typedef TileLds<T, CPLX, BM, BN, BKT, PADB> L;
   typedef typename L::E E;
   __shared__ E lds[L::elems];
-  const int i = blockIdx.x / S, r = blockIdx.x % S;
-  int tm, tn;
-  launch_tile(p, base + i, tm, tn);
-  const int64_t k0 = int64_t(r) * kc * BKT;
-  Params q = p;
-  q.A = static_cast<const E*>(p.A) + (AK ? k0 * p.lda : k0);
-  q.B = static_cast<const E*>(p.B) + (BK ? k0 * p.ldb : k0);
-  q.K = min(int64_t(kc) * BKT, p.K - k0);
-  gemm_tile<T, CPLX, AK, BK, false, BM, BN, BKT, WM, WN, PADB, TILE_PARTIAL>(
-      q, tm, tn, false, lds, static_cast<char*>(part) + size_t(blockIdx.x) * slot_bytes);
+  // neighbouring ranges on one XCD: they share a tile's operand rows
+  const int w = xcd_linear(blockIdx.x, ts.G);
+  int64_t x = ts.start(w);
+  const int64_t end = ts.start(w + 1);
+#pragma unroll 1
+  while (x < end) {
+    const int i = int(x / ts.kt);
+    const int64_t kx = x - i * ts.kt, len = min(ts.kt - kx, end - x);
+    int tm, tn;
+    launch_tile(p, ts.base + i, tm, tn);
+    const int64_t k0 = kx * BKT;
+    Params q = p;
+    q.A = static_cast<const E*>(p.A) + (AK ? k0 * p.lda : k0);
+    q.B = static_cast<const E*>(p.B) + (BK ? k0 * p.ldb : k0);
+    q.K = len * BKT;
+    gemm_tile<T, CPLX, AK, BK, false, BM, BN, BKT, WM, WN, PADB, TILE_PARTIAL>(
+        q, tm, tn, false, lds, static_cast<char*>(part) + size_t(w + i) * slot_bytes);
+    x += len;
+    if (x < end) __syncthreads();          // the LDS is reused
+  }
 }
 
 template <typename T, bool CPLX, bool AK, bool BK, int BM, int BN, int BKT, int WM, int WN,
           int PADB>
 __global__ void __launch_bounds__(64 * (BM / (16 * WM)) * (BN / (16 * WN)), 1)
-gemm_tail_finish_kernel(const Params p, int base, int S, const void* part, size_t slot_bytes) {
-  typedef TileLds<T, CPLX, BM, BN, BKT, PADB> L;
-  __shared__ typename L::E lds[L::elems];
+gemm_tail_finish_kernel(const Params p, TailSplit ts, const void* part, size_t slot_bytes) {
+  const int i = blockIdx.x;
   int tm, tn;
-  launch_tile(p, base + int(blockIdx.x), tm, tn);
+  launch_tile(p, ts.base + i, tm, tn);
+  const int w0 = ts.owner(i * ts.kt), w1 = ts.owner((i + 1) * ts.kt - 1);
   gemm_tile<T, CPLX, AK, BK, false, BM, BN, BKT, WM, WN, PADB, TILE_FINISH>(
-      p, tm, tn, p.herm && tm != tn, lds,
-      const_cast<char*>(static_cast<const char*>(part)) + size_t(blockIdx.x) * S * slot_bytes, S);
+      p, tm, tn, p.herm && tm != tn, nullptr,
+      const_cast<char*>(static_cast<const char*>(part)) + size_t(w0 + i) * slot_bytes,
+      w1 - w0 + 1, blockIdx.y);
 }
 
 // Persistent grouped products: items[0 .. count) each describe one product
@@ -721,33 +750,32 @@ int launch_shape(const GemmDesc& d, hipStream_t s) {
   const dim3 grid{unsigned(tiles), 1u, 1u}, block{unsigned(S::NT), 1u, 1u};
   ProfileScope prof(sizeof(T) == 8 ? TC_KERNEL_GEMM_F64 : TC_KERNEL_GEMM_F32, s);
   if (exact && d.tail_ws) {
-    // a last round that would leave at least half of the CUs idle (the whole
-    // product, when it has that few tiles): its tiles go split over K, one
-    // workgroup and one slot of partial sums per K range of at least 4 K tiles
+    // a partial last round (the whole product, when it has fewer tiles than
+    // CUs) is spread over the CUs, ranges of at least 4 K tiles each, when that
+    // saves at least 4 K tiles' time (about what storing and adding the partial
+    // sums costs; a K tile of a 128 x 128 FP64 tile takes 7 us)
     const int cus = device_cus();
-    const int64_t full = tiles / cus, tail = tiles % cus, kt = d.K / S::BKT;
     const size_t slot = size_t(S::BM) * S::BN * (CPLX ? 2 : 1) * sizeof(T);
-    const int64_t slots = int64_t(d.tail_ws_bytes / slot);
-    int R = int(std::min<int64_t>(std::min<int64_t>(cus, slots) / std::max<int64_t>(tail, 1),
-                                  std::min<int64_t>(8, kt / 4)));
-    if (tail > 0 && tail * 2 <= cus && R >= 2) {
-      const int64_t kc = (kt + R - 1) / R;
-      R = int((kt + kc - 1) / kc);         // every K range non-empty
-      const int base = int(full * cus);
-      if (base > 0) {
+    TailSplit ts;
+    ts.kt = d.K / S::BKT;
+    ts.base = int(tiles / cus * cus);
+    ts.tail = int(tiles - ts.base);
+    const int64_t slots = std::min<int64_t>(int64_t(d.tail_ws_bytes / slot), 1 << 20);
+    ts.G = int(std::min<int64_t>(std::min<int64_t>(cus, ts.tail * ts.kt / 4), slots - ts.tail + 1));
+    if (ts.tail > 0 && ts.G > ts.tail && ts.kt * (ts.G - ts.tail) >= 4 * int64_t(ts.G)) {
+      if (ts.base > 0) {
         hipLaunchKernelGGL((gemm_kernel<T, CPLX, AK, BK, false, S::BM, S::BN, S::BKT, S::WM,
                                         S::WN, S::PADB>),
-                           dim3(unsigned(base)), block, 0, s, p);
+                           dim3(unsigned(ts.base)), block, 0, s, p);
         TC_TRY_HIP(hipGetLastError());
       }
       hipLaunchKernelGGL((gemm_tail_kernel<T, CPLX, AK, BK, S::BM, S::BN, S::BKT, S::WM, S::WN,
                                            S::PADB>),
-                         dim3(unsigned(tail * R)), block, 0, s, p, base, R, int(kc), d.tail_ws,
-                         slot);
+                         dim3(unsigned(ts.G)), block, 0, s, p, ts, d.tail_ws, slot);
       TC_TRY_HIP(hipGetLastError());
       hipLaunchKernelGGL((gemm_tail_finish_kernel<T, CPLX, AK, BK, S::BM, S::BN, S::BKT, S::WM,
                                                   S::WN, S::PADB>),
-                         dim3(unsigned(tail)), block, 0, s, p, base, R,
+                         dim3(unsigned(ts.tail), unsigned(S::WM)), block, 0, s, p, ts,
                          static_cast<const void*>(d.tail_ws), slot);
       TC_TRY_HIP(hipGetLastError());
       return TC_OK;

@@ -318,6 +318,29 @@ def test_small_products_on_64_tiles(n, c, mode, frame, rdt, tol, full):
     assert err < tol and perr < tol
 
 
+@pytest.mark.parametrize("n,c", [(7, 4), (7, 8), (8, 7)])
+@pytest.mark.parametrize("mode,frame,rdt,tol", [
+    (tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-10),
+    (tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5)])
+@pytest.mark.parametrize("full", [False, True])
+def test_partial_round_ranges_across_tiles(n, c, mode, frame, rdt, tol, full):
+    """N = 640 (15 or 25 tiles, fewer than the CUs: ranges of 4 K tiles),
+    N = 1152 (45 or 81) and N = 2048 (136 tiles of the triangle on 256 CUs: K
+    ranges that end inside one tile and begin inside the next; every tile of
+    the full product: whole rounds): every entry and every 5th population
+    record against the oracle after 20 steps."""
+    inst = ti.random_model(n, c, 450 + n, state="haar2")
+    dt, steps = 0.05, 20
+    rho, pop, _ = run_gpu(inst, dt, steps, mode, frame, renorm=10, rho_dtype=rdt, full=full)
+    P = oev.SectorPropagator(inst.n, inst.c, inst.g, inst.omega_a)
+    O = excitation_op(inst.n, inst.c)
+    perr = max(abs(pop[s] - float(np.sum(O * np.abs(P.psi(inst.psi0, s * dt)) ** 2)))
+               for s in range(0, steps + 1, 5))
+    err = max_entry_error_pure(rho, P.psi(inst.psi0, steps * dt))
+    print(f"N={inst.N} mode={mode} full={full} max-entry={err:.3e} pop={perr:.3e}", flush=True)
+    assert err < tol and perr < tol
+
+
 def mid_instance(seed=0):
     """C3-shaped but smaller: n=7, c=5 (N=768), 2 photons x Haar product."""
     return ti.random_model(7, 5, 100 + seed, state="haar2")
