@@ -46,53 +46,88 @@ int make_model_args(const tc_model* m, ModelArgs* out) {
 // ----------------------------------------------------------------- expm
 namespace {
 
-// Real FP64 product C = alpha A B + gamma I (all N x N row-major, ld N).
-int rgemm(const double* A, const double* B, double* C, int64_t N, double alpha, double gamma,
-          hipStream_t s) {
-  GemmDesc d;
-  d.M = d.N = d.K = N;
-  d.A = A; d.lda = N; d.a_kmaj = false;
-  d.B = B; d.ldb = N; d.b_kmaj = true;
-  d.C = C; d.ldc = N;
-  d.alpha_re = alpha; d.gamma = gamma;
-  d.complex = false;
-  return gemm_f64(d, s);
-}
+// Every matrix of the exponential is a polynomial in the symmetric B, so every
+// product is symmetric too: only its upper tile triangle is multiplied, and
+// mirrored.  A, B, C: N x N row-major, ld N.
+struct SymProducts {
+  int64_t N = 0;
+  void* tail = nullptr; size_t tail_bytes = 0;   // partial sums of a last round
+  hipStream_t s = nullptr;
+  // C = alpha A B + beta C + gamma I
+  int run(const double* A, const double* B, double* C, double alpha, double beta,
+          double gamma = 0.0) const {
+    GemmDesc d;
+    d.M = d.N = d.K = N;
+    d.A = A; d.lda = N; d.a_kmaj = false;
+    d.B = B; d.ldb = N; d.b_kmaj = true;
+    d.C = C; d.ldc = N;
+    d.alpha_re = alpha;
+    if (beta != 0.0) { d.Cin = C; d.ldcin = N; d.beta_re = beta; }
+    d.gamma = gamma;
+    d.complex = false;
+    d.herm = true;
+    d.tail_ws = tail; d.tail_ws_bytes = tail_bytes;
+    return gemm_f64(d, s);
+  }
+};
 
+// Six N x N matrices.
 struct ExpmLayout {
-  double *B, *X, *P0, *P1, *Q0, *Q1;
-  c128* T;   // complex ping-pong for squaring (aliases P0..P1 storage)
+  double *B, *X, *X2, *X3, *T, *W;
 };
 
 void expm_layout(Arena& ar, int64_t N, ExpmLayout* L) {
   const size_t rb = size_t(N) * size_t(N) * sizeof(double);
-  L->B = static_cast<double*>(ar.take(rb));
-  L->X = static_cast<double*>(ar.take(rb));
-  L->P0 = static_cast<double*>(ar.take(2 * rb));  // 2 rb: also holds a complex N x N
-  L->P1 = L->P0 ? L->P0 + size_t(N) * size_t(N) : nullptr;
-  L->Q0 = static_cast<double*>(ar.take(rb));
-  L->Q1 = static_cast<double*>(ar.take(rb));
-  L->T = reinterpret_cast<c128*>(L->P0);
+  double** m[6] = {&L->B, &L->X, &L->X2, &L->X3, &L->T, &L->W};
+  for (auto p : m) *p = static_cast<double*>(ar.take(rb));
 }
 
-// Horner: out = sum_{k=0}^{deg} coef[k] X^k  (uses ping-pong a/b; returns the buffer holding it)
-int horner(const double* X, const std::vector<double>& coef, double* a, double* b, int64_t N,
-           hipStream_t s, double** result) {
-  const int deg = int(coef.size()) - 1;
-  // P = coef[deg] X + coef[deg-1] I  (first step without a product)
-  if (deg == 0) {
-    TC_RETURN_IF(launch_axpb_identity(X, N, 0.0, coef[0], a, N, N, s));
-    *result = a;
-    return TC_OK;
+// cos and sin of B from their Taylor polynomials in X = B^2 (coefficients cc,
+// cs, of degree 9, or 5 and 4 for the ten-term series), with X^2 and X^3 formed
+// once and three coefficients per product (Paterson and Stockmeyer's scheme):
+//   p(X) = (a0 + a1 X + a2 X^2) + X^3 ((a3 + a4 X + a5 X^2) + X^3 (a6 .. + a9 X^3)),
+// 8 products of half the tiles instead of 18 whole ones by Horner's rule (U at
+// N = 5120: 17.8 ms against 79.4).  Each identity term is added last, in the
+// product's epilogue, so that the entries near 1 are rounded once.
+int cos_sin(const ExpmLayout& L, const SymProducts& g, const std::vector<double>& cc,
+            const std::vector<double>& cs, double** cosB, double** sinB) {
+  const int64_t N = g.N;
+  hipStream_t s = g.s;
+  // coefficients from .. to of a block a[3b] + a[3b + 1] X + a[3b + 2] X^2 (+ a[9] X^3)
+  auto lin = [](const std::vector<double>& a, int from, int to) {
+    LinCoef c{{0.0, 0.0, 0.0, 0.0}};
+    for (int k = from; k <= to && k < int(a.size()); ++k) c.a[k % 3 + (k == 9 ? 3 : 0)] = a[k];
+    return c;
+  };
+  TC_RETURN_IF(g.run(L.B, L.B, L.X, 1.0, 0.0));
+  TC_RETURN_IF(g.run(L.X, L.X, L.X2, 1.0, 0.0));
+  TC_RETURN_IF(g.run(L.X, L.X2, L.X3, 1.0, 0.0));
+  if (cc.size() > 6) {
+    TC_RETURN_IF(launch_lin_powers(L.X, L.X2, L.X3, N, lin(cc, 6, 9), L.T, lin(cc, 4, 5), L.W,
+                                   LinCoef(), nullptr, s));
+    TC_RETURN_IF(g.run(L.X3, L.T, L.W, 1.0, 1.0, cc[3]));
+    TC_RETURN_IF(launch_lin_powers(L.X, L.X2, L.X3, N, lin(cc, 1, 2), L.T, LinCoef(), nullptr,
+                                   LinCoef(), nullptr, s));
+    TC_RETURN_IF(g.run(L.X3, L.W, L.T, 1.0, 1.0, cc[0]));
+    // the sine's three combinations, two of them in place of X^2 and X
+    TC_RETURN_IF(launch_lin_powers(L.X, L.X2, L.X3, N, lin(cs, 6, 9), L.W, lin(cs, 4, 5), L.X2,
+                                   lin(cs, 1, 2), L.X, s));
+    TC_RETURN_IF(g.run(L.X3, L.W, L.X2, 1.0, 1.0, cs[3]));
+    TC_RETURN_IF(g.run(L.X3, L.X2, L.X, 1.0, 1.0, cs[0]));
+    TC_RETURN_IF(g.run(L.B, L.X, L.W, 1.0, 0.0));
+    *cosB = L.T;
+    *sinB = L.W;
+  } else {
+    TC_RETURN_IF(launch_lin_powers(L.X, L.X2, L.X3, N, lin(cc, 3, 5), L.T, lin(cc, 1, 2), L.W,
+                                   LinCoef(), nullptr, s));
+    TC_RETURN_IF(g.run(L.X3, L.T, L.W, 1.0, 1.0, cc[0]));
+    TC_RETURN_IF(launch_lin_powers(L.X, L.X2, L.X3, N, lin(cs, 3, 5), L.T, lin(cs, 1, 2), L.X,
+                                   LinCoef(), nullptr, s));
+    TC_RETURN_IF(g.run(L.X3, L.T, L.X, 1.0, 1.0, cs[0]));
+    TC_RETURN_IF(g.run(L.B, L.X, L.T, 1.0, 0.0));
+    *cosB = L.W;
+    *sinB = L.T;
   }
-  TC_RETURN_IF(launch_axpb_identity(X, N, coef[deg], coef[deg - 1], a, N, N, s));
-  double* cur = a;
-  double* nxt = b;
-  for (int k = deg - 2; k >= 0; --k) {
-    TC_RETURN_IF(rgemm(cur, X, nxt, N, 1.0, coef[k], s));
-    std::swap(cur, nxt);
-  }
-  *result = cur;
   return TC_OK;
 }
 
@@ -288,7 +323,6 @@ int tc_expm(const double* H, int64_t N, int64_t ldh, double dt, double lam_lo, d
     // the helper reads with ld = ldh and writes with ld = N
     TC_RETURN_IF(launch_axpb_identity(H, ldh, scale, -mu * scale, L.B, N, N, s));
   }
-  TC_RETURN_IF(rgemm(L.B, L.B, L.X, N, 1.0, 0.0, s));                  // X = B^2
   std::vector<double> cc(kc + 1), cs(ks + 1);
   {
     double f = 1.0;   // (2k)!
@@ -302,39 +336,36 @@ int tc_expm(const double* H, int64_t N, int64_t ldh, double dt, double lam_lo, d
       cs[k] = (k % 2 ? -1.0 : 1.0) / f;
     }
   }
-  double* cosB = nullptr;
-  double* sinpoly = nullptr;
-  TC_RETURN_IF(horner(L.X, cc, L.Q0, L.Q1, N, s, &cosB));
-  // sin poly goes to the ping-pong pair not holding cos: use P0/P1 (real halves)
-  TC_RETURN_IF(horner(L.X, cs, L.P0, L.P1, N, s, &sinpoly));
-  double* sinB = (cosB == L.Q0) ? L.Q1 : L.Q0;
-  TC_RETURN_IF(rgemm(L.B, sinpoly, sinB, N, 1.0, 0.0, s));             // sin B = B p(B^2)
-  // U0 = e^{-i mu scale} (cos B - i sin B)
-  const double ph = -mu * scale;
-  if (sq == 0) {
-    TC_RETURN_IF(launch_assemble_cs(cosB, sinB, N, std::cos(ph), std::sin(ph),
-                                    reinterpret_cast<c128*>(U), ldu, N, s));
-  } else {
-    // squarings ping-pong between T (workspace, ld N) and U (ldu); the last lands in U
-    c128* bufs[2] = {L.T, reinterpret_cast<c128*>(U)};
-    int64_t lds[2] = {N, ldu};
-    int cur = (sq % 2 == 0) ? 1 : 0;  // start so that after sq squarings we are in U
-    // T aliases P0/P1, which held the sin polynomial; it is consumed already.
-    TC_RETURN_IF(launch_assemble_cs(cosB, sinB, N, std::cos(ph), std::sin(ph), bufs[cur],
-                                    lds[cur], N, s));
-    for (int q = 0; q < sq; ++q) {
-      const int nxt = cur ^ 1;
-      GemmDesc d;
-      d.M = d.N = d.K = N;
-      d.A = bufs[cur]; d.lda = lds[cur]; d.a_kmaj = false;
-      d.B = bufs[cur]; d.ldb = lds[cur]; d.b_kmaj = true;
-      d.C = bufs[nxt]; d.ldc = lds[nxt];
-      TC_RETURN_IF(gemm_f64(d, s));
-      cur = nxt;
-    }
+  SymProducts g;
+  g.N = N;
+  g.s = s;
+  // U is written last; until then its memory (when it has no columns of the
+  // caller's between its rows) takes the partial sums
+  if (ldu == N) {
+    g.tail = U;
+    g.tail_bytes = size_t(N) * size_t(N) * sizeof(tc_c128);
   }
-  TC_RETURN_IF(launch_symmetrize(reinterpret_cast<c128*>(U), ldu, N, s));
-  return TC_OK;
+  double *C = nullptr, *S = nullptr;
+  TC_RETURN_IF(cos_sin(L, g, cc, cs, &C, &S));
+  // squarings of cos B - i sin B as cos 2B = (C - S)(C + S), sin 2B = 2 S C (C
+  // and S commute): two symmetric real products instead of a complex one
+  double* free_[4];
+  {
+    int k = 0;
+    for (double* p : {L.B, L.X, L.X2, L.X3, L.T, L.W})
+      if (p != C && p != S) free_[k++] = p;
+  }
+  for (int q = 0; q < sq; ++q) {
+    TC_RETURN_IF(launch_diff_sum(C, S, free_[0], free_[1], N, s));
+    TC_RETURN_IF(g.run(free_[0], free_[1], free_[2], 1.0, 0.0));
+    TC_RETURN_IF(g.run(S, C, free_[3], 2.0, 0.0));
+    std::swap(C, free_[2]);
+    std::swap(S, free_[3]);
+  }
+  // U = e^{-i mu dt} (cos - i sin), symmetrised
+  const double ph = -mu * scale * std::ldexp(1.0, sq);
+  return launch_assemble_cs(C, S, N, std::cos(ph), std::sin(ph), reinterpret_cast<c128*>(U), ldu,
+                            N, s);
 }
 
 }  // extern "C"

@@ -73,26 +73,26 @@ __global__ void axpb_identity_kernel(const double* __restrict__ X, int64_t ldx, 
     out[row * ldo + col] = a * X[row * ldx + col] + (row == col ? b : 0.0);
 }
 
-__global__ void assemble_cs_kernel(const double* __restrict__ Cm, const double* __restrict__ Sm,
-                                   int64_t ld, double pr, double pi, c128* __restrict__ U,
-                                   int64_t ldu, int64_t N) {
-  const int64_t col = int64_t(blockIdx.x) * TPB + threadIdx.x;
-  if (col >= N) return;
-  for (int64_t row = blockIdx.y; row < N; row += gridDim.y) {
-    const double c = Cm[row * ld + col], sv = Sm[row * ld + col];
-    // (pr + i pi) (c - i s)
-    U[row * ldu + col] = c128{pr * c + pi * sv, pi * c - pr * sv};
+__global__ void lin_powers_kernel(const double* X, const double* X2, const double* X3,
+                                  int64_t count, int64_t N, LinCoef c0, double* out0, LinCoef c1,
+                                  double* out1, LinCoef c2, double* out2) {
+  const int64_t step = int64_t(gridDim.x) * TPB;
+  for (int64_t e = int64_t(blockIdx.x) * TPB + threadIdx.x; e < count; e += step) {
+    const double x = X[e], x2 = X2[e], x3 = X3[e];
+    const double d = e / N == e % N ? 1.0 : 0.0;
+    if (out0) out0[e] = c0.a[0] * d + c0.a[1] * x + c0.a[2] * x2 + c0.a[3] * x3;
+    if (out1) out1[e] = c1.a[0] * d + c1.a[1] * x + c1.a[2] * x2 + c1.a[3] * x3;
+    if (out2) out2[e] = c2.a[0] * d + c2.a[1] * x + c2.a[2] * x2 + c2.a[3] * x3;
   }
 }
 
-__global__ void symmetrize_kernel(c128* __restrict__ U, int64_t ldu, int64_t N) {
-  const int64_t col = int64_t(blockIdx.x) * TPB + threadIdx.x;
-  if (col >= N) return;
-  for (int64_t row = blockIdx.y; row < col; row += gridDim.y) {
-    const c128 a = U[row * ldu + col], b = U[col * ldu + row];
-    const c128 v{0.5 * (a.re + b.re), 0.5 * (a.im + b.im)};
-    U[row * ldu + col] = v;
-    U[col * ldu + row] = v;
+__global__ void diff_sum_kernel(const double* __restrict__ C, const double* __restrict__ S,
+                                double* __restrict__ D, double* __restrict__ E, int64_t count) {
+  const int64_t step = int64_t(gridDim.x) * TPB;
+  for (int64_t e = int64_t(blockIdx.x) * TPB + threadIdx.x; e < count; e += step) {
+    const double c = C[e], s = S[e];
+    D[e] = c - s;
+    E[e] = c + s;
   }
 }
 
@@ -558,6 +558,44 @@ __device__ __forceinline__ void pair_index(int64_t b, int64_t& bi, int64_t& bj) 
   bi = b - j * (j + 1) / 2;
 }
 
+// One workgroup per tile pair (bi, bj), (bj, bi): both tiles of C and S are read
+// once, along rows, averaged with their transposes, and both tiles of U are
+// written along rows.  HBM-bound: 32 bytes read and written per entry.
+__global__ void assemble_cs_kernel(const double* __restrict__ Cm, const double* __restrict__ Sm,
+                                   int64_t ld, double pr, double pi, c128* __restrict__ U,
+                                   int64_t ldu, int64_t N) {
+  __shared__ double2 t[RT][RT + 1];
+  int64_t bi, bj;
+  pair_index(blockIdx.x, bi, bj);
+  const int tx = threadIdx.x % RT, ty = threadIdx.x / RT;   // 32 x 8
+  for (int r = ty; r < RT; r += TPB / RT) {
+    const int64_t i = bj * RT + r, j = bi * RT + tx;
+    if (i < N && j < N) t[r][tx] = make_double2(Cm[i * ld + j], Sm[i * ld + j]);
+  }
+  __syncthreads();
+  double2 v[RT / (TPB / RT)];
+#pragma unroll
+  for (int q = 0; q < RT / (TPB / RT); ++q) {
+    const int r = ty + q * (TPB / RT);
+    const int64_t i = bi * RT + r, j = bj * RT + tx;
+    if (i < N && j < N) {
+      const double2 b = t[tx][r];
+      const double c = 0.5 * (Cm[i * ld + j] + b.x), s = 0.5 * (Sm[i * ld + j] + b.y);
+      v[q] = make_double2(pr * c + pi * s, pi * c - pr * s);    // (pr + i pi)(c - i s)
+      U[i * ldu + j] = c128{v[q].x, v[q].y};
+    }
+  }
+  if (bi == bj) return;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < RT / (TPB / RT); ++q) t[tx][ty + q * (TPB / RT)] = v[q];
+  __syncthreads();
+  for (int r = ty; r < RT; r += TPB / RT) {
+    const int64_t i = bj * RT + r, j = bi * RT + tx;
+    if (i < N && j < N) U[i * ldu + j] = c128{t[r][tx].x, t[r][tx].y};
+  }
+}
+
 template <typename E>
 __global__ void renorm_kernel(E* __restrict__ rho, int64_t ld, int64_t N, const double* scratch) {
   __shared__ double2 tA[RT][RT + 1];
@@ -888,6 +926,11 @@ dim3 grid2(int64_t cols, int64_t rows) {
   return dim3(unsigned(gx > 0 ? gx : 1), unsigned(gy > 0 ? gy : 1));
 }
 
+unsigned grid1(int64_t count) {
+  const int64_t g = (count + TPB - 1) / TPB;
+  return unsigned(g < 16384 ? g : 16384);
+}
+
 int64_t npairs_of(int64_t N) {
   const int64_t T = (N + RT - 1) / RT;
   return T * (T + 1) / 2;
@@ -913,14 +956,26 @@ int launch_axpb_identity(const double* X, int64_t ldx, double a, double b, doubl
 int launch_assemble_cs(const double* Cm, const double* Sm, int64_t ld, double pr, double pi,
                        c128* U, int64_t ldu, int64_t N, hipStream_t s) {
   if (N == 0) return TC_OK;
-  hipLaunchKernelGGL(assemble_cs_kernel, grid2(N, N), dim3(TPB), 0, s, Cm, Sm, ld, pr, pi, U, ldu, N);
+  hipLaunchKernelGGL(assemble_cs_kernel, dim3(unsigned(npairs_of(N))), dim3(TPB), 0, s, Cm, Sm, ld,
+                     pr, pi, U, ldu, N);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }
 
-int launch_symmetrize(c128* U, int64_t ldu, int64_t N, hipStream_t s) {
+int launch_lin_powers(const double* X, const double* X2, const double* X3, int64_t N, LinCoef c0,
+                      double* out0, LinCoef c1, double* out1, LinCoef c2, double* out2,
+                      hipStream_t s) {
   if (N == 0) return TC_OK;
-  hipLaunchKernelGGL(symmetrize_kernel, grid2(N, N), dim3(TPB), 0, s, U, ldu, N);
+  hipLaunchKernelGGL(lin_powers_kernel, dim3(grid1(N * N)), dim3(TPB), 0, s, X, X2, X3, N * N, N,
+                     c0, out0, c1, out1, c2, out2);
+  TC_TRY_HIP(hipGetLastError());
+  return TC_OK;
+}
+
+int launch_diff_sum(const double* C, const double* S, double* D, double* E, int64_t N,
+                    hipStream_t s) {
+  if (N == 0) return TC_OK;
+  hipLaunchKernelGGL(diff_sum_kernel, dim3(grid1(N * N)), dim3(TPB), 0, s, C, S, D, E, N * N);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }

@@ -811,7 +811,10 @@ int launch2(const GemmDesc& d, hipStream_t s) {
     // the K-split 128 x 128 tiles give the shorter critical path.)
     const int env = variant_for(-1);
     const int64_t t128 = ((d.M + 127) / 128) * ((d.N + 127) / 128);
-    const int v = env >= 0 ? env : (t128 <= 16 ? 2 : DefaultVariant<T, CPLX>::value);
+    // Real products (U formation, a tile is a quarter of the work): up to 100
+    // tiles, or one round when there is no buffer for K ranges.
+    const int64_t few = CPLX ? 16 : d.tail_ws ? 100 : 256;
+    const int v = env >= 0 ? env : (t128 <= few ? 2 : DefaultVariant<T, CPLX>::value);
     switch (v) {
       case 1: return launch_shape<T, CPLX, false, true, typename V::V1>(d, s);
       case 2: return launch_shape<T, CPLX, false, true, typename V::V2>(d, s);

@@ -11,12 +11,22 @@ int launch_ham_fill(const ModelArgs& m, double* H, int64_t ldh, hipStream_t s);
 int launch_axpb_identity(const double* X, int64_t ldx, double a, double b,
                          double* out, int64_t ldo, int64_t N, hipStream_t s);
 
-// U = ph * (Cm - i Sm) (complex from two real N x N), ph = (ph_re, ph_im).
+// U = ph * (Cm - i Sm) (complex from two real N x N, each taken as
+// (A + A^T) / 2), ph = (ph_re, ph_im): U is exactly symmetric.
 int launch_assemble_cs(const double* Cm, const double* Sm, int64_t ld, double ph_re,
                        double ph_im, c128* U, int64_t ldu, int64_t N, hipStream_t s);
 
-// U <- (U + U^T) / 2 in place (complex, square).
-int launch_symmetrize(c128* U, int64_t ldu, int64_t N, hipStream_t s);
+// Up to three combinations out = a0 I + a1 X + a2 X2 + a3 X3 of the real N x N
+// matrices X, X2, X3 (ld N) in one pass; an output may be one of the inputs, a
+// null one is left out.
+struct LinCoef { double a[4]; };
+int launch_lin_powers(const double* X, const double* X2, const double* X3, int64_t N, LinCoef c0,
+                      double* out0, LinCoef c1, double* out1, LinCoef c2, double* out2,
+                      hipStream_t s);
+
+// D = C - S, E = C + S (real N x N, ld N).
+int launch_diff_sum(const double* C, const double* S, double* D, double* E, int64_t N,
+                    hipStream_t s);
 
 // Copies with type conversion; ld in elements.
 int launch_copy_c128_to_c64(const c128* src, int64_t lds, c64* dst, int64_t ldd,

@@ -176,6 +176,41 @@ def test_expm_matches_eigendecomposition(n, c, dt, seed):
     assert np.all(Ug[k[:, None] != k[None, :]] == 0)                 # exact zeros across sectors
 
 
+@pytest.mark.parametrize("n,c,dt,pad", [(7, 9, 0.05, 0), (8, 5, 0.05, 0), (8, 5, 0.05, 3),
+                                        (8, 3, 0.6, 0), (6, 2, 0.4, 1)])
+def test_expm_symmetric_products_tiles(n, c, dt, pad):
+    """N = 1280 (64 x 64 tiles), 1536 (128 x 128 tiles whose last round's partial
+    sums lie in U, or with U's rows padded 64 x 64 tiles and no such buffer),
+    1024 and 192 with squarings: the whole U against the oracle, exactly
+    symmetric, and the padding columns untouched."""
+    inst = ti.random_model(n, c, 21)
+    m = pipeline.model_of(inst)
+    H = pipeline.hamiltonian(m)
+    buf = torch.full((m.N, m.N + pad), 7.0, dtype=torch.complex128, device=DEV)
+    lo, hi = tcm.tc_spectral_bounds(m)
+    tcm.tc_expm(H, dt, lo, hi, buf)
+    U = buf[:, :m.N].cpu().numpy()
+    Ho = omodel.hamiltonian(n, c, inst.g, inst.omega_a)
+    norm = abs(dt) * (c + n + 1)
+    assert np.max(np.abs(U - oev.propagator(Ho, dt))) <= 1e-13 * max(1.0, norm)
+    assert np.array_equal(U, U.T)
+    assert bool((buf[:, m.N:] == 7.0).all())
+
+
+def test_expm_odd_dimension():
+    """One excitation sector of odd dimension (35 states): ragged tiles of the
+    symmetric products."""
+    inst = ti.random_model(6, 1, 22)
+    m = pipeline.model_of(inst)
+    _, U = pipeline.sector_propagator(m, 3, 0.3)
+    st = tcm.tc_sector_states(m, 3)
+    assert st.size == 35
+    Ho = omodel.hamiltonian(6, 1, inst.g, inst.omega_a)
+    Uo = oev.propagator(Ho, 0.3)[np.ix_(st, st)]
+    Ug = U.cpu().numpy()
+    assert np.max(np.abs(Ug - Uo)) <= 1e-13 and np.array_equal(Ug, Ug.T)
+
+
 @pytest.mark.parametrize("n,c,dt", [(3, 3, 0.01), (5, 4, 0.05), (6, 3, 0.05)])
 def test_expm_taylor10_matches_oracle(n, c, dt):
     inst = ti.random_model(n, c, 11)
