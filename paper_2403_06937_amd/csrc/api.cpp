@@ -9,6 +9,7 @@
 #include "common.h"
 #include "gemm_mfma.h"
 #include "kernels.h"
+#include "sym_products.h"
 
 namespace tcm {
 
@@ -46,31 +47,6 @@ int make_model_args(const tc_model* m, ModelArgs* out) {
 // ----------------------------------------------------------------- expm
 namespace {
 
-// Every matrix of the exponential is a polynomial in the symmetric B, so every
-// product is symmetric too: only its upper tile triangle is multiplied, and
-// mirrored.  A, B, C: N x N row-major, ld N.
-struct SymProducts {
-  int64_t N = 0;
-  void* tail = nullptr; size_t tail_bytes = 0;   // partial sums of a last round
-  hipStream_t s = nullptr;
-  // C = alpha A B + beta C + gamma I
-  int run(const double* A, const double* B, double* C, double alpha, double beta,
-          double gamma = 0.0) const {
-    GemmDesc d;
-    d.M = d.N = d.K = N;
-    d.A = A; d.lda = N; d.a_kmaj = false;
-    d.B = B; d.ldb = N; d.b_kmaj = true;
-    d.C = C; d.ldc = N;
-    d.alpha_re = alpha;
-    if (beta != 0.0) { d.Cin = C; d.ldcin = N; d.beta_re = beta; }
-    d.gamma = gamma;
-    d.complex = false;
-    d.herm = true;
-    d.tail_ws = tail; d.tail_ws_bytes = tail_bytes;
-    return gemm_f64(d, s);
-  }
-};
-
 // Six N x N matrices.
 struct ExpmLayout {
   double *B, *X, *X2, *X3, *T, *W;
@@ -93,12 +69,7 @@ int cos_sin(const ExpmLayout& L, const SymProducts& g, const std::vector<double>
             const std::vector<double>& cs, double** cosB, double** sinB) {
   const int64_t N = g.N;
   hipStream_t s = g.s;
-  // coefficients from .. to of a block a[3b] + a[3b + 1] X + a[3b + 2] X^2 (+ a[9] X^3)
-  auto lin = [](const std::vector<double>& a, int from, int to) {
-    LinCoef c{{0.0, 0.0, 0.0, 0.0}};
-    for (int k = from; k <= to && k < int(a.size()); ++k) c.a[k % 3 + (k == 9 ? 3 : 0)] = a[k];
-    return c;
-  };
+  auto lin = [](const std::vector<double>& a, int from, int to) { return block_coef(a, from, to); };
   TC_RETURN_IF(g.run(L.B, L.B, L.X, 1.0, 0.0));
   TC_RETURN_IF(g.run(L.X, L.X, L.X2, 1.0, 0.0));
   TC_RETURN_IF(g.run(L.X, L.X2, L.X3, 1.0, 0.0));
@@ -323,19 +294,8 @@ int tc_expm(const double* H, int64_t N, int64_t ldh, double dt, double lam_lo, d
     // the helper reads with ld = ldh and writes with ld = N
     TC_RETURN_IF(launch_axpb_identity(H, ldh, scale, -mu * scale, L.B, N, N, s));
   }
-  std::vector<double> cc(kc + 1), cs(ks + 1);
-  {
-    double f = 1.0;   // (2k)!
-    for (int k = 0; k <= kc; ++k) {
-      if (k > 0) f *= double(2 * k - 1) * double(2 * k);
-      cc[k] = (k % 2 ? -1.0 : 1.0) / f;
-    }
-    f = 1.0;          // (2k+1)!
-    for (int k = 0; k <= ks; ++k) {
-      if (k > 0) f *= double(2 * k) * double(2 * k + 1);
-      cs[k] = (k % 2 ? -1.0 : 1.0) / f;
-    }
-  }
+  std::vector<double> cc, cs;
+  taylor_cos_sin(kc, ks, &cc, &cs);
   SymProducts g;
   g.N = N;
   g.s = s;

@@ -835,36 +835,52 @@ __global__ void accumulate_c64_kernel(const c64* __restrict__ T, int64_t ldt, c1
   }
 }
 
-__global__ void minus_i_shifted_kernel(ModelArgs m, const double* __restrict__ H, int64_t ldh,
-                                       double mu, double scale, c128* __restrict__ out,
-                                       int64_t ldo) {
+__global__ void shifted_h_kernel(ModelArgs m, const double* __restrict__ H, int64_t ldh, double mu,
+                                 double scale, double* __restrict__ out) {
   const int64_t col = int64_t(blockIdx.x) * TPB + threadIdx.x;
   if (col >= m.N) return;
   for (int64_t row = blockIdx.y; row < m.N; row += gridDim.y) {
     double h = H[row * ldh + col];
     if (row == col) h -= m.omega_c * double(exc_number(row, m.n)) + mu;
-    out[row * ldo + col] = c128{0.0, -h * scale};
+    out[row * m.N + col] = h * scale;
   }
 }
 
-__global__ void scale_c128_kernel(c128* __restrict__ X, int64_t ld, double a, int64_t N) {
-  const int64_t col = int64_t(blockIdx.x) * TPB + threadIdx.x;
-  if (col >= N) return;
-  for (int64_t row = blockIdx.y; row < N; row += gridDim.y) {
-    c128 v = X[row * ld + col];
-    X[row * ld + col] = c128{a * v.re, a * v.im};
+// One workgroup per tile pair: both tiles of M are read along rows and both
+// tiles of the planes written along rows.
+__global__ void sym_planes_kernel(const c128* __restrict__ M, int64_t N, double a,
+                                  double* __restrict__ re, double* __restrict__ im) {
+  __shared__ double2 tA[RT][RT + 1];
+  __shared__ double2 tB[RT][RT + 1];
+  int64_t bi, bj;
+  pair_index(blockIdx.x, bi, bj);
+  const int tx = threadIdx.x % RT, ty = threadIdx.x / RT;   // 32 x 8
+  for (int r = ty; r < RT; r += TPB / RT) {
+    const int64_t i = bi * RT + r, j = bj * RT + tx;
+    if (i < N && j < N) { const c128 v = M[i * N + j]; tA[r][tx] = make_double2(v.re, v.im); }
+    const int64_t i2 = bj * RT + r, j2 = bi * RT + tx;
+    if (i2 < N && j2 < N) { const c128 v = M[i2 * N + j2]; tB[r][tx] = make_double2(v.re, v.im); }
   }
-}
-
-__global__ void identity_c128_kernel(c128* __restrict__ X, int64_t ld, int64_t N) {
-  const int64_t col = int64_t(blockIdx.x) * TPB + threadIdx.x;
-  if (col >= N) return;
-  for (int64_t row = blockIdx.y; row < N; row += gridDim.y)
-    X[row * ld + col] = c128{row == col ? 1.0 : 0.0, 0.0};
+  __syncthreads();
+  for (int r = ty; r < RT; r += TPB / RT) {
+    const int64_t i = bi * RT + r, j = bj * RT + tx;
+    if (i < N && j < N) {
+      const double2 p = tA[r][tx], q = tB[tx][r];
+      re[i * N + j] = 0.5 * a * (p.x + q.x);
+      im[i * N + j] = 0.5 * a * (p.y + q.y);
+    }
+    const int64_t i2 = bj * RT + r, j2 = bi * RT + tx;
+    if (bi != bj && i2 < N && j2 < N) {
+      const double2 p = tB[r][tx], q = tA[tx][r];
+      re[i2 * N + j2] = 0.5 * a * (p.x + q.x);
+      im[i2 * N + j2] = 0.5 * a * (p.y + q.y);
+    }
+  }
 }
 
 // One workgroup per parameter: blocks 0..n-1 give dL/dg_i, n..2n-1 dL/ddelta_i.
-__global__ void grad_trace_kernel(ModelArgs m, const c128* __restrict__ G, int64_t ld, double pr,
+__global__ void grad_trace_kernel(ModelArgs m, const double* __restrict__ Gr,
+                                  const double* __restrict__ Gi, int stride, int64_t ld, double pr,
                                   double pi, double dt, double* __restrict__ grad_g,
                                   double* __restrict__ grad_delta) {
   __shared__ double sh[TPB / 64];
@@ -880,15 +896,15 @@ __global__ void grad_trace_kernel(ModelArgs m, const c128* __restrict__ G, int64
       if (!(uint64_t(s) & bit)) continue;
       const int64_t t = s + per - int64_t(bit);
       const double w = sqrt(double((s >> n) + 1));
-      const c128 a = G[s * ld + t], b = G[t * ld + s];
-      const double zr = w * (a.re + b.re), zi = w * (a.im + b.im);
+      const int64_t a = (s * ld + t) * stride, b = (t * ld + s) * stride;
+      const double zr = w * (Gr[a] + Gr[b]), zi = w * (Gi[a] + Gi[b]);
       acc += pr * zi + pi * zr;
     }
   } else {
     for (int64_t s = threadIdx.x; s < m.N; s += TPB) {
       if (!(uint64_t(s) & bit)) continue;
-      const c128 a = G[s * ld + s];
-      acc += pr * a.im + pi * a.re;
+      const int64_t a = s * (ld + 1) * stride;
+      acc += pr * Gi[a] + pi * Gr[a];
     }
   }
   const double tot = block_sum(acc, sh);
@@ -1226,33 +1242,27 @@ int launch_accumulate_c64(const c64* T, int64_t ldt, c128* M, int64_t ldm, int64
   return TC_OK;
 }
 
-int launch_minus_i_shifted(const ModelArgs& m, const double* H, int64_t ldh, double mu,
-                           double scale, c128* out, int64_t ldo, hipStream_t s) {
+int launch_shifted_h(const ModelArgs& m, const double* H, int64_t ldh, double mu, double scale,
+                     double* out, int64_t N, hipStream_t s) {
   if (m.N == 0) return TC_OK;
-  hipLaunchKernelGGL(minus_i_shifted_kernel, grid2(m.N, m.N), dim3(TPB), 0, s, m, H, ldh, mu,
-                     scale, out, ldo);
+  hipLaunchKernelGGL(shifted_h_kernel, grid2(N, N), dim3(TPB), 0, s, m, H, ldh, mu, scale, out);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }
 
-int launch_scale_c128(c128* X, int64_t ld, double a, int64_t N, hipStream_t s) {
+int launch_sym_planes(const c128* M, int64_t N, double a, double* re, double* im, hipStream_t s) {
   if (N == 0) return TC_OK;
-  hipLaunchKernelGGL(scale_c128_kernel, grid2(N, N), dim3(TPB), 0, s, X, ld, a, N);
+  hipLaunchKernelGGL(sym_planes_kernel, dim3(unsigned(npairs_of(N))), dim3(TPB), 0, s, M, N, a, re,
+                     im);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }
 
-int launch_identity_c128(c128* X, int64_t ld, int64_t N, hipStream_t s) {
-  if (N == 0) return TC_OK;
-  hipLaunchKernelGGL(identity_c128_kernel, grid2(N, N), dim3(TPB), 0, s, X, ld, N);
-  TC_TRY_HIP(hipGetLastError());
-  return TC_OK;
-}
-
-int launch_grad_trace(const ModelArgs& m, const c128* G, int64_t ld, double ph_re, double ph_im,
-                      double dt, double* grad_g, double* grad_delta, hipStream_t s) {
-  hipLaunchKernelGGL(grad_trace_kernel, dim3(unsigned(2 * m.n)), dim3(TPB), 0, s, m, G, ld, ph_re,
-                     ph_im, dt, grad_g, grad_delta);
+int launch_grad_trace(const ModelArgs& m, const double* Gr, const double* Gi, int stride,
+                      int64_t ld, double ph_re, double ph_im, double dt, double* grad_g,
+                      double* grad_delta, hipStream_t s) {
+  hipLaunchKernelGGL(grad_trace_kernel, dim3(unsigned(2 * m.n)), dim3(TPB), 0, s, m, Gr, Gi, stride,
+                     ld, ph_re, ph_im, dt, grad_g, grad_delta);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }

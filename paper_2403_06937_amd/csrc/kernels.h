@@ -101,20 +101,19 @@ int launch_excitation_op_c64(const ModelArgs& m, c64* O, int64_t ld, hipStream_t
 // M += T (complex64 into complex128).
 int launch_accumulate_c64(const c64* T, int64_t ldt, c128* M, int64_t ldm, int64_t N,
                           hipStream_t s);
-// out = -i (H - w_c N_exc - mu I) * scale  (complex128 from real FP64): the
-// rotating-frame generator H' = H - w_c N_exc, shifted by mu.
-int launch_minus_i_shifted(const ModelArgs& m, const double* H, int64_t ldh, double mu,
-                           double scale, c128* out, int64_t ldo, hipStream_t s);
-// X *= a (complex128, in place).
-int launch_scale_c128(c128* X, int64_t ld, double a, int64_t N, hipStream_t s);
-// X = I (complex128).
-int launch_identity_c128(c128* X, int64_t ld, int64_t N, hipStream_t s);
+// out = (H - w_c N_exc - mu I) * scale (N x N, ld N): the rotating-frame
+// Hamiltonian H' = H - w_c N_exc, shifted by mu.
+int launch_shifted_h(const ModelArgs& m, const double* H, int64_t ldh, double mu, double scale,
+                     double* out, int64_t N, hipStream_t s);
+// re, im: the planes of a (M + M^T) / 2 (N x N, ld N).
+int launch_sym_planes(const c128* M, int64_t N, double a, double* re, double* im, hipStream_t s);
 // Parameter gradients from G (scaled by the complex factor ph):
 //   grad_g[i]     = 2 dt Im( ph sum_{s,t} sqrt(m+1) (G_st + G_ts) )   over the (s, t)
 //                   pairs coupled by g_i (s = (m, l) with l_i = 1, t = (m+1, l - e_i))
 //   grad_delta[i] = 2 dt Im( ph sum_{s: l_i = 1} G_ss )
-int launch_grad_trace(const ModelArgs& m, const c128* G, int64_t ld, double ph_re, double ph_im,
-                      double dt, double* grad_g, double* grad_delta, hipStream_t s);
+// Gr, Gi: the parts of entry (s, t) at (s ld + t) stride.
+int launch_grad_trace(const ModelArgs& m, const double* Gr, const double* Gi, int stride,
+                      int64_t ld, double ph_re, double ph_im, double dt, double* grad_g, double* grad_delta, hipStream_t s);
 
 // ---- excitation-sector stepping (sectors.hip)
 // dst[i][j] = ph * src[map[ro + i]][map[co + j]] - sub_identity * [ro + i == co + j]

@@ -60,6 +60,23 @@ def test_adjoint_fp64_small(state, steps, every, sectors):
     assert np.max(np.abs(gd - do)) <= 1e-9 * scale
 
 
+@pytest.mark.parametrize("n,c,dt", [(3, 2, 1.5), (3, 2, 4.0), (2, 10, 0.7)])
+def test_adjoint_scaled_and_squared(n, c, dt):
+    """Strong couplings and long steps (N = 24, 24, 44): the derivative of the
+    exponential with one to several squarings, FP64 gradients to 1e-9 of the
+    oracle's Daleckii-Krein gradient."""
+    inst = ti.random_model(n, c, 64, delta_sigma=0.05, state="gaussian")
+    inst.g = inst.g * 20
+    steps = 4
+    L, gg, gd = gpu_grad(inst, dt, steps, 2, tcm.TC_GEMM_F64, torch.complex128)
+    Lo, go, do = ograd.grad_daleckii_krein(inst.n, inst.c, inst.g, inst.omega_a - 1, inst.rho0(),
+                                           steps * dt)
+    scale = max(np.max(np.abs(go)), np.max(np.abs(do)))
+    assert abs(L - Lo) < 1e-12
+    assert np.max(np.abs(gg - go)) <= 1e-9 * scale
+    assert np.max(np.abs(gd - do)) <= 1e-9 * scale
+
+
 @pytest.mark.parametrize("sectors", [False, True])
 def test_adjoint_zero_steps(sectors):
     inst = ti.random_model(2, 2, 62, state="gaussian")
