@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <type_traits>
 #include "ham_entry.h"
+#include "readout.h"
 
 namespace tcm {
 namespace {
@@ -466,71 +467,29 @@ __global__ void damp_cavity_reg_kernel(E* __restrict__ rho, int64_t ld, int n, i
 }
 
 // ------------------------------------------------------- per-step readout
-// map == NULL: rho is in the basis order; else basis state s sits at row and
-// column map[s] of rho (the excitation-sorted order of the sector stepper, or
-// the order of one sector, where states outside it have map[s] = -1).
-// Writes pop = sum_s |l(s)| Re rho_ss, pdist[m] = sum_{photon(s) = m} Re rho_ss
-// and pstate[m] = P({m>) of Eq. (13) (m photons and n - m excited atoms),
-// m = 0 .. min(n, c); each output may be NULL.
 template <typename E>
-__device__ __forceinline__ void readout_body(int n, int c, const E* __restrict__ rho, int64_t ld,
-                                             const int32_t* __restrict__ map,
-                                             double* __restrict__ pop, double* __restrict__ pdist,
-                                             double* __restrict__ pstate, double* sh) {
-  const int64_t per = int64_t(1) << n;
-  const uint64_t mask = uint64_t(per - 1);
-  double tot = 0.0;
-  for (int mm = 0; mm <= c; ++mm) {
-    double part = 0.0, ex = 0.0, st = 0.0;
-    for (int64_t s = mm * per + threadIdx.x; s < (mm + 1) * per; s += TPB) {
-      const int64_t q = map ? int64_t(map[s]) : s;
-      if (q < 0) continue;                     // state outside a one-sector rho
-      const double d = double(rho[q * ld + q].re);
-      const int pc = popc64(uint64_t(s) & mask);
-      part += d;
-      ex += double(pc) * d;
-      if (pc == n - mm) st += d;
-    }
-    if (pdist) {
-      const double pm = block_sum(part, sh);
-      if (threadIdx.x == 0) pdist[mm] = pm;
-    }
-    if (pstate && mm <= n) {
-      const double pm = block_sum(st, sh);
-      if (threadIdx.x == 0) pstate[mm] = pm;
-    }
-    tot += ex;
-  }
-  const double t = block_sum(tot, sh);
-  if (threadIdx.x == 0 && pop) *pop = t;
+__global__ void __launch_bounds__(READOUT_NT)
+readout_kernel(ModelArgs m, const E* __restrict__ rho, int64_t ld,
+               const int32_t* __restrict__ map, const int32_t* __restrict__ off, int k,
+               double* __restrict__ pop, double* __restrict__ pdist,
+               double* __restrict__ pstate) {
+  __shared__ double sh[READOUT_LDS];
+  readout_body(m.n, m.c, rho, ld, map, off, k, pop, pdist, pstate, sh);
 }
 
+// Each workgroup advances its own item's record index, after the body's
+// barrier, by which point every thread has read it.
 template <typename E>
-__global__ void readout_kernel(ModelArgs m, const E* __restrict__ rho, int64_t ld,
-                               const int32_t* __restrict__ map, double* __restrict__ pop,
-                               double* __restrict__ pdist, double* __restrict__ pstate) {
-  __shared__ double sh[TPB / 64];
-  readout_body(m.n, m.c, rho, ld, map, pop, pdist, pstate, sh);
-}
-
-// advance (a launch of one item only): the kernel also moves the record
-// index on, after the block's last barrier, by which point every thread has
-// read it; a captured step then needs no separate counter launch.
-template <typename E>
-__global__ void grouped_readout_kernel(const ReadoutItem* __restrict__ items,
-                                       int* __restrict__ counter, int advance) {
-  __shared__ double sh[TPB / 64];
+__global__ void __launch_bounds__(READOUT_NT)
+grouped_readout_kernel(const ReadoutItem* __restrict__ items, int* counter) {
+  __shared__ double sh[READOUT_LDS];
   const ReadoutItem it = items[blockIdx.x];
-  const int64_t r = *counter;
+  const int64_t r = counter[blockIdx.x];
   const int ns = (it.n < it.c ? it.n : it.c) + 1;
-  readout_body(it.n, it.c, static_cast<const E*>(it.rho), it.ld, it.map,
+  readout_body(it.n, it.c, static_cast<const E*>(it.rho), it.ld, it.map, it.off, it.k,
                it.pop ? it.pop + r : nullptr, it.pdist ? it.pdist + r * (it.c + 1) : nullptr,
                it.pstate ? it.pstate + r * ns : nullptr, sh);
-  if (advance && threadIdx.x == 0) *counter = int(r) + 1;
-}
-
-__global__ void advance_counter_kernel(int* counter) {
-  if (threadIdx.x == 0) *counter += 1;
+  if (threadIdx.x == 0) counter[blockIdx.x] = int(r) + 1;
 }
 
 // ---------------------------------------------------- FP64 renormalisation
@@ -1111,17 +1070,19 @@ int launch_dissipation_c64(const ModelArgs& m, c64* rho, int64_t ld, double dt, 
 }
 
 int launch_readout_c128(const ModelArgs& m, const c128* rho, int64_t ld, double* pop,
-                        double* pdist, hipStream_t s, const int32_t* map, double* pstate) {
-  hipLaunchKernelGGL(readout_kernel<c128>, dim3(1), dim3(TPB), 0, s, m, rho, ld, map, pop, pdist,
-                     pstate);
+                        double* pdist, hipStream_t s, const int32_t* map, double* pstate,
+                        const int32_t* off, int k) {
+  hipLaunchKernelGGL(readout_kernel<c128>, dim3(1), dim3(READOUT_NT), 0, s, m, rho, ld, map, off, k,
+                     pop, pdist, pstate);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }
 
 int launch_readout_c64(const ModelArgs& m, const c64* rho, int64_t ld, double* pop,
-                       double* pdist, hipStream_t s, const int32_t* map, double* pstate) {
-  hipLaunchKernelGGL(readout_kernel<c64>, dim3(1), dim3(TPB), 0, s, m, rho, ld, map, pop, pdist,
-                     pstate);
+                       double* pdist, hipStream_t s, const int32_t* map, double* pstate,
+                       const int32_t* off, int k) {
+  hipLaunchKernelGGL(readout_kernel<c64>, dim3(1), dim3(READOUT_NT), 0, s, m, rho, ld, map, off, k,
+                     pop, pdist, pstate);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }
@@ -1198,24 +1159,14 @@ int launch_split_bf16(const float* x, int64_t count, uint16_t* hi, uint16_t* lo,
 }
 
 int launch_grouped_readout(const ReadoutItem* items_dev, int count, bool c128_storage,
-                           int* counter, hipStream_t s, bool advance) {
+                           int* counter, hipStream_t s) {
   if (count == 0) return TC_OK;
-  if (advance && count != 1) {
-    set_error("readout: only a single-item launch can advance the record index");
-    return TC_ERR_INVALID_ARGUMENT;
-  }
   if (c128_storage)
-    hipLaunchKernelGGL(grouped_readout_kernel<c128>, dim3(unsigned(count)), dim3(TPB), 0, s,
-                       items_dev, counter, advance ? 1 : 0);
+    hipLaunchKernelGGL(grouped_readout_kernel<c128>, dim3(unsigned(count)), dim3(READOUT_NT), 0, s,
+                       items_dev, counter);
   else
-    hipLaunchKernelGGL(grouped_readout_kernel<c64>, dim3(unsigned(count)), dim3(TPB), 0, s,
-                       items_dev, counter, advance ? 1 : 0);
-  TC_TRY_HIP(hipGetLastError());
-  return TC_OK;
-}
-
-int launch_advance_counter(int* counter, hipStream_t s) {
-  hipLaunchKernelGGL(advance_counter_kernel, dim3(1), dim3(64), 0, s, counter);
+    hipLaunchKernelGGL(grouped_readout_kernel<c64>, dim3(unsigned(count)), dim3(READOUT_NT), 0, s,
+                       items_dev, counter);
   TC_TRY_HIP(hipGetLastError());
   return TC_OK;
 }

@@ -9,6 +9,7 @@
 #include "common.h"
 #include "gemm_mfma.h"
 #include "gemm_bf16.h"
+#include "gemm_small.h"
 #include "kernels.h"
 #include "profile.h"
 
@@ -40,8 +41,9 @@ struct InstPlan {
   // Each sector's positions are padded to a multiple of the product tile
   // (padding states hold exact zeros), so every block product is whole tiles.
   // stepping within one excitation sector (tc_evolve_sector): rho, U are the
-  // d_k x d_k blocks; inv maps every basis state to its position or -1
+  // d_k x d_k blocks; sec_off[m]: first position of the states with m photons
   int in_sector = -1;
+  int32_t* sec_off = nullptr;
   bool sectors = false;
   int64_t Np = 0;                    // padded dimension of the sorted order
   int svar = 2;                      // tile shape of the grouped block products (1: 128, 2: 64)
@@ -206,7 +208,8 @@ void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelAr
     plan_sectors(o, ar, p);
     return;
   }
-  if (p->in_sector >= 0) p->inv = static_cast<int32_t*>(ar.take(size_t(m.N) * 4));
+  if (p->in_sector >= 0)
+    p->sec_off = static_cast<int32_t*>(ar.take(std::max(size_t(m.N), size_t(m.c) + 2) * 4));
   if (o.gemm_mode == TC_GEMM_F64) {
     if (o.rho_dtype == TC_C128) {
       p->rho = in.rho; p->ldr = in.ldr; p->rho_converted = false;
@@ -236,9 +239,9 @@ int readout(const InstPlan& p, const tc_evolve_opts& o, double* pop, double* pdi
             double* pstate, hipStream_t s) {
   if (o.gemm_mode == TC_GEMM_F64)
     return launch_readout_c128(p.m, static_cast<const c128*>(p.rho), p.ldr, pop, pdist, s,
-                               p.inv, pstate);
+                               p.inv, pstate, p.sec_off, p.in_sector);
   return launch_readout_c64(p.m, static_cast<const c64*>(p.rho), p.ldr, pop, pdist, s, p.inv,
-                            pstate);
+                            pstate, p.sec_off, p.in_sector);
 }
 
 // Sector order: rebuilds the lower block triangle of rho hat from the upper one
@@ -338,9 +341,19 @@ void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDe
 //   rotating: X = rho + D rho,    rho' = X + X conj(D)         (U~ = I + D symmetric)
 // rho' is Hermitian: unless full_product is set, the second product forms only
 // its upper tile triangle and mirrors it.
-int step_mfma(InstPlan& p, const tc_evolve_opts& o, hipStream_t s) {
+// ro: records of the state before the step, read along with the first product
+// (only when takes_record(p, o)).
+int step_mfma(InstPlan& p, const tc_evolve_opts& o, const SmallReadout* ro, hipStream_t s) {
   GemmDesc g1, g2;
   step_descs(p, o, g1, g2);
+  if (ro) {
+    if (o.gemm_mode == TC_GEMM_F64) {
+      TC_RETURN_IF(small_gemm<double>(g1, ro, s));
+      return gemm_f64(g2, s);
+    }
+    TC_RETURN_IF(small_gemm<float>(g1, ro, s));
+    return gemm_f32(g2, s);
+  }
   if (o.gemm_mode == TC_GEMM_F64) {
     TC_RETURN_IF(gemm_f64(g1, s));
     TC_RETURN_IF(gemm_f64(g2, s));
@@ -515,22 +528,25 @@ int prepare_sectors(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o,
   return TC_OK;
 }
 
-// One-sector run: position of every basis state in the sector's order (-1 outside).
-int upload_sector_map(InstPlan& p, hipStream_t s) {
+// One-sector run: the states are ordered by increasing index, so by photon
+// number m, C(n, k - m) of them each; the first position of each m.
+int upload_sector_offsets(InstPlan& p, hipStream_t s) {
   const int n = p.m.n, k = p.in_sector;
-  const uint64_t mask = (uint64_t(1) << n) - 1;
-  std::vector<int32_t> map(p.m.N, -1);
-  int32_t pos = 0;
-  for (int64_t st = 0; st < p.m.N; ++st)
-    if (int(st >> n) + __builtin_popcountll(uint64_t(st) & mask) == k) map[st] = pos++;
-  TC_TRY_HIP(hipMemcpyAsync(p.inv, map.data(), map.size() * 4, hipMemcpyHostToDevice, s));
-  TC_TRY_HIP(hipStreamSynchronize(s));   // map is host memory of this call
+  std::vector<int32_t> off(p.m.c + 2, 0);
+  for (int mm = 0; mm <= p.m.c; ++mm) {
+    const int e = k - mm;                    // excited atoms
+    int64_t cnt = e >= 0 && e <= n ? 1 : 0;
+    for (int q = 1; cnt && q <= e; ++q) cnt = cnt * (n - e + q) / q;
+    off[mm + 1] = off[mm] + int32_t(cnt);
+  }
+  TC_TRY_HIP(hipMemcpyAsync(p.sec_off, off.data(), off.size() * 4, hipMemcpyHostToDevice, s));
+  TC_TRY_HIP(hipStreamSynchronize(s));   // off is host memory of this call
   return TC_OK;
 }
 
 int prepare(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipStream_t s) {
   if (p.sectors) return prepare_sectors(p, in, o, s);
-  if (p.in_sector >= 0) TC_RETURN_IF(upload_sector_map(p, s));
+  if (p.in_sector >= 0) TC_RETURN_IF(upload_sector_offsets(p, s));
   TC_TRY_HIP(hipMemsetAsync(p.scratch, 0, 4 * sizeof(double), s));
   // master state
   if (p.rho_converted) {
@@ -598,7 +614,16 @@ int finish(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipStrea
   return TC_OK;
 }
 
-int step(InstPlan& p, const tc_evolve_opts& o, hipStream_t s) {
+// Whether a step's first product is a small one, whose launch can also read the
+// records of the state it multiplies.
+bool takes_record(const InstPlan& p, const tc_evolve_opts& o) {
+  if (p.sectors || o.gemm_mode == TC_GEMM_SPLIT_BF16) return false;
+  GemmDesc g1, g2;
+  step_descs(p, o, g1, g2);
+  return small_product(g1, o.gemm_mode == TC_GEMM_F64);
+}
+
+int step(InstPlan& p, const tc_evolve_opts& o, const SmallReadout* ro, hipStream_t s) {
   if (p.sectors && o.gemm_mode == TC_GEMM_SPLIT_BF16) {
     TC_RETURN_IF(split_grouped_run(p.sg1, s));
     return split_grouped_run(p.sg2, s);
@@ -610,7 +635,7 @@ int step(InstPlan& p, const tc_evolve_opts& o, hipStream_t s) {
   if (o.gemm_mode == TC_GEMM_SPLIT_BF16)
     return step_split(static_cast<c64*>(p.rho), p.ldr, static_cast<c64*>(p.X), p.ldx, p.N,
                       o.frame == TC_FRAME_ROTATING, o.full_product == 0, p.planes, s);
-  return step_mfma(p, o, s);
+  return step_mfma(p, o, ro, s);
 }
 
 // The step pattern repeats with period lcm(record_every, renorm_every); a
@@ -706,39 +731,49 @@ int evolve_one(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipS
   const int64_t chunk = graph_chunk(o, rec);
   const bool graph = o.use_graph && !in.checkpoints && chunk <= 256 && o.steps >= chunk;
   const bool c128s = o.gemm_mode == TC_GEMM_F64;
+  SmallReadout ro;
+  ro.item.rho = p.rho; ro.item.ld = p.ldr; ro.item.n = p.m.n; ro.item.c = p.m.c;
+  ro.item.pop = in.pop_out; ro.item.pdist = in.photon_dist_out;
+  ro.item.pstate = in.photon_state_out;
+  ro.item.map = p.inv;
+  ro.item.off = p.sec_off; ro.item.k = p.in_sector;
   if (graph && rec) {
     // the record index lives on the device, so that a captured chunk replays
-    ReadoutItem ri;
-    ri.rho = p.rho; ri.ld = p.ldr; ri.n = p.m.n; ri.c = p.m.c;
-    ri.pop = in.pop_out; ri.pdist = in.photon_dist_out; ri.pstate = in.photon_state_out;
-    ri.map = p.inv;
-    TC_TRY_HIP(hipMemcpyAsync(p.ritem, &ri, sizeof(ri), hipMemcpyHostToDevice, s));
+    ro.counter = p.counter;
+    TC_TRY_HIP(hipMemcpyAsync(p.ritem, &ro.item, sizeof(ro.item), hipMemcpyHostToDevice, s));
     TC_TRY_HIP(hipMemsetAsync(p.counter, 0, sizeof(int), s));
-    TC_TRY_HIP(hipStreamSynchronize(s));   // ri is host memory of this call
-    TC_RETURN_IF(launch_grouped_readout(p.ritem, 1, c128s, p.counter, s, true));
-  } else if (rec) {
-    TC_RETURN_IF(readout(p, o, in.pop_out, in.photon_dist_out, in.photon_state_out, s));
+    TC_TRY_HIP(hipStreamSynchronize(s));   // ro is host memory of this call
   }
+  auto record = [&](int64_t r, hipStream_t q) -> int {
+    if (graph) return launch_grouped_readout(p.ritem, 1, c128s, p.counter, q);
+    return readout(p, o, in.pop_out ? in.pop_out + r : nullptr,
+                   in.photon_dist_out ? in.photon_dist_out + r * c1 : nullptr,
+                   in.photon_state_out ? in.photon_state_out + r * ns : nullptr, q);
+  };
+  // A small instance's record is read by the next step's first product (the
+  // state does not change in between), the last one after the last step.  A
+  // captured chunk begins and ends with a record due, being a whole number of
+  // record periods.
+  const bool along = rec && takes_record(p, o);
+  if (rec && !(along && o.steps > 0)) TC_RETURN_IF(record(0, s));
   if (in.checkpoints) TC_RETURN_IF(copy_checkpoint(p, in, o, 0, 0.0, s));
   auto one_step = [&](int64_t st, hipStream_t q) -> int {
-    TC_RETURN_IF(step(p, o, q));
+    if (along && (st - 1) % o.record_every == 0) {
+      ro.index = (st - 1) / o.record_every;
+      TC_RETURN_IF(step(p, o, &ro, q));
+    } else {
+      TC_RETURN_IF(step(p, o, nullptr, q));
+    }
     TC_RETURN_IF(dissipate(p, o, q));
     if (o.renorm_every > 0 && st % o.renorm_every == 0) TC_RETURN_IF(renorm(p, o, q));
-    if (rec && st % o.record_every == 0) {
-      if (graph) {
-        TC_RETURN_IF(launch_grouped_readout(p.ritem, 1, c128s, p.counter, q, true));
-      } else {
-        const int64_t r = st / o.record_every;
-        TC_RETURN_IF(readout(p, o, in.pop_out ? in.pop_out + r : nullptr,
-                             in.photon_dist_out ? in.photon_dist_out + r * c1 : nullptr,
-                             in.photon_state_out ? in.photon_state_out + r * ns : nullptr, q));
-      }
-    }
+    if (rec && !along && st % o.record_every == 0) TC_RETURN_IF(record(st / o.record_every, q));
     if (in.checkpoints && st % o.checkpoint_every == 0)
       TC_RETURN_IF(copy_checkpoint(p, in, o, st / o.checkpoint_every, double(st) * o.dt, q));
     return TC_OK;
   };
   TC_RETURN_IF(run_steps(one_step, o.steps, chunk, graph, s));
+  if (along && o.steps > 0 && o.steps % o.record_every == 0)
+    TC_RETURN_IF(record(o.steps / o.record_every, s));
   return finish(p, in, o, s);
 }
 
@@ -748,10 +783,21 @@ int evolve_one(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipS
 // tiles, the readout is one launch for all instances (record index kept in a
 // device counter), and with use_graph the launches of a chunk of steps are
 // captured once in a hipGraph and replayed.
+// Dense instances of a batch that take the small product kernel, as they do on
+// their own: always up to N = 192 (16 instances of N = 160: 82 -> 47 us a step
+// in FP64, 62 -> 36 in FP32, N = 64: 44 -> 24), and up to N = 512 where the
+// 64 x 64 tiles would be ragged (the persistent kernel) or fewer than the CUs.  A
+// chip full of whole 64 x 64 tiles reads less per product: 30 instances of
+// N = 256 take 176 us against 185.
+bool batch_small(int64_t N, int64_t tiles64) {
+  return N <= 192 || (N <= 512 && (N % 64 != 0 || tiles64 < 256));
+}
+
 struct BatchBufs {
   char* items = nullptr;          // 8 groups of count GroupItem descriptors
+  char* small = nullptr;          // 2 groups of count small products
   ReadoutItem* ritems = nullptr;  // count readout descriptors
-  int* counter = nullptr;         // record index
+  int* counter = nullptr;         // record index of each instance
 };
 
 bool use_batched(int count, const tc_evolve_opts& o) {
@@ -764,8 +810,9 @@ void plan_batch(Arena& ar, int count, int64_t sector_items, BatchBufs* b) {
   const size_t blocks = std::max(grouped_bytes(int(sector_items)),
                                  split_grouped_bytes(int(sector_items)));
   b->items = static_cast<char*>(ar.take(std::max(8 * grouped_bytes(count), 4 * blocks)));
+  b->small = static_cast<char*>(ar.take(2 * small_grouped_bytes(count)));
   b->ritems = static_cast<ReadoutItem*>(ar.take(size_t(count) * sizeof(ReadoutItem)));
-  b->counter = static_cast<int*>(ar.take(sizeof(int)));
+  b->counter = static_cast<int*>(ar.take(size_t(count) * sizeof(int)));
 }
 
 void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDesc& g2) {
@@ -808,8 +855,13 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   // tile with the unchecked tile (fewer registers), the rest persistently.
   // By sectors, the block products of every instance (whole tiles of the
   // instance's padding) go into one group per tile shape, largest K first.
-  std::vector<GemmDesc> d1[3][2], d2[3][2];
+  // Small dense instances (batch_small) go into one group of small products
+  // per product phase.
+  std::vector<GemmDesc> d1[3][2], d2[3][2], s1, s2;
   std::vector<SplitProduct> sp1, sp2;
+  int64_t tiles64 = 0;
+  for (int b = 0; b < count; ++b)
+    if (plans[b].N <= 512) tiles64 += ((plans[b].N + 63) / 64) * ((plans[b].N + 63) / 64);
   for (int b = 0; b < count; ++b) {
     const int v = sec ? plans[b].svar : tile_variant_for(plans[b].N, f64);
     if (sec && split) {
@@ -821,6 +873,11 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     } else {
       GemmDesc g1, g2;
       step_descs(plans[b], o, g1, g2);
+      if (batch_small(plans[b].N, tiles64)) {
+        s1.push_back(g1);
+        s2.push_back(g2);
+        continue;
+      }
       const int edge = v == 1 ? 128 : 64;
       const int e = plans[b].N % edge == 0 ? 0 : 1;
       d1[v][e].push_back(g1);
@@ -829,6 +886,8 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   }
   auto by_k = [](const auto& x, const auto& y) { return x.K > y.K; };
   auto by_kp = [](const SplitProduct& x, const SplitProduct& y) { return x.Kp > y.Kp; };
+  std::stable_sort(s1.begin(), s1.end(), by_k);
+  std::stable_sort(s2.begin(), s2.end(), by_k);
   std::stable_sort(sp1.begin(), sp1.end(), by_kp);
   std::stable_sort(sp2.begin(), sp2.end(), by_kp);
   GroupedProducts G1[3][2], G2[3][2];
@@ -843,6 +902,9 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     TC_RETURN_IF(split_grouped_build(sp2, it, &S2, s));
     it += gstep;
   }
+  SmallGroup T1, T2;
+  TC_RETURN_IF(small_grouped_build(s1, f64, bb.small, &T1, s));
+  TC_RETURN_IF(small_grouped_build(s2, f64, bb.small + small_grouped_bytes(count), &T2, s));
   for (int v = 1; v <= 2; ++v)
     for (int e = 0; e < 2; ++e) {
       if (d1[v][e].empty()) continue;
@@ -867,18 +929,16 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     ri[b].pdist = inst[b].photon_dist_out;
     ri[b].map = sec ? plans[b].inv : nullptr;
     ri[b].pstate = inst[b].photon_state_out;
+    ri[b].off = nullptr; ri[b].k = 0;
     rec = rec || inst[b].pop_out || inst[b].photon_dist_out || inst[b].photon_state_out;
     ckpt = ckpt || inst[b].checkpoints;
   }
   TC_TRY_HIP(hipMemcpyAsync(bb.ritems, ri.data(), ri.size() * sizeof(ReadoutItem),
                             hipMemcpyHostToDevice, s));
-  TC_TRY_HIP(hipMemsetAsync(bb.counter, 0, sizeof(int), s));
+  TC_TRY_HIP(hipMemsetAsync(bb.counter, 0, size_t(count) * sizeof(int), s));
   TC_TRY_HIP(hipStreamSynchronize(s));   // ri is host memory of this call
   const bool c128s = f64;
-  if (rec) {
-    TC_RETURN_IF(launch_grouped_readout(bb.ritems, count, c128s, bb.counter, s));
-    TC_RETURN_IF(launch_advance_counter(bb.counter, s));
-  }
+  if (rec) TC_RETURN_IF(launch_grouped_readout(bb.ritems, count, c128s, bb.counter, s));
   for (int b = 0; b < count; ++b)
     if (inst[b].checkpoints) TC_RETURN_IF(copy_checkpoint(plans[b], inst[b], o, 0, 0.0, s));
 
@@ -886,16 +946,16 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     TC_RETURN_IF(split_grouped_run(S1, q));
     for (int v = 1; v <= 2; ++v)
       for (int e = 0; e < 2; ++e) TC_RETURN_IF(grouped_run(G1[v][e], q));
+    TC_RETURN_IF(small_grouped_run(T1, q));
     TC_RETURN_IF(split_grouped_run(S2, q));
     for (int v = 1; v <= 2; ++v)
       for (int e = 0; e < 2; ++e) TC_RETURN_IF(grouped_run(G2[v][e], q));
+    TC_RETURN_IF(small_grouped_run(T2, q));
     for (int b = 0; b < count; ++b) TC_RETURN_IF(dissipate(plans[b], o, q));
     if (o.renorm_every > 0 && st % o.renorm_every == 0)
       for (int b = 0; b < count; ++b) TC_RETURN_IF(renorm(plans[b], o, q));
-    if (rec && st % o.record_every == 0) {
+    if (rec && st % o.record_every == 0)
       TC_RETURN_IF(launch_grouped_readout(bb.ritems, count, c128s, bb.counter, q));
-      TC_RETURN_IF(launch_advance_counter(bb.counter, q));
-    }
     if (ckpt && o.checkpoint_every > 0 && st % o.checkpoint_every == 0)
       for (int b = 0; b < count; ++b)
         if (inst[b].checkpoints)

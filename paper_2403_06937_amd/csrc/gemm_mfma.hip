@@ -21,6 +21,7 @@
 //     contiguous range of tiles, walked in groups of GROUP_M tile rows, so
 //     tiles that share A rows / B columns share that XCD's L2.
 #include "gemm_mfma.h"
+#include "gemm_small.h"
 #include "profile.h"
 
 #include <algorithm>
@@ -802,6 +803,8 @@ int variant_for(int default_variant) {
 template <typename T, bool CPLX>
 int launch2(const GemmDesc& d, hipStream_t s) {
   typedef Variants<T, CPLX> V;
+  if constexpr (CPLX)
+    if (variant_for(-1) < 0 && small_product(d, sizeof(T) == 8)) return small_gemm<T>(d, nullptr, s);
   if (!d.a_kmaj && d.b_kmaj) {
     // A product of at most 16 tiles of 128 x 128 (N <= 512 when square)
     // takes 64 x 64 tiles (variant 2 in every element type): four times the

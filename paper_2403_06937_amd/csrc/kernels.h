@@ -58,16 +58,18 @@ int launch_dissipation_c64(const ModelArgs& m, c64* rho, int64_t ld, double dt, 
 // pstate != NULL, pstate[m] = P({m>) of Eq. (13), the sum over the states with
 // m photons and n - m excited atoms (m = 0..min(n, c)).  With a map, basis
 // state s is row and column map[s] of rho (sector-sorted order).
+// off, k: rho holds the states of sector k only, those with m photons at
+// positions off[m] .. off[m + 1] - 1.
 int launch_readout_c128(const ModelArgs& m, const c128* rho, int64_t ld, double* pop,
                         double* pdist, hipStream_t s, const int32_t* map = nullptr,
-                        double* pstate = nullptr);
+                        double* pstate = nullptr, const int32_t* off = nullptr, int k = 0);
 int launch_readout_c64(const ModelArgs& m, const c64* rho, int64_t ld, double* pop,
                        double* pdist, hipStream_t s, const int32_t* map = nullptr,
-                       double* pstate = nullptr);
+                       double* pstate = nullptr, const int32_t* off = nullptr, int k = 0);
 
 // Readout of many instances in one launch (one workgroup each): record index
-// r = *counter; pop[r], pdist[r*(c+1) + m] and pstate[r*(min(n,c)+1) + m] as
-// above.  advance_counter adds 1.
+// r = counter[i] of item i; pop[r], pdist[r*(c+1) + m] and
+// pstate[r*(min(n,c)+1) + m] as above; counter[i] is then advanced.
 struct ReadoutItem {
   const void* rho;
   int64_t ld;
@@ -76,11 +78,11 @@ struct ReadoutItem {
   double* pdist;    // may be NULL
   const int32_t* map;   // NULL, or the position of each basis state in rho (sector order)
   double* pstate;   // may be NULL
+  const int32_t* off;   // one sector k only: first position of each photon number, or NULL
+  int k;
 };
-// advance: also move the record index on (count must be 1)
 int launch_grouped_readout(const ReadoutItem* items_dev, int count, bool c128_storage,
-                           int* counter, hipStream_t s, bool advance = false);
-int launch_advance_counter(int* counter, hipStream_t s);
+                           int* counter, hipStream_t s);
 
 // Hermitise and divide by Re Tr rho, in FP64.  scratch: device double[2]
 // (trace, non-finite flag).  For c64 storage the arithmetic is FP64 too.

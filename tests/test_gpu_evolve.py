@@ -341,6 +341,42 @@ def test_partial_round_ranges_across_tiles(n, c, mode, frame, rdt, tol, full):
     assert err < tol and perr < tol
 
 
+@pytest.mark.parametrize("n,c", [(1, 8), (2, 4), (3, 10), (5, 4), (5, 9), (4, 20), (6, 12), (8, 3)])
+@pytest.mark.parametrize("mode,frame,rdt,tol", [
+    (tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-10),
+    (tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5)])
+@pytest.mark.parametrize("full,graph", [(False, False), (True, False), (False, True)])
+def test_small_product_kernel(n, c, mode, frame, rdt, tol, full, graph):
+    """N = 18 .. 1024 through the small product kernel (K a multiple of 8 and
+    not, ragged 16 x 16 and 32 x 32 tiles, triangle or every tile), with the
+    records read along with the next step's first product: every record of
+    every kind over 37 steps, record_every = 3, and the final rho, against the
+    oracle."""
+    inst = ti.random_model(n, c, 520 + n, state="gaussian")
+    dt, steps, every = 0.05, 37, 3
+    m = pipeline.model_of(inst)
+    _, U = pipeline.propagator(m, dt)
+    rho = _dev(inst.rho0(), rdt)
+    pop, pd, _, ps = pipeline.evolve(m, U, rho, steps, dt, mode, frame, 10, every,
+                                     record_photons=True, record_states=True, full_product=full,
+                                     use_graph=graph, no_resident=True)
+    torch.cuda.synchronize()
+    pop, pd, ps = pop.cpu().numpy(), pd.cpu().numpy(), ps.cpu().numpy()
+    P = oev.SectorPropagator(n, c, inst.g, inst.omega_a)
+    O = excitation_op(n, c)
+    assert pop.shape == (steps // every + 1,)
+    for r in range(pop.size):
+        d = np.abs(P.psi(inst.psi0, r * every * dt)) ** 2
+        diag = np.diag(d) if n < 6 else None
+        assert abs(pop[r] - float(np.sum(O * d))) <= tol, r
+        assert np.max(np.abs(pd[r] - d.reshape(c + 1, -1).sum(1))) <= tol, r
+        if diag is not None:
+            assert np.max(np.abs(ps[r] - oobs.photon_state_probability(diag, n, c))) <= tol, r
+    err = max_entry_error_pure(rho.cpu().numpy().astype(np.complex128),
+                               P.psi(inst.psi0, steps * dt))
+    assert err < tol
+
+
 def mid_instance(seed=0):
     """C3-shaped but smaller: n=7, c=5 (N=768), 2 photons x Haar product."""
     return ti.random_model(7, 5, 100 + seed, state="haar2")
