@@ -277,6 +277,44 @@ def test_eq13_readings_shapes(n, c):
     assert np.max(np.abs(got["dicke"] - oobs.dicke_probability(rho, n, c))) < 1e-14
 
 
+@pytest.mark.parametrize("n,c,pad,dtype", [(1, 0, 0, np.complex128), (2, 10, 3, np.complex128),
+                                           (6, 19, 0, np.complex64), (8, 7, 1, np.complex128),
+                                           (9, 4, 0, np.complex64)])
+def test_observables_passes(n, c, pad, dtype):
+    """One tile, ragged tiles with a row stride, and more tile pairs than pass 1
+    has workgroups (N = 2048 and 2560; 1280 has fewer): every output against the
+    oracle's definitions on the same entries, a Hermiticity error in one far
+    corner, non-finite entries in the first and last tile, and a scalars-only
+    call."""
+    m = pipeline.model_of(ti.random_model(n, c, 16))
+    N = m.N
+    rho = ti.random_density(N, 6, rank=2)
+    rho[0, N - 1] += 1e-3j
+    rho = rho.astype(dtype)
+    buf = torch.zeros((N, N + pad), dtype=_dev(rho[:1]).dtype, device=DEV)
+    buf[:, :N] = torch.from_numpy(rho).to(DEV)
+    view = buf[:, :N]
+    got = pipeline.observables(m, view)
+    r = rho.astype(np.complex128)
+    inv = oobs.invariants(r)
+    for k in ("trace_re", "trace_im", "purity", "herm_err"):
+        assert abs(got[k] - inv[k]) < 1e-13, k
+    assert np.max(np.abs(got["atom_pop"] - oobs.atom_populations(r, n, c))) < 1e-13
+    assert np.max(np.abs(got["photon_dist"] - oobs.photon_distribution(r, n, c))) < 1e-13
+    assert np.max(np.abs(got["exc_dist"] - oobs.excitation_distribution(r, n, c))) < 1e-13
+    assert np.max(np.abs(got["photon_state"] - oobs.photon_state_probability(r, n, c))) < 1e-13
+    assert np.max(np.abs(got["dicke"] - oobs.dicke_probability(r, n, c))) < 1e-13
+    assert got["nonfinite"] == 0.0
+    sc = torch.zeros(8, dtype=torch.float64, device=DEV)
+    tcm.tc_observables(m, view, sc)
+    assert sc[2].item() == got["purity"] and sc[3].item() == got["herm_err"]
+    for i, j in ((0, 0), (N - 1, 0), (0, N - 1)):
+        keep = view[i, j].item()
+        view[i, j] = float("inf")
+        assert pipeline.observables(m, view)["nonfinite"] == 1.0
+        view[i, j] = keep
+
+
 @pytest.mark.parametrize("kind,peak", [(tcm.TC_PROBE_BF16_16X16X32, 2.5e15),
                                        (tcm.TC_PROBE_BF16_32X32X16, 2.5e15),
                                        (tcm.TC_PROBE_F64_16X16X4, 78.6e12)])
