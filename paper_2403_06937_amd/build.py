@@ -21,7 +21,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libtcm.so")
 
-SOURCES = ["gemm_mfma.hip", "gemm_small.hip", "gemm_bf16.hip", "elementwise.hip", "api.cpp", "evolve.cpp",
+SOURCES = ["gemm_mfma.hip", "gemm_small.hip", "gemm_bf16.hip", "gemm_bf16_small.hip", "elementwise.hip", "api.cpp", "evolve.cpp",
            "profile.cpp", "backward.cpp", "autotune.cpp", "sectors.hip", "noalloc.hip", "resident.hip", "probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -10,6 +10,7 @@
 #include "gemm_mfma.h"
 #include "gemm_bf16.h"
 #include "gemm_small.h"
+#include "gemm_bf16_small.h"
 #include "kernels.h"
 #include "profile.h"
 
@@ -617,7 +618,8 @@ int finish(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipStrea
 // Whether a step's first product is a small one, whose launch can also read the
 // records of the state it multiplies.
 bool takes_record(const InstPlan& p, const tc_evolve_opts& o) {
-  if (p.sectors || o.gemm_mode == TC_GEMM_SPLIT_BF16) return false;
+  if (p.sectors) return false;
+  if (o.gemm_mode == TC_GEMM_SPLIT_BF16) return split_small_step(p.N);
   GemmDesc g1, g2;
   step_descs(p, o, g1, g2);
   return small_product(g1, o.gemm_mode == TC_GEMM_F64);
@@ -634,7 +636,7 @@ int step(InstPlan& p, const tc_evolve_opts& o, const SmallReadout* ro, hipStream
   }
   if (o.gemm_mode == TC_GEMM_SPLIT_BF16)
     return step_split(static_cast<c64*>(p.rho), p.ldr, static_cast<c64*>(p.X), p.ldx, p.N,
-                      o.frame == TC_FRAME_ROTATING, o.full_product == 0, p.planes, s);
+                      o.frame == TC_FRAME_ROTATING, o.full_product == 0, p.planes, ro, s);
   return step_mfma(p, o, ro, s);
 }
 

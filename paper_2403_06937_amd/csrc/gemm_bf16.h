@@ -48,8 +48,11 @@ int split_state(const c64* rho, int64_t ld, int64_t N, const SplitPlanes& p, hip
 // One step rho <- op rho op^dag (lab) or rho <- (I + D) rho (I + D)^dag (rotating).
 // herm: rho is Hermitian, so the second product forms its upper tile triangle
 // and mirrors it.
+// ro: records of the state before the step, read along with the first product
+// (small steps only), or NULL.
+struct SmallReadout;
 int step_split(c64* rho, int64_t ldr, c64* X, int64_t ldx, int64_t N, bool rotating, bool herm,
-               const SplitPlanes& p, hipStream_t s);
+               const SplitPlanes& p, const SmallReadout* ro, hipStream_t s);
 
 // Planes of rows x ld bf16 (ld a multiple of SPLIT_BK) carved from a workspace.
 Planes4 split_take_planes(Arena& ar, int64_t rows, int64_t ld);

@@ -40,6 +40,7 @@
 // FP32 result, and the hi/lo planes of the result (row-major or transposed)
 // for the next product.
 #include "gemm_bf16.h"
+#include "gemm_bf16_small.h"
 #include "profile.h"
 
 #include <atomic>
@@ -767,14 +768,21 @@ split_tail_kernel(const SplitParams p, int base, int S, int kc, float* __restric
   split_tile<2, 4, 4, 2, true, true>(q, tm, tn, sA, sB, acc + size_t(blockIdx.x) * TILE_ACC);
 }
 
-__global__ void __launch_bounds__(512, 1)
+// Workgroup (i, h): waves 2h and 2h + 1 of tile i, whose outputs and staging are
+// their own; a quarter of a tile per workgroup spreads the slots' reads and the
+// epilogue over four times the CUs (step at N = 768 68 -> 56 us, 1280 97 -> 91).
+// Equal K ranges over all CUs, as the FP64 product takes for its last round, lost
+// here: N = 1536 158 us against 133, 2304 332 against 309, and the triangle's 136
+// tiles at N = 2048 gained nothing, since the shorter ranges share fewer operand
+// rows in L2.
+__global__ void __launch_bounds__(128)
 split_tail_finish_kernel(const SplitParams p, int base, int S, const float* __restrict__ acc) {
-  __shared__ SplitLds sA, sB;
+  __shared__ u4 stage[2 * 1024];
   constexpr int NT = 512, WM = 4, WN = 2, WGN = 4;
   const int i = blockIdx.x;
   int tm, tn;
   launch_tile(p, base + i, tm, tn);
-  const int tid = threadIdx.x;
+  const int tid = blockIdx.y * 128 + threadIdx.x;      // thread of the tile
   const int wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
   f4 acc_re[WM][WN], acc_im[WM][WN];
@@ -797,9 +805,8 @@ split_tail_finish_kernel(const SplitParams p, int base, int S, const float* __re
       }
   }
   const int64_t m0 = int64_t(tm) * SPLIT_BM, n0 = int64_t(tn) * SPLIT_BN;
-  u4* stage = (wave < 4 ? &sA[0][0][0] : &sB[0][0][0]) + (wave & 3) * 1024;
   split_epilogue_staged(p, acc_re, acc_im, m0 + wm * WM * 16, n0 + wn * WN * 16,
-                        p.herm && tm != tn, stage);
+                        p.herm && tm != tn, stage + (threadIdx.x >> 6) * 1024);
 }
 
 // Many split products in one launch, one workgroup per tile of the
@@ -968,8 +975,8 @@ int run_split(const Planes4& A, const Planes4& B, int64_t M, int64_t N, int64_t 
       hipLaunchKernelGGL(split_tail_kernel, dim3(unsigned(tail * S)), dim3(512), 0, s, q, base, S,
                          int(kc), tail_acc);
       TC_TRY_HIP(hipGetLastError());
-      hipLaunchKernelGGL(split_tail_finish_kernel, dim3(unsigned(tail)), dim3(512), 0, s, q, base,
-                         S, static_cast<const float*>(tail_acc));
+      hipLaunchKernelGGL(split_tail_finish_kernel, dim3(unsigned(tail), 4), dim3(128), 0, s, q,
+                         base, S, static_cast<const float*>(tail_acc));
       TC_TRY_HIP(hipGetLastError());
       return TC_OK;
     }
@@ -1070,7 +1077,27 @@ int split_state(const c64* rho, int64_t ld, int64_t N, const SplitPlanes& p, hip
 }
 
 int step_split(c64* rho, int64_t ldr, c64* X, int64_t ldx, int64_t N, bool rotating, bool herm,
-               const SplitPlanes& p, hipStream_t s) {
+               const SplitPlanes& p, const SmallReadout* ro, hipStream_t s) {
+  if (split_small_step(N) && split_variant() == 0) {
+    SplitSmall g;
+    g.M = g.N = N;
+    g.Kp = round_up(N, SPLIT_BK);
+    g.A = p.opA.base; g.lda = p.opA.ld;
+    g.B = p.Rt.base; g.ldb = p.Rt.ld;
+    if (rotating) { g.Cin = rho; g.ldcin = ldr; g.Cf = X; g.ldcf = ldx; }
+    g.P = p.X.base; g.ldp = p.X.ld;
+    TC_RETURN_IF(split_small(g, ro, s));
+    SplitSmall h;
+    h.M = h.N = N;
+    h.Kp = g.Kp;
+    h.A = p.X.base; h.lda = p.X.ld;
+    h.B = p.opB.base; h.ldb = p.opB.ld;
+    if (rotating) { h.Cin = X; h.ldcin = ldx; }
+    h.Cf = rho; h.ldcf = ldr;
+    h.P = p.Rt.base; h.ldp = p.Rt.ld; h.p_trans = 1;
+    h.herm = herm;
+    return split_small(h, nullptr, s);
+  }
   // X = op rho (+ rho): A = split(op), B = split(rho^T); planes of X row-major
   TC_RETURN_IF(run_split(p.opA, p.Rt, N, N, p.Np, 1.f, 0.f, rotating ? 1.f : 0.f, 0.f,
                          rotating ? rho : nullptr, ldr, false, rotating ? X : nullptr, ldx,

@@ -344,11 +344,13 @@ def test_partial_round_ranges_across_tiles(n, c, mode, frame, rdt, tol, full):
 @pytest.mark.parametrize("n,c", [(1, 8), (2, 4), (3, 10), (5, 4), (5, 9), (4, 20), (6, 12), (8, 3)])
 @pytest.mark.parametrize("mode,frame,rdt,tol", [
     (tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-10),
-    (tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5)])
+    (tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5),
+    (tcm.TC_GEMM_SPLIT_BF16, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5)])
 @pytest.mark.parametrize("full,graph", [(False, False), (True, False), (False, True)])
 def test_small_product_kernel(n, c, mode, frame, rdt, tol, full, graph):
-    """N = 18 .. 1024 through the small product kernel (K a multiple of 8 and
-    not, ragged 16 x 16 and 32 x 32 tiles, triangle or every tile), with the
+    """N = 18 .. 1024 through the small product kernels (K a multiple of 8 and
+    not, ragged 16 x 16 and 32 x 32 tiles, triangle or every tile; split-BF16
+    up to its N = 640), with the
     records read along with the next step's first product: every record of
     every kind over 37 steps, record_every = 3, and the final rho, against the
     oracle."""
