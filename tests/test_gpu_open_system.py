@@ -150,6 +150,36 @@ def test_damping_alone_n10_against_oracle(pad):
         assert torch.all(buf[:, N:] == 0)                # the padding column is untouched
 
 
+@pytest.mark.parametrize("n,c,pad", [(1, 3, 0), (2, 7, 1), (3, 8, 0), (4, 15, 0), (5, 2, 3),
+                                     (6, 1, 0), (7, 3, 0), (8, 2, 1), (3, 17, 0)])
+@pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
+def test_damping_alone_shapes(n, c, pad, dtype):
+    """U = I: the damping channels alone where the six-atom tile is ragged
+    (N = 8 .. 96, odd strides), where it holds fewer than six atoms, seven and
+    eight atoms (a second pass), and cavity chains in registers of 8 and 16
+    elements and beyond.  FP64: each entry is rounded a few times per channel,
+    1e-14 of the largest entry; FP32 as above."""
+    inst = _open(n, c, 95 + n, 0.06, 0.09)
+    m = pipeline.model_of(inst)
+    N = m.N
+    dt = 0.7
+    f64 = dtype == torch.complex128
+    rho0 = inst.rho0().astype(np.complex128 if f64 else np.complex64)
+    U = torch.eye(N, dtype=torch.complex128, device="cuda")
+    buf = torch.zeros((N, N + pad), dtype=dtype, device="cuda")
+    rho = buf[:, :N]
+    rho.copy_(torch.from_numpy(rho0))
+    pipeline.evolve(m, U, rho, 1, dt, tcm.TC_GEMM_F64 if f64 else tcm.TC_GEMM_F32,
+                    tcm.TC_FRAME_LAB, 0, 1)
+    torch.cuda.synchronize()
+    ref = oos.dissipation(rho0.astype(np.complex128), n, c, 0.06, 0.09, dt)
+    got = rho.cpu().numpy().astype(np.complex128)
+    scale = np.max(np.abs(ref))
+    assert np.max(np.abs(ref - rho0)) > 0.02 * scale
+    assert np.max(np.abs(got - ref)) <= (1e-14 if f64 else 4e-6) * scale
+    assert torch.all(buf[:, N:] == 0)
+
+
 @pytest.mark.parametrize("mode,dtype", [(tcm.TC_GEMM_F32, torch.complex64),
                                         (tcm.TC_GEMM_F64, torch.complex128)])
 def test_batched_equals_single(mode, dtype):
