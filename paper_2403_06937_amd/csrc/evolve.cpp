@@ -699,30 +699,43 @@ int run_steps(StepFn&& one_step, int64_t steps, int64_t chunk, bool graph, hipSt
   return rc;
 }
 
-// One small instance stepped densely, without checkpoints or damping, runs
-// in the LDS-resident kernel (one launch for all steps).
+// A small instance (or one small sector) stepped densely, without checkpoints
+// or damping, runs in the LDS-resident kernel (one launch for all steps).
 bool use_resident(const InstPlan& p, const tc_instance& in, const tc_evolve_opts& o) {
-  if (o.no_resident || p.sectors || p.in_sector >= 0 || in.checkpoints) return false;
+  if (o.no_resident || p.sectors || in.checkpoints) return false;
   if (p.m.kappa > 0.0 || p.m.gamma > 0.0) return false;
+  if (p.m.c > 63) return false;            // a lane per photon number for the records
   if (o.gemm_mode == TC_GEMM_F64) return p.N <= RESIDENT_MAX_N_C128;
   if (o.gemm_mode == TC_GEMM_F32) return p.N <= RESIDENT_MAX_N_C64;
   return false;
 }
 
-int evolve_resident(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipStream_t s) {
-  TC_RETURN_IF(prepare(p, in, o, s));
-  ResidentArgs a;
-  a.op = p.op; a.ldop = p.ldop;
-  a.rho = p.rho; a.ldr = p.ldr;
-  a.rot = o.frame == TC_FRAME_ROTATING;
+ResidentItem resident_item(const InstPlan& p, const tc_instance& in) {
+  ResidentItem it;
+  it.n = p.m.n; it.c = p.m.c; it.N = int(p.N);
+  it.k = p.in_sector;
+  it.omega_c = p.m.omega_c;
+  it.U = reinterpret_cast<const c128*>(in.U); it.ldu = in.ldu;
+  it.rho = in.rho; it.ldr = in.ldr;
+  it.pop = in.pop_out; it.pdist = in.photon_dist_out; it.pstate = in.photon_state_out;
+  it.scratch = p.scratch;
+  return it;
+}
+
+ResidentRun resident_run(const tc_evolve_opts& o) {
+  ResidentRun a;
   a.steps = o.steps;
+  a.dt = o.dt;
+  a.rot = o.frame == TC_FRAME_ROTATING;
+  a.rho_c128 = o.rho_dtype == TC_C128;
   a.renorm_every = o.renorm_every;
   a.record_every = o.record_every;
-  a.pop = in.pop_out; a.pdist = in.photon_dist_out; a.pstate = in.photon_state_out;
-  a.scratch = p.scratch;
-  TC_RETURN_IF(o.gemm_mode == TC_GEMM_F64 ? launch_resident_c128(p.m, a, s)
-                                          : launch_resident_c64(p.m, a, s));
-  return finish(p, in, o, s);
+  return a;
+}
+
+int evolve_resident(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipStream_t s) {
+  const ResidentItem it = resident_item(p, in);
+  return launch_resident(o.gemm_mode == TC_GEMM_F64, it.N, &it, nullptr, 1, resident_run(o), s);
 }
 
 int evolve_one(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipStream_t s) {
@@ -799,6 +812,7 @@ struct BatchBufs {
   char* items = nullptr;          // 8 groups of count GroupItem descriptors
   char* small = nullptr;          // 2 groups of count small products
   ReadoutItem* ritems = nullptr;  // count readout descriptors
+  ResidentItem* resident = nullptr;   // count LDS-resident instances
   int* counter = nullptr;         // record index of each instance
 };
 
@@ -815,6 +829,7 @@ void plan_batch(Arena& ar, int count, int64_t sector_items, BatchBufs* b) {
   b->small = static_cast<char*>(ar.take(2 * small_grouped_bytes(count)));
   b->ritems = static_cast<ReadoutItem*>(ar.take(size_t(count) * sizeof(ReadoutItem)));
   b->counter = static_cast<int*>(ar.take(size_t(count) * sizeof(int)));
+  b->resident = static_cast<ResidentItem*>(ar.take(size_t(count) * sizeof(ResidentItem)));
 }
 
 void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDesc& g2) {
@@ -848,6 +863,24 @@ int64_t sector_items(const tc_instance* inst, int count, const tc_evolve_opts& o
 int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int count,
                    const tc_evolve_opts& o, const BatchBufs& bb, hipStream_t s) {
   const bool f64 = o.gemm_mode == TC_GEMM_F64;
+  // a batch of nothing but LDS-resident instances: one workgroup each, all steps
+  // in one launch (30 of N = 32: per-step launches took 23 us a step).  With
+  // full_product a batch keeps the per-step products, whose bits equal those of
+  // its members' own runs with no_resident.
+  bool all = o.full_product == 0;
+  for (int b = 0; b < count; ++b) all = all && use_resident(plans[b], inst[b], o);
+  if (all) {
+    std::vector<ResidentItem> items(count);
+    int maxN = 0;
+    for (int b = 0; b < count; ++b) {
+      items[b] = resident_item(plans[b], inst[b]);
+      maxN = std::max(maxN, items[b].N);
+    }
+    TC_TRY_HIP(hipMemcpyAsync(bb.resident, items.data(), items.size() * sizeof(ResidentItem),
+                              hipMemcpyHostToDevice, s));
+    TC_TRY_HIP(hipStreamSynchronize(s));   // items is host memory of this call
+    return launch_resident(f64, maxN, nullptr, bb.resident, count, resident_run(o), s);
+  }
   const bool sec = o.sectors != 0, split = o.gemm_mode == TC_GEMM_SPLIT_BF16;
   for (int b = 0; b < count; ++b)
     TC_RETURN_IF(sec ? prepare_sectors(plans[b], inst[b], o, s, false)

@@ -181,28 +181,37 @@ int launch_block_diag_c64(const BlockTable& t, const c64* blocks, int64_t Np, c6
 int launch_scale_vec_c128(c128* x, int64_t count, double a, hipStream_t s);
 int launch_accumulate_vec_c64(const c64* t, c128* m, int64_t count, hipStream_t s);
 
-// ---- LDS-resident stepping of one small instance (resident.hip)
-// All steps in one launch of one workgroup, op, rho and X held in LDS:
+// ---- LDS-resident stepping of small instances (resident.hip)
+// All steps in one launch, one workgroup per instance, op, rho and X held in
+// LDS: op = U, or e^{i w_c k dt} U - I in the rotating frame;
 // X = op R (+ R if rot), R' = X op^dag (+ X if rot) per step, renormalisation
 // in FP64 every renorm_every steps (scratch[0] = last trace, scratch[1] = 1
 // once a trace is non-finite or non-positive), records of the diagonal
-// every record_every steps (record 0 = the initial state), rho written back at
-// the end.  The master storage is c128 (N <= 48) or c64 (N <= 64).
+// every record_every steps (record 0 = the initial state), rho written back in
+// the lab frame at the end.  The state is held in c128 (N <= 48) or c64
+// (N <= 64); c <= 63.
 constexpr int RESIDENT_MAX_N_C128 = 48;
 constexpr int RESIDENT_MAX_N_C64 = 64;
-struct ResidentArgs {
-  const void* op; int64_t ldop;   // U (lab) or D = U~ - I (rotating), master precision
-  void* rho; int64_t ldr;         // master state, in/out
-  int rot;
-  int64_t steps;
-  int renorm_every, record_every;
-  double* pop;                    // [steps/record_every + 1] or NULL
-  double* pdist;                  // [..][c + 1] or NULL
-  double* pstate;                 // [..][min(n, c) + 1] or NULL
-  double* scratch;                // [2]
+struct ResidentItem {
+  int n = 0, c = 0, N = 0;
+  int k = -1;                   // one sector's states only (N = d_k), or -1: all states
+  double omega_c = 0.0;
+  const c128* U = nullptr; int64_t ldu = 0;
+  void* rho = nullptr; int64_t ldr = 0;
+  double *pop = nullptr, *pdist = nullptr, *pstate = nullptr;
+  double* scratch = nullptr;    // [2]: trace, non-finite flag (cleared at the start)
 };
-int launch_resident_c128(const ModelArgs& m, const ResidentArgs& a, hipStream_t s);
-int launch_resident_c64(const ModelArgs& m, const ResidentArgs& a, hipStream_t s);
+struct ResidentRun {
+  int64_t steps = 0;
+  double dt = 0.0;
+  int rot = 0;                  // rotating frame
+  int rho_c128 = 0;             // storage of rho: complex128, else complex64
+  int renorm_every = 0, record_every = 0;
+};
+// One item, or count items in device memory (one workgroup each); maxN: the
+// largest N of them.
+int launch_resident(bool f64, int maxN, const ResidentItem* one, const ResidentItem* many_dev,
+                    int count, const ResidentRun& a, hipStream_t s);
 
 // bfloat16 hi/lo split of binary32 values.
 int launch_split_bf16(const float* x, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t s);

@@ -218,6 +218,73 @@ def test_resident_kernel_against_oracle_and_general_path(n, c, mode, frame, dtyp
     assert dgen <= tol
 
 
+@pytest.mark.parametrize("n,c,k,mode,frame,dtype,tol", [
+    (5, 5, 5, tcm.TC_GEMM_F64, tcm.TC_FRAME_ROTATING, torch.complex128, 1e-12),   # 32 states
+    (6, 2, 3, tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-12),        # 41
+    (3, 40, 20, tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-12),      # 8
+    (3, 80, 20, tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-12),      # c > 63
+    (6, 6, 6, tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5),     # 64
+    (4, 4, 4, tcm.TC_GEMM_F32, tcm.TC_FRAME_LAB, torch.complex128, 1e-5)])        # 16, converted
+def test_resident_one_sector(n, c, k, mode, frame, dtype, tol):
+    """One small excitation sector, stepped by the LDS-resident kernel (its
+    records by photon number): 120 steps, renormalised every 50, records every
+    3, against the oracle's exact evolution in the whole space."""
+    inst = ti.random_model(n, c, 70 + n, state="gaussian")
+    m = pipeline.model_of(inst)
+    st = tcm.tc_sector_states(m, k)
+    psi0 = np.zeros(inst.N, np.complex128)
+    psi0[st] = inst.psi0[st] / np.linalg.norm(inst.psi0[st])
+    dt, steps, every = 0.07, 120, 3
+    _, U = pipeline.sector_propagator(m, k, dt)
+    rho = _dev(np.outer(psi0[st], psi0[st].conj()), dtype)
+    pop, pd, _ = pipeline.evolve_sector(m, k, U, rho, steps, dt, mode, frame, 50, every,
+                                        record_photons=True)
+    pop, pd = pop.cpu().numpy(), pd.cpu().numpy()
+    P = oev.SectorPropagator(n, c, inst.g, inst.omega_a)
+    O = excitation_op(n, c)
+    assert pd.shape == (steps // every + 1, c + 1)
+    for r in range(pop.size):
+        d = np.abs(P.psi(psi0, r * every * dt)) ** 2
+        assert abs(pop[r] - float(np.sum(O * d))) <= tol
+        assert np.max(np.abs(pd[r] - d.reshape(c + 1, -1).sum(1))) <= tol
+    psi = P.psi(psi0, steps * dt)[st]
+    got = rho.cpu().numpy().astype(np.complex128)
+    assert np.max(np.abs(got - np.outer(psi, psi.conj()))) <= tol
+
+
+@pytest.mark.parametrize("mode,frame,dtype,tol", [
+    (tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-12),
+    (tcm.TC_GEMM_F64, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5),
+    (tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5)])
+def test_resident_batch(mode, frame, dtype, tol):
+    """A batch of nothing but LDS-resident instances (N = 4 .. 48): each equals
+    its own run bit for bit where both use the same padding, and the oracle."""
+    shapes = [(1, 1), (3, 3), (2, 11), (4, 2), (3, 2), (5, 0)]
+    insts = [ti.random_model(n, c, 90 + i, state="gaussian") for i, (n, c) in enumerate(shapes)]
+    dt, steps, every = 0.05, 61, 2
+    models = [pipeline.model_of(i) for i in insts]
+    Us = [pipeline.propagator(m, dt)[1] for m in models]
+    rhos = [_dev(i.rho0(), dtype) for i in insts]
+    pops = [torch.zeros(steps // every + 1, dtype=torch.float64, device=DEV) for _ in insts]
+    opts = tcm.make_opts(steps, dt, mode, tcm.TC_C128 if dtype == torch.complex128 else tcm.TC_C64,
+                         frame, 20, every, 0, 1)
+    tcm.tc_evolve([tcm.make_instance(m, U, r, p) for m, U, r, p in zip(models, Us, rhos, pops)],
+                  opts)
+    for k, inst in enumerate(insts):
+        P = oev.SectorPropagator(inst.n, inst.c, inst.g, inst.omega_a)
+        O = excitation_op(inst.n, inst.c)
+        pop = pops[k].cpu().numpy()
+        for r in range(pop.size):
+            d = np.abs(P.psi(inst.psi0, r * every * dt)) ** 2
+            assert abs(pop[r] - float(np.sum(O * d))) <= tol
+        psi = P.psi(inst.psi0, steps * dt)
+        got = rhos[k].cpu().numpy().astype(np.complex128)
+        assert np.max(np.abs(got - np.outer(psi, psi.conj()))) <= tol
+    rho, pop, _ = run_gpu(insts[3], dt, steps, mode, frame, 20, dtype, every)
+    assert np.array_equal(rho, rhos[3].cpu().numpy().astype(np.complex128))
+    assert np.array_equal(pop, pops[3].cpu().numpy())
+
+
 def test_resident_nonfinite_and_zero_steps():
     """The resident kernel reports a non-finite trace like the general path and
     leaves rho as it is for zero steps."""
