@@ -353,7 +353,8 @@ int backward_by_sectors(const ModelArgs& a, const double* H, int64_t ldh, const 
     std::vector<GemmDesc> ds;
     for (int k = 0; k < nb; ++k) {
       GemmDesc dd;
-      dd.M = dd.N = dd.K = L.dim[k];
+      dd.M = dd.N = L.dim[k];
+      dd.K = (L.d[k] + 15) / 16 * 16;       // whole K tiles: the padding beyond is zero
       dd.A = blk(const_cast<void*>(A), k, e); dd.lda = L.dim[k]; dd.a_kmaj = false; dd.conj_a = ca;
       dd.B = blk(const_cast<void*>(B), k, e); dd.ldb = L.dim[k]; dd.b_kmaj = true; dd.conj_b = cb;
       dd.C = blk(Cm, k, e); dd.ldc = L.dim[k];

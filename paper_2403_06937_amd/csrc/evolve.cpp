@@ -148,7 +148,10 @@ void plan_sectors(const tc_evolve_opts& o, Arena& ar, InstPlan* p) {
   p->perm = static_cast<int32_t*>(ar.take(size_t(pos) * 4));
   p->inv = static_cast<int32_t*>(ar.take(size_t(N) * 4));
   p->secpos = static_cast<int32_t*>(ar.take(size_t(pos) * 4));
-  p->items = static_cast<char*>(ar.take(2 * (split ? split_grouped_bytes(ns) : grouped_bytes(ns))));
+  // one descriptor per block of the first product, two of the second (one in
+  // split-BF16)
+  p->items = static_cast<char*>(
+      ar.take(split ? 2 * split_grouped_bytes(ns) : grouped_bytes(ns) + grouped_bytes(2 * ns)));
   if (split) {
     p->sopA.resize(ns);
     p->sopB.resize(ns);
@@ -423,17 +426,18 @@ int prepare_sector_split(InstPlan& p, const tc_evolve_opts& o, const std::vector
   d1.clear(); d2.clear();
   for (int k : order) {
     const int64_t off = p.spo[k], d = p.spd[k];
+    const int64_t dk = round_up(p.sdim[k], SPLIT_BK);   // K: the padding beyond is zero
     SplitProduct g1;                    // X_{k, k:} = op_k rho_{k, k:}
     g1.A = p.sopA[k].base; g1.lda = p.sopA[k].ld;
     g1.B = p.sRt.base + plane_offset(p.sRt.ld, off, off, 0); g1.ldb = p.sRt.ld;
-    g1.M = d; g1.N = Np - off; g1.Kp = d;
+    g1.M = d; g1.N = Np - off; g1.Kp = dk;
     if (rot) { g1.br = 1.f; g1.Cin = rho + off * p.ldr + off; g1.ldcin = p.ldr; }
     g1.Cf = X + off * p.ldx + off; g1.ldcf = p.ldx;
     g1.P = p.sXp.base + plane_offset(p.sXp.ld, off, off, 0); g1.ldp = p.sXp.ld;
     SplitProduct g2;                    // rho'_{:k, k} = X_{:k, k} op_k^dag
     g2.A = p.sXp.base + plane_offset(p.sXp.ld, 0, off, 0); g2.lda = p.sXp.ld;
     g2.B = p.sopB[k].base; g2.ldb = p.sopB[k].ld;
-    g2.M = off + d; g2.N = d; g2.Kp = d;
+    g2.M = off + d; g2.N = d; g2.Kp = dk;
     if (rot) { g2.br = 1.f; g2.Cin = X + off; g2.ldcin = p.ldx; }
     g2.Cf = rho + off; g2.ldcf = p.ldr;
     g2.P = p.sRt.base + plane_offset(p.sRt.ld, off, 0, 0); g2.ldp = p.sRt.ld; g2.p_trans = true;
@@ -505,20 +509,32 @@ int prepare_sectors(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o,
   d1.clear(); d2.clear();
   for (int k : order) {
     const int64_t off = p.spo[k], d = p.spd[k];
+    const int64_t dk = round_up(p.sdim[k], 16);   // K in whole K tiles: zeros beyond
     const void* blk = static_cast<char*>(p.blocks) + p.boff[k] * eb;
     GemmDesc g1;                        // X_{k, k:} = U_k rho_{k, k:}
-    g1.M = d; g1.N = Np - off; g1.K = d;
+    g1.M = d; g1.N = Np - off; g1.K = dk;
     g1.A = blk; g1.lda = d; g1.a_kmaj = false;
     g1.B = at(p.rho, off, off, p.ldr); g1.ldb = p.ldr; g1.b_kmaj = true;
     g1.C = at(p.X, off, off, p.ldx); g1.ldc = p.ldx;
     if (rot) { g1.Cin = g1.B; g1.ldcin = p.ldr; g1.beta_re = 1.0; }
-    GemmDesc g2;                        // rho'_{:k, k} = X_{:k, k} U_k^dag
-    g2.M = off + d; g2.N = d; g2.K = d;
-    g2.A = at(p.X, 0, off, p.ldx); g2.lda = p.ldx; g2.a_kmaj = false;
+    // rho'_{:k, k} = X_{:k, k} U_k^dag: the diagonal block is Hermitian, so its
+    // upper tile triangle is multiplied and mirrored; the blocks above it whole
+    // (this and K = d_k rounded up to a K tile, not to the block's padding: N = 5120
+    // FP64 step 1.95 -> 1.85 ms)
+    GemmDesc g2;
+    g2.M = d; g2.N = d; g2.K = dk;
+    g2.A = at(p.X, off, off, p.ldx); g2.lda = p.ldx; g2.a_kmaj = false;
     g2.B = blk; g2.ldb = d; g2.b_kmaj = true; g2.conj_b = true;
-    g2.C = at(p.rho, 0, off, p.ldr); g2.ldc = p.ldr;
+    g2.C = at(p.rho, off, off, p.ldr); g2.ldc = p.ldr;
     if (rot) { g2.Cin = g2.A; g2.ldcin = p.ldx; g2.beta_re = 1.0; }
+    GemmDesc g3 = g2;
+    g2.herm = true;
+    g3.M = off;
+    g3.A = at(p.X, 0, off, p.ldx);
+    g3.C = at(p.rho, 0, off, p.ldr);
+    if (rot) g3.Cin = g3.A;
     d1.push_back(g1);
+    if (off > 0) d2.push_back(g3);
     d2.push_back(g2);
   }
   if (!build) return TC_OK;
@@ -820,7 +836,7 @@ bool use_batched(int count, const tc_evolve_opts& o) {
   return count > 1 && (o.gemm_mode != TC_GEMM_SPLIT_BF16 || o.sectors);
 }
 
-// sector_items: total sector blocks of the batch (0 without sectors); the
+// sector_items: total block products of the batch (0 without sectors); the
 // block products of all instances share two groups per tile shape
 void plan_batch(Arena& ar, int count, int64_t sector_items, BatchBufs* b) {
   const size_t blocks = std::max(grouped_bytes(int(sector_items)),
@@ -851,12 +867,13 @@ void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDe
   g2.tail_ws = p.tail_ws; g2.tail_ws_bytes = p.tail_ws_bytes;
 }
 
-// Sector blocks of all instances of a batch (0 without sectors).
+// Block products of one product phase over all instances of a batch: at most
+// two per sector (0 without sectors).
 int64_t sector_items(const tc_instance* inst, int count, const tc_evolve_opts& o) {
   if (!o.sectors) return 0;
   int64_t t = 0;
   for (int b = 0; b < count; ++b)
-    t += inst[b].model->n_atoms + inst[b].model->photon_cutoff + 1;
+    t += 2 * (inst[b].model->n_atoms + inst[b].model->photon_cutoff + 1);
   return t;
 }
 
@@ -928,7 +945,7 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   GroupedProducts G1[3][2], G2[3][2];
   SplitGrouped S1, S2;
   char* it = bb.items;
-  const size_t gstep = sec ? std::max(grouped_bytes(int(d1[1][0].size() + d1[2][0].size())),
+  const size_t gstep = sec ? std::max(grouped_bytes(int(d2[1][0].size() + d2[2][0].size())),
                                       split_grouped_bytes(int(sp1.size())))
                            : grouped_bytes(count);
   if (sec && split) {
