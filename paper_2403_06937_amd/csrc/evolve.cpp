@@ -121,11 +121,7 @@ void plan_sectors(const tc_evolve_opts& o, Arena& ar, InstPlan* p) {
   p->sectors = true;
   std::vector<int64_t> off;
   sector_sizes(p->m.n, p->m.c, p->sdim, off);
-  // FP64 blocks above 1024 states take 128 x 128 tiles (0.81 of the FP64 peak
-  // on the padded work at N = 12288 against 0.75 with 64 x 64, for slightly
-  // less time despite the extra padding); otherwise the autotuner's table
-  const int64_t maxd = *std::max_element(p->sdim.begin(), p->sdim.end());
-  p->svar = (f64 && maxd > 1024) ? 1 : tile_variant_for(N, f64);
+  p->svar = tile_variant_for(N, f64);
   const int64_t q = split ? SPLIT_BM : (p->svar == 1 ? 128 : 64);
   const int ns = int(p->sdim.size());
   p->spo.assign(ns, 0);
@@ -400,8 +396,8 @@ int copy_checkpoint(const InstPlan& p, const tc_instance& in, const tc_evolve_op
 }
 
 // Sector stepping: sorted order, blocks of U (or D), and the descriptors of
-// the two grouped products of a step (largest sectors first, so the
-// persistent launch starts on the longest tiles).
+// the two grouped products of a step (largest sectors first, so that the
+// launch starts on the longest tiles).
 // Split-BF16 by sectors: planes of every block and of rho hat^T, then the two
 // grouped split products of a step,
 //   X_{k,k:} = U_k rho_{k,k:}   (rotating: + rho_{k,k:}), planes of X written by rows
@@ -810,18 +806,19 @@ int evolve_one(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipS
 
 // ------------------------------------------------------------------ batching
 // count > 1 instances with FP64 / FP32 products: each product phase of a step
-// is one persistent grouped launch per tile shape over every instance's
+// is one grouped launch per tile shape over every instance's
 // tiles, the readout is one launch for all instances (record index kept in a
 // device counter), and with use_graph the launches of a chunk of steps are
 // captured once in a hipGraph and replayed.
 // Dense instances of a batch that take the small product kernel, as they do on
 // their own: always up to N = 192 (16 instances of N = 160: 82 -> 47 us a step
-// in FP64, 62 -> 36 in FP32, N = 64: 44 -> 24), and up to N = 512 where the
-// 64 x 64 tiles would be ragged (the persistent kernel) or fewer than the CUs.  A
-// chip full of whole 64 x 64 tiles reads less per product: 30 instances of
-// N = 256 take 176 us against 185.
-bool batch_small(int64_t N, int64_t tiles64) {
-  return N <= 192 || (N <= 512 && (N % 64 != 0 || tiles64 < 256));
+// in FP64, 62 -> 36 in FP32, N = 64: 44 -> 24), and up to N = 512 where there are
+// fewer 64 x 64 tiles than CUs (4 x 256 in FP64 36 us against 92) or, in FP32,
+// ragged ones (the persistent kernel).  A chip full of 64 x 64 tiles reads less
+// per product: FP64 48 x 224 take 170 us a step against 219, 16 x 480 425
+// against 468; FP32 30 x 256 176 against 185.
+bool batch_small(int64_t N, int64_t tiles64, bool f64) {
+  return N <= 192 || (N <= 512 && (tiles64 < 256 || (!f64 && N % 64 != 0)));
 }
 
 struct BatchBufs {
@@ -925,7 +922,7 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     } else {
       GemmDesc g1, g2;
       step_descs(plans[b], o, g1, g2);
-      if (batch_small(plans[b].N, tiles64)) {
+      if (batch_small(plans[b].N, tiles64, f64)) {
         s1.push_back(g1);
         s2.push_back(g2);
         continue;

@@ -51,15 +51,17 @@ int gemm_f64(const GemmDesc& d, hipStream_t s);   // elements double / cplx<doub
 int gemm_f32(const GemmDesc& d, hipStream_t s);   // elements float / cplx<float>
 
 // Grouped complex products (A and B row-major, the layout of the time step):
-// every product of the group shares one tile shape and one persistent launch.
+// every product of the group shares one tile shape and one launch.
 //   variant 1: 128 x 128 tiles, 8 waves (K tile 16 for FP64, as the one-product
-//              FP64 default);  variant 2: 64 x 64 tiles, 4 waves.
+//              FP64 default);  variant 2: 64 x 64 tiles, 4 waves (FP64: direct
+//              tiles, without LDS, where every K is a multiple of 8).
 struct GroupedProducts {
   int variant = 1;
   bool f64 = false;
   int count = 0;
   int total_tiles = 0;
   bool all_exact = false;      // every product a multiple of the tile (unchecked kernel)
+  bool direct = false;         // FP64, every K a multiple of 8: variant 2 takes direct tiles
   bool persistent = true;      // false (all_exact only): one workgroup per tile
   void* items_dev = nullptr;   // device copy of the descriptors (grouped_bytes(count))
   // host copy of each product's first tile, tile count and K (the launch

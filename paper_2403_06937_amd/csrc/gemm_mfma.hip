@@ -600,6 +600,21 @@ struct GroupItem {
   int exact;        // M, N multiples of the tile and K of the K tile
 };
 
+// Tile of an item's own list: a Hermitian product's upper tile triangle, else
+// GROUP_M tile rows at a time, column by column.
+__device__ __forceinline__ void grouped_coords(const Params& p, int local, int& tm, int& tn) {
+  if (p.herm) {
+    tri_coords(local, p.tiles_m, tm, tn);
+    return;
+  }
+  const int per_group = GROUP_M * p.tiles_n;
+  const int first_m = (local / per_group) * GROUP_M;
+  const int gsize = min(p.tiles_m - first_m, GROUP_M);
+  const int in_group = local % per_group;
+  tm = first_m + in_group % gsize;
+  tn = in_group / gsize;
+}
+
 // Tile ranges per XCD: the workgroups with id % 8 == x (one XCD) walk the
 // tiles [bound[x], bound[x + 1]) of the concatenated list, so the tiles that
 // run together on an XCD are neighbours that share operand panels in its L2.
@@ -628,16 +643,7 @@ grouped_gemm_kernel(const GroupItem* __restrict__ items, int count, XcdSplit xs)
     const Params p = items[lo].p;
     const int local = t - items[lo].tile_begin;
     int tm, tn;
-    if (p.herm) {
-      tri_coords(local, p.tiles_m, tm, tn);
-    } else {                              // GROUP_M tile rows at a time, column by column
-      const int per_group = GROUP_M * p.tiles_n;
-      const int first_m = (local / per_group) * GROUP_M;
-      const int gsize = min(p.tiles_m - first_m, GROUP_M);
-      const int in_group = local % per_group;
-      tm = first_m + in_group % gsize;
-      tn = in_group / gsize;
-    }
+    grouped_coords(p, local, tm, tn);
     const bool mirror = p.herm && tm != tn;
     if (ALL_EXACT || items[lo].exact)
       gemm_tile<T, CPLX, AK, BK, false, BM, BN, BKT, WM, WN, PADB>(p, tm, tn, mirror, lds);
@@ -666,18 +672,169 @@ grouped_tile_kernel(const GroupItem* __restrict__ items, int count) {
   const Params p = items[lo].p;
   const int local = t - items[lo].tile_begin;
   int tm, tn;
-  if (p.herm) {
-    tri_coords(local, p.tiles_m, tm, tn);
-  } else {
-    const int per_group = GROUP_M * p.tiles_n;
-    const int first_m = (local / per_group) * GROUP_M;
-    const int gsize = min(p.tiles_m - first_m, GROUP_M);
-    const int in_group = local % per_group;
-    tm = first_m + in_group % gsize;
-    tn = in_group / gsize;
-  }
+  grouped_coords(p, local, tm, tn);
   gemm_tile<T, CPLX, AK, BK, false, BM, BN, BKT, WM, WN, PADB>(p, tm, tn, p.herm && tm != tn,
                                                                lds);
+}
+
+// Direct tiles: a workgroup of 4 waves forms a 64 x 64 tile of a complex FP64
+// product, each wave a 32 x 32 quarter over the whole K, with MFMA fragments read
+// straight from global memory (L1 / L2) into registers, DIRECT_DEPTH slices of 8
+// K values ahead.  No LDS, no barrier: a wave waits for its own loads only, and
+// three workgroups a CU cover each other's.  An FP64 MFMA takes 64 cycles, so a
+// 32 x 32 wave tile asks L1 for 16 bytes a clock and CU, a quarter of what it
+// gives: staging operands in LDS has nothing to save, and its barriers cost the
+// 64 x 64 LDS tile a quarter of the matrix cores' time.  Lane l takes
+// A[l%16][2(l/16), +1] and B[2(l/16), +1][l%16] of a slice: both list K in the
+// order 0 2 4 6 | 1 3 5 7, so that a lane's two A elements are neighbours.
+// M and N need not be whole tiles; K has to be a multiple of 8 (direct_product).
+// Bound by the MFMA pipes.  Per step, LDS tiles against direct ones: a batch of
+// 16 x N = 512 558 -> 447 us, 8 x 608 548 -> 445, 8 x 2304 19.1 -> 16.1 ms
+// (67 TFLOP/s); by sectors N = 2304 264 -> 219 us, 5120 1795 -> 1534.  In FP32
+// (MFMA of 32 cycles) they gain nothing (16 x 512 269 -> 270 us).
+constexpr int DIRECT_EDGE = 64, DIRECT_DEPTH = 2;
+__device__ __forceinline__ void direct_tile(const Params& p, int tm, int tn, bool mirror) {
+  typedef double T;
+  typedef cplx<T> E;
+  typedef acc_t<T>::type A4;
+  constexpr int WM = 2, WN = 2, DEPTH = DIRECT_DEPTH;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4, q2 = 2 * lq;
+  const int64_t m0 = int64_t(tm) * DIRECT_EDGE + (wave / 2) * 16 * WM;
+  const int64_t n0 = int64_t(tn) * DIRECT_EDGE + (wave % 2) * 16 * WN;
+  if (m0 >= p.M || n0 >= p.N) return;
+  const int K = int(p.K);
+  const int64_t ldb = p.ldb;
+  const E* pa[WM];
+  const E* pb[WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+    pa[i] = static_cast<const E*>(p.A) + min(m0 + 16 * i + lr, p.M - 1) * p.lda + q2;
+#pragma unroll
+  for (int j = 0; j < WN; ++j)
+    pb[j] = static_cast<const E*>(p.B) + min(n0 + 16 * j + lr, p.N - 1) + q2 * ldb;
+  const T sa = p.conj_a ? T(-1) : T(1), sb = p.conj_b ? T(-1) : T(1);
+  A4 re[WM][WN], im[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      re[i][j] = A4{0, 0, 0, 0};
+      im[i][j] = A4{0, 0, 0, 0};
+    }
+  const int slices = K / 8;
+  E a[DEPTH][WM][2], b[DEPTH][WN][2];
+  // past the last slice the load repeats it (in bounds, never used)
+  auto load = [&](int d, int it) {
+    const int k0 = 8 * min(it, slices - 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i) a[d][i][h] = gload(pa[i] + k0 + h);
+#pragma unroll
+      for (int j = 0; j < WN; ++j) b[d][j][h] = gload(pb[j] + (k0 + h) * ldb);
+    }
+  };
+  auto mul = [&](int d) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      E x[WM], y[WN];
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        x[i] = a[d][i][h];
+        x[i].im *= sa;
+      }
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        y[j] = b[d][j][h];
+        y[j].im *= sb;
+      }
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          re[i][j] = mma(x[i].re, y[j].re, re[i][j]);
+          im[i][j] = mma(x[i].re, y[j].im, im[i][j]);
+          re[i][j] = mma_nega(x[i].im, y[j].im, re[i][j]);
+          im[i][j] = mma(x[i].im, y[j].re, im[i][j]);
+        }
+    }
+  };
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) load(d, d);
+  int it = 0;
+  for (; it + DEPTH <= slices; it += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      mul(d);
+      load(d, it + d + DEPTH);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d)
+    if (it + d < slices) mul(d);
+
+  // C = alpha * acc + beta * Cin + gamma * [m == n]
+  E* __restrict__ Cg = static_cast<E*>(p.C);
+  const E* __restrict__ Cin = static_cast<const E*>(p.Cin);
+  const T ar = T(p.alpha_re), ai = T(p.alpha_im), br = T(p.beta_re), bi = T(p.beta_im);
+  const T gam = T(p.gamma);
+  const bool use_beta = Cin != nullptr && (p.beta_re != 0.0 || p.beta_im != 0.0);
+  auto out_row = [&](int i, int r) -> int64_t {
+    return m0 + 16 * i + lq + 4 * r;
+  };
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    // beta's operand for a row of blocks before any of it is used (addresses
+    // clamped into the matrix)
+    E cin[WN][4];
+    if (use_beta)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          cin[j][r] = gload(Cin + min(out_row(i, r), p.M - 1) * p.ldcin +
+                            min(n0 + 16 * j + lr, p.N - 1));
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t row = out_row(i, r), col = n0 + 16 * j + lr;
+        if (row >= p.M || col >= p.N) continue;
+        const T xr = re[i][j][r], xi = im[i][j][r];
+        E out{ar * xr - ai * xi, ar * xi + ai * xr};
+        if (use_beta) {
+          const E y = cin[j][r];
+          out.re += br * y.re - bi * y.im;
+          out.im += br * y.im + bi * y.re;
+        }
+        if (row == col) out.re += gam;
+        gstore(Cg + row * p.ldc + col, out);
+        if (mirror) gstore(Cg + col * p.ldc + row, E{out.re, -out.im});
+      }
+  }
+}
+
+// One workgroup per direct tile of one product.
+__global__ void __launch_bounds__(256, 3) gemm_direct_kernel(const Params p) {
+  int tm, tn;
+  launch_tile(p, blockIdx.x, tm, tn);
+  direct_tile(p, tm, tn, p.herm && tm != tn);
+}
+
+// One workgroup per direct tile of the concatenated list.
+__global__ void __launch_bounds__(256, 3)
+grouped_direct_kernel(const GroupItem* __restrict__ items, int count) {
+  int lo = 0, hi = count - 1;            // last item with tile_begin <= blockIdx.x
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (items[mid].tile_begin <= int(blockIdx.x)) lo = mid; else hi = mid - 1;
+  }
+  const Params p = items[lo].p;
+  int tm, tn;
+  grouped_coords(p, int(blockIdx.x) - items[lo].tile_begin, tm, tn);
+  direct_tile(p, tm, tn, p.herm && tm != tn);
 }
 
 // Tile shapes (BM, BN, BKT, WM, WN); the wave count is (BM/16WM)(BN/16WN).
@@ -800,11 +957,56 @@ int variant_for(int default_variant) {
   return env >= 0 ? env : default_variant;
 }
 
+template <typename S>
+Params make_params(const GemmDesc& d) {
+  Params p;
+  p.M = d.M; p.N = d.N; p.K = d.K;
+  p.A = d.A; p.lda = d.lda; p.B = d.B; p.ldb = d.ldb;
+  p.C = d.C; p.ldc = d.ldc; p.Cin = d.Cin; p.ldcin = d.ldcin;
+  p.alpha_re = d.alpha_re; p.alpha_im = d.alpha_im;
+  p.beta_re = d.beta_re; p.beta_im = d.beta_im; p.gamma = d.gamma;
+  p.conj_a = d.conj_a; p.conj_b = d.conj_b; p.c_trans = d.c_trans; p.cin_trans = d.cin_trans;
+  p.herm = d.herm && S::BM == S::BN && d.M == d.N;
+  p.tiles_m = int((d.M + S::BM - 1) / S::BM);
+  p.tiles_n = int((d.N + S::BN - 1) / S::BN);
+  return p;
+}
+
+// What direct tiles take: complex, row-major, K in whole slices of 8.
+bool direct_product(const GemmDesc& d) {
+  return d.complex && !d.a_kmaj && d.b_kmaj && !d.c_trans && !d.cin_trans && d.K > 0 &&
+         d.K % 8 == 0;
+}
+
+typedef Shp<DIRECT_EDGE, DIRECT_EDGE, 8, 2, 2> DirectShape;
+
+int launch_direct(const GemmDesc& d, hipStream_t s) {
+  const Params p = make_params<DirectShape>(d);
+  const int64_t tiles = p.herm ? int64_t(p.tiles_m) * (p.tiles_m + 1) / 2
+                               : int64_t(p.tiles_m) * p.tiles_n;
+  if (tiles > (int64_t(1) << 31) - 1) { set_error("product too large"); return TC_ERR_UNSUPPORTED; }
+  ProfileScope prof(TC_KERNEL_GEMM_F64, s);
+  hipLaunchKernelGGL(gemm_direct_kernel, dim3(unsigned(tiles)), dim3(256), 0, s, p);
+  TC_TRY_HIP(hipGetLastError());
+  return TC_OK;
+}
+
 template <typename T, bool CPLX>
 int launch2(const GemmDesc& d, hipStream_t s) {
   typedef Variants<T, CPLX> V;
   if constexpr (CPLX)
     if (variant_for(-1) < 0 && small_product(d, sizeof(T) == 8)) return small_gemm<T>(d, nullptr, s);
+  if constexpr (CPLX && sizeof(T) == 8)
+    if (variant_for(-1) < 0 && direct_product(d)) {
+      // Direct tiles instead of 128 x 128 LDS tiles where those would be ragged
+      // (range checks and padding: N = 1088, 1.08 ms a step against 0.41; 2112,
+      // 3.11 against 1.94), have no scratch to spread a last round over, or are
+      // so many that a last round no longer counts (N = 5120, 1600 tiles, 22.6
+      // against 22.0; 12288, 308 against 298).  In between the spread last round
+      // wins (N = 2304, 2.19 against 2.38; 3584, 7.90 against 8.15; 4608 equal).
+      const int64_t tiles = ((d.M + 127) / 128) * ((d.N + 127) / 128);
+      if (!d.tail_ws || d.M % 128 || d.N % 128 || tiles >= 1600) return launch_direct(d, s);
+    }
   if (!d.a_kmaj && d.b_kmaj) {
     // A product of at most 16 tiles of 128 x 128 (N <= 512 when square)
     // takes 64 x 64 tiles (variant 2 in every element type): four times the
@@ -831,21 +1033,6 @@ int launch2(const GemmDesc& d, hipStream_t s) {
   if (d.a_kmaj && d.b_kmaj) return launch_shape<T, CPLX, true, true, typename V::V0>(d, s);
   if (d.a_kmaj && !d.b_kmaj) return launch_shape<T, CPLX, true, false, typename V::V0>(d, s);
   return launch_shape<T, CPLX, false, false, typename V::V0>(d, s);
-}
-
-template <typename S>
-Params make_params(const GemmDesc& d) {
-  Params p;
-  p.M = d.M; p.N = d.N; p.K = d.K;
-  p.A = d.A; p.lda = d.lda; p.B = d.B; p.ldb = d.ldb;
-  p.C = d.C; p.ldc = d.ldc; p.Cin = d.Cin; p.ldcin = d.ldcin;
-  p.alpha_re = d.alpha_re; p.alpha_im = d.alpha_im;
-  p.beta_re = d.beta_re; p.beta_im = d.beta_im; p.gamma = d.gamma;
-  p.conj_a = d.conj_a; p.conj_b = d.conj_b; p.c_trans = d.c_trans; p.cin_trans = d.cin_trans;
-  p.herm = d.herm && S::BM == S::BN && d.M == d.N;
-  p.tiles_m = int((d.M + S::BM - 1) / S::BM);
-  p.tiles_n = int((d.N + S::BN - 1) / S::BN);
-  return p;
 }
 
 template <typename S>
@@ -963,6 +1150,8 @@ int grouped_build(const std::vector<GemmDesc>& ds, bool f64, int variant, void* 
   g->total_tiles = total;
   g->items_dev = items_dev;
   g->all_exact = true;
+  g->direct = f64;
+  for (const GemmDesc& d : ds) g->direct = g->direct && direct_product(d);
   for (const GroupItem& it : items) g->all_exact = g->all_exact && it.exact;
   g->begins.clear(); g->tiles.clear(); g->ks.clear();
   for (size_t i = 0; i < items.size(); ++i) {
@@ -993,6 +1182,13 @@ int grouped_launch_tiles(const GroupedProducts& g, hipStream_t s) {
 
 template <typename T, typename S>
 int grouped_launch_any(const GroupedProducts& g, hipStream_t s) {
+  if (sizeof(T) == 8 && S::BM == DIRECT_EDGE && g.direct) {
+    ProfileScope prof(TC_KERNEL_GEMM_F64, s);
+    hipLaunchKernelGGL(grouped_direct_kernel, dim3(unsigned(g.total_tiles)), dim3(256), 0, s,
+                       static_cast<const GroupItem*>(g.items_dev), g.count);
+    TC_TRY_HIP(hipGetLastError());
+    return TC_OK;
+  }
   if (g.all_exact && !g.persistent) return grouped_launch_tiles<T, S>(g, s);
   return g.all_exact ? grouped_launch_t<T, S, true>(g, s) : grouped_launch_t<T, S, false>(g, s);
 }

@@ -285,6 +285,24 @@ def test_resident_batch(mode, frame, dtype, tol):
     assert np.array_equal(pop, pops[3].cpu().numpy())
 
 
+@pytest.mark.parametrize("frame,full", [
+    (tcm.TC_FRAME_LAB, 0), (tcm.TC_FRAME_ROTATING, 0), (tcm.TC_FRAME_ROTATING, 1)])
+def test_batch_direct_tiles(frame, full):
+    """A batch whose FP64 products take 64 x 64 direct tiles, N = 608 (ragged
+    tiles) beside 576 and 520, triangle or every tile, against the oracle."""
+    shapes = [(5, 18), (6, 8), (3, 64)]
+    insts = [ti.random_model(n, c, 70 + i, state="gaussian") for i, (n, c) in enumerate(shapes)]
+    dt, steps = 0.05, 7
+    models = [pipeline.model_of(i) for i in insts]
+    Us = [pipeline.propagator(m, dt)[1] for m in models]
+    rhos = [_dev(i.rho0()) for i in insts]
+    opts = tcm.make_opts(steps, dt, tcm.TC_GEMM_F64, tcm.TC_C128, frame, 0, 1, 0, full)
+    tcm.tc_evolve([tcm.make_instance(m, U, r) for m, U, r in zip(models, Us, rhos)], opts)
+    for inst, rho in zip(insts, rhos):
+        psi = oev.SectorPropagator(inst.n, inst.c, inst.g, inst.omega_a).psi(inst.psi0, steps * dt)
+        assert np.max(np.abs(rho.cpu().numpy() - np.outer(psi, psi.conj()))) <= 1e-10
+
+
 def test_resident_nonfinite_and_zero_steps():
     """The resident kernel reports a non-finite trace like the general path and
     leaves rho as it is for zero steps."""

@@ -77,6 +77,16 @@ def test_zgemm_f64(M, N, K, op_a, op_b):
     assert err <= 1e-13 * max(1.0, math.sqrt(K)) * np.max(np.abs(ref)) + 1e-15
 
 
+@pytest.mark.parametrize("M,N,K,op_a,op_b", [
+    (1030, 65, 8, 0, 0), (63, 1601, 16, 1, 0), (129, 1100, 24, 0, 1), (1, 2049, 1032, 1, 1),
+    (1088, 192, 40, 0, 0), (1152, 1152, 128, 0, 0)])
+def test_zgemm_f64_direct_tiles(M, N, K, op_a, op_b):
+    """Products past the small kernel's sizes with K a multiple of 8 (1, 2, odd
+    and even counts of slices), ragged and whole 64 x 64 tiles, conjugated
+    operands."""
+    test_zgemm_f64(M, N, K, op_a, op_b)
+
+
 @pytest.mark.parametrize("M,N,K", SIZES)
 def test_zgemm_f32(M, N, K):
     A = ti.random_matrix((M, K), 4)
