@@ -29,8 +29,12 @@ const int64_t kBucketRep[NB] = {256, 1024, 4096, 7168};
 
 std::mutex g_mu;
 bool g_loaded = false;
-// defaults from timing on gfx950: FP32 small products prefer 64 x 64 tiles
-int g_table[2][NB] = {{2, 2, 1, 1},    // FP32
+// Defaults from timing on gfx950: 64 x 64 tiles for groups of any size.  One FP32
+// product prefers 128 x 128 tiles from N = 1024 (12288: 158 ms a step against
+// 167), but a group gains more from the finer tiles' smaller padding and shorter
+// last round: 24 instances of N = 32 .. 3072 7.14 -> 6.79 ms a step, by sectors
+// N = 1536 153 -> 79 us, 2304 184 -> 130, 5120 998 -> 871, 12288 15.1 -> 14.9 ms.
+int g_table[2][NB] = {{2, 2, 2, 2},    // FP32
                       {2, 2, 2, 2}};   // FP64
 
 int bucket_of(int64_t N) {
