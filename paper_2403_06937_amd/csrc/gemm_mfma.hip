@@ -81,12 +81,11 @@ constexpr int GROUP_M = 8;
 
 // Default tile variant per element type for the step / exponential layout,
 // chosen by timing every variant at N = 12288 on gfx950:
-//   complex FP64: 128x128 tiles, 8 waves, K tile 16 (240 ms per full
-//                 product before the staged tile was stored early, 231 ms
-//                 after; 64x64: 285 ms; 128x128 with K tile 8: 294 ms;
-//                 128x64: 438 ms; LDS row padding of 0, 16 or 32 bytes: no
-//                 difference)
-//   real FP64:    128x128 tiles, 8 waves (U formation 1.07 s; 128x64: 1.42 s)
+//   complex FP64: 128x128 tiles, 8 waves, K tile 16 (231 ms per full product;
+//                 64x64: 285 ms; 128x128 with K tile 8: 294 ms; 128x64: 438 ms;
+//                 LDS row padding of 0, 16 or 32 bytes: no difference), for K
+//                 that direct tiles do not take
+//   real FP64:    128x128 tiles, 8 waves (128x64: a third slower), likewise
 //   complex FP32: 128x128 tiles, 8 waves (112 ms; 128x64: 118 ms)
 template <typename T, bool CPLX> struct DefaultVariant { static constexpr int value = 1; };
 template <> struct DefaultVariant<double, true> { static constexpr int value = 6; };
@@ -519,11 +518,11 @@ gemm_kernel(const Params p) {
 // tile i: unique, and a tile's pieces are neighbours in K order), and
 // gemm_tail_finish_kernel adds each tile's slots in order and runs the epilogue
 // (mirror included for a Hermitian product), one workgroup per tile and row of
-// its waves' blocks.  Bound by the MFMA pipes like the tile loop; N = 2304 FP64
-// (324 tiles, one round and 68; the triangle 171) takes 2.21 ms a step against
-// 2.59 ms when each tile of a last round was cut into the same whole number of
-// ranges, which left the triangle's 171 tiles a whole tile each on two thirds
-// of the CUs; complex FP32 the same way (40-step gradient 301 -> 269 ms).
+// its waves' blocks.  Bound by the MFMA pipes like the tile loop; for complex FP32
+// at N = 2304 (324 tiles, one round and 68; the triangle 171) a 40-step gradient
+// takes 269 ms against 301 when each tile of a last round was cut into the same
+// whole number of ranges, which left the triangle's 171 tiles a whole tile each on
+// two thirds of the CUs.
 // Positions base .. base + tail - 1 of the launch's tile
 // order are the tiles the main launch (grid base) leaves out.
 struct TailSplit {
@@ -678,87 +677,157 @@ grouped_tile_kernel(const GroupItem* __restrict__ items, int count) {
 }
 
 // Direct tiles: a workgroup of 4 waves forms a 64 x 64 tile of a complex FP64
-// product, each wave a 32 x 32 quarter over the whole K, with MFMA fragments read
-// straight from global memory (L1 / L2) into registers, DIRECT_DEPTH slices of 8
-// K values ahead.  No LDS, no barrier: a wave waits for its own loads only, and
-// three workgroups a CU cover each other's.  An FP64 MFMA takes 64 cycles, so a
-// 32 x 32 wave tile asks L1 for 16 bytes a clock and CU, a quarter of what it
-// gives: staging operands in LDS has nothing to save, and its barriers cost the
-// 64 x 64 LDS tile a quarter of the matrix cores' time.  Lane l takes
-// A[l%16][2(l/16), +1] and B[2(l/16), +1][l%16] of a slice: both list K in the
-// order 0 2 4 6 | 1 3 5 7, so that a lane's two A elements are neighbours.
+// product (128 x 128 of a real one), each wave a quarter over the whole K, with
+// MFMA fragments read straight from global memory (L1 / L2) into registers,
+// DIRECT_DEPTH slices of 8 K values ahead.  No LDS, no barrier: a wave waits for its
+// own loads only, and three workgroups a CU cover each other's.  An FP64 MFMA takes
+// 64 cycles, so a wave tile of 32 x 32 (64 x 64) asks L1 for 16 bytes a clock and
+// CU, a quarter of what it gives: staging operands in LDS has nothing to save, and
+// its barriers cost the 64 x 64 LDS tile a quarter of the matrix cores' time.
+// Lane l takes A[l%16][2(l/16), +1] and B[2(l/16), +1][l%16] of a slice: both list K
+// in the order 0 2 4 6 | 1 3 5 7, so that a lane's two A elements are neighbours.
 // M and N need not be whole tiles; K has to be a multiple of 8 (direct_product).
 // Bound by the MFMA pipes.  Per step, LDS tiles against direct ones: a batch of
 // 16 x N = 512 558 -> 447 us, 8 x 608 548 -> 445, 8 x 2304 19.1 -> 16.1 ms
 // (67 TFLOP/s); by sectors N = 2304 264 -> 219 us, 5120 1795 -> 1534.  In FP32
 // (MFMA of 32 cycles) they gain nothing (16 x 512 269 -> 270 us).
-constexpr int DIRECT_EDGE = 64, DIRECT_DEPTH = 2;
-__device__ __forceinline__ void direct_tile(const Params& p, int tm, int tn, bool mirror) {
-  typedef double T;
-  typedef cplx<T> E;
-  typedef acc_t<T>::type A4;
-  constexpr int WM = 2, WN = 2, DEPTH = DIRECT_DEPTH;
+constexpr int DIRECT_DEPTH = 2, DIRECT_NT = 256;
+template <bool CPLX> struct Direct {
+  static constexpr int W = CPLX ? 2 : 4;                // 16 x 16 blocks per wave and side
+  static constexpr int EDGE = 32 * W;                   // 2 x 2 waves
+  static constexpr int PER_CU = CPLX ? 3 : 2;           // workgroups, by registers
+  static constexpr int CHUNKS = (CPLX ? 2 : 1) * W * W * 2;   // 16 bytes each, per lane
+  static constexpr size_t SLOT = size_t(CHUNKS) * 16 * DIRECT_NT;
+  typedef typename elem<double, CPLX>::type E;
+  typedef acc_t<double>::type A4;
+};
+
+// C = alpha * acc + beta * Cin + gamma * [m == n] of a wave's block row i.
+template <bool CPLX>
+__device__ __forceinline__ void direct_epilogue(const Params& p, int64_t m, int64_t n, bool mirror,
+                                                const typename Direct<CPLX>::A4* re,
+                                                const typename Direct<CPLX>::A4* im) {
+  typedef typename Direct<CPLX>::E E;
+  constexpr int W = Direct<CPLX>::W;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  E* __restrict__ Cg = static_cast<E*>(p.C);
+  const E* __restrict__ Cin = static_cast<const E*>(p.Cin);
+  const bool use_beta = Cin != nullptr && (p.beta_re != 0.0 || p.beta_im != 0.0);
+  // beta's operand before any of it is used (addresses clamped into the matrix)
+  E cin[W][4];
+  if (use_beta)
+#pragma unroll
+    for (int j = 0; j < W; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        cin[j][r] = gload(Cin + min(m + lq + 4 * r, p.M - 1) * p.ldcin +
+                          min(n + 16 * j + lr, p.N - 1));
+#pragma unroll
+  for (int j = 0; j < W; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = m + lq + 4 * r, col = n + 16 * j + lr;
+      if (row >= p.M || col >= p.N) continue;
+      E out;
+      if constexpr (CPLX) {
+        const double xr = re[j][r], xi = im[j][r];
+        out = E{p.alpha_re * xr - p.alpha_im * xi, p.alpha_re * xi + p.alpha_im * xr};
+        if (use_beta) {
+          const E y = cin[j][r];
+          out.re += p.beta_re * y.re - p.beta_im * y.im;
+          out.im += p.beta_re * y.im + p.beta_im * y.re;
+        }
+        if (row == col) out.re += p.gamma;
+      } else {
+        out = p.alpha_re * re[j][r];
+        if (use_beta) out += p.beta_re * cin[j][r];
+        if (row == col) out += p.gamma;
+      }
+      gstore(Cg + row * p.ldc + col, out);
+      if (mirror) gstore(Cg + col * p.ldc + row, elem<double, CPLX>::cj(out, true));
+    }
+}
+
+// Tile (tm, tn) over the slices s0 .. s0 + slices - 1 of K: the result, or with
+// part the raw accumulators (chunk c of thread t at c DIRECT_NT + t, block row by
+// block row, a block's real then imaginary values).
+template <bool CPLX>
+__device__ __forceinline__ void direct_tile(const Params& p, int tm, int tn, bool mirror,
+                                            int64_t s0, int slices, u4* part) {
+  typedef Direct<CPLX> D;
+  typedef typename D::E E;
+  typedef typename D::A4 A4;
+  constexpr int W = D::W, DEPTH = DIRECT_DEPTH;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lq = lane >> 4, q2 = 2 * lq;
-  const int64_t m0 = int64_t(tm) * DIRECT_EDGE + (wave / 2) * 16 * WM;
-  const int64_t n0 = int64_t(tn) * DIRECT_EDGE + (wave % 2) * 16 * WN;
+  const int lr = lane & 15, q2 = 2 * (lane >> 4);
+  const int64_t m0 = int64_t(tm) * D::EDGE + (wave / 2) * 16 * W;
+  const int64_t n0 = int64_t(tn) * D::EDGE + (wave % 2) * 16 * W;
   if (m0 >= p.M || n0 >= p.N) return;
-  const int K = int(p.K);
   const int64_t ldb = p.ldb;
-  const E* pa[WM];
-  const E* pb[WN];
+  const E* pa[W];
+  const E* pb[W];
 #pragma unroll
-  for (int i = 0; i < WM; ++i)
-    pa[i] = static_cast<const E*>(p.A) + min(m0 + 16 * i + lr, p.M - 1) * p.lda + q2;
+  for (int i = 0; i < W; ++i) {
+    pa[i] = static_cast<const E*>(p.A) + min(m0 + 16 * i + lr, p.M - 1) * p.lda + 8 * s0 + q2;
+    pb[i] = static_cast<const E*>(p.B) + min(n0 + 16 * i + lr, p.N - 1) + (8 * s0 + q2) * ldb;
+  }
+  const double sa = p.conj_a ? -1.0 : 1.0, sb = p.conj_b ? -1.0 : 1.0;
+  A4 re[W][W], im[CPLX ? W : 1][CPLX ? W : 1];
 #pragma unroll
-  for (int j = 0; j < WN; ++j)
-    pb[j] = static_cast<const E*>(p.B) + min(n0 + 16 * j + lr, p.N - 1) + q2 * ldb;
-  const T sa = p.conj_a ? T(-1) : T(1), sb = p.conj_b ? T(-1) : T(1);
-  A4 re[WM][WN], im[WM][WN];
+  for (int i = 0; i < W; ++i)
 #pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
+    for (int j = 0; j < W; ++j) {
       re[i][j] = A4{0, 0, 0, 0};
-      im[i][j] = A4{0, 0, 0, 0};
+      if constexpr (CPLX) im[i][j] = A4{0, 0, 0, 0};
     }
-  const int slices = K / 8;
-  E a[DEPTH][WM][2], b[DEPTH][WN][2];
+  E a[DEPTH][W][2], b[DEPTH][W][2];
   // past the last slice the load repeats it (in bounds, never used)
   auto load = [&](int d, int it) {
     const int k0 = 8 * min(it, slices - 1);
+    if constexpr (!CPLX)
+#pragma unroll
+      for (int i = 0; i < W; ++i) {             // the two neighbours in one load
+        const cplx<double> v = gload(reinterpret_cast<const cplx<double>*>(pa[i] + k0));
+        a[d][i][0] = v.re;
+        a[d][i][1] = v.im;
+      }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
+      if constexpr (CPLX)
 #pragma unroll
-      for (int i = 0; i < WM; ++i) a[d][i][h] = gload(pa[i] + k0 + h);
+        for (int i = 0; i < W; ++i) a[d][i][h] = gload(pa[i] + k0 + h);
 #pragma unroll
-      for (int j = 0; j < WN; ++j) b[d][j][h] = gload(pb[j] + (k0 + h) * ldb);
+      for (int j = 0; j < W; ++j) b[d][j][h] = gload(pb[j] + (k0 + h) * ldb);
     }
   };
   auto mul = [&](int d) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      E x[WM], y[WN];
+      if constexpr (CPLX) {
+        E x[W], y[W];
 #pragma unroll
-      for (int i = 0; i < WM; ++i) {
-        x[i] = a[d][i][h];
-        x[i].im *= sa;
-      }
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        y[j] = b[d][j][h];
-        y[j].im *= sb;
-      }
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          re[i][j] = mma(x[i].re, y[j].re, re[i][j]);
-          im[i][j] = mma(x[i].re, y[j].im, im[i][j]);
-          re[i][j] = mma_nega(x[i].im, y[j].im, re[i][j]);
-          im[i][j] = mma(x[i].im, y[j].re, im[i][j]);
+        for (int i = 0; i < W; ++i) {
+          x[i] = a[d][i][h];
+          x[i].im *= sa;
+          y[i] = b[d][i][h];
+          y[i].im *= sb;
         }
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+#pragma unroll
+          for (int j = 0; j < W; ++j) {
+            re[i][j] = mma(x[i].re, y[j].re, re[i][j]);
+            im[i][j] = mma(x[i].re, y[j].im, im[i][j]);
+            re[i][j] = mma_nega(x[i].im, y[j].im, re[i][j]);
+            im[i][j] = mma(x[i].im, y[j].re, im[i][j]);
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+#pragma unroll
+          for (int j = 0; j < W; ++j) re[i][j] = mma(a[d][i][h], b[d][j][h], re[i][j]);
+      }
     }
   };
 #pragma unroll
@@ -775,56 +844,106 @@ __device__ __forceinline__ void direct_tile(const Params& p, int tm, int tn, boo
   for (int d = 0; d < DEPTH; ++d)
     if (it + d < slices) mul(d);
 
-  // C = alpha * acc + beta * Cin + gamma * [m == n]
-  E* __restrict__ Cg = static_cast<E*>(p.C);
-  const E* __restrict__ Cin = static_cast<const E*>(p.Cin);
-  const T ar = T(p.alpha_re), ai = T(p.alpha_im), br = T(p.beta_re), bi = T(p.beta_im);
-  const T gam = T(p.gamma);
-  const bool use_beta = Cin != nullptr && (p.beta_re != 0.0 || p.beta_im != 0.0);
-  auto out_row = [&](int i, int r) -> int64_t {
-    return m0 + 16 * i + lq + 4 * r;
-  };
+  if (part) {
+    struct Chunks { u4 c[2]; };
+    u4* dst = part + tid;
 #pragma unroll
-  for (int i = 0; i < WM; ++i) {
-    // beta's operand for a row of blocks before any of it is used (addresses
-    // clamped into the matrix)
-    E cin[WN][4];
-    if (use_beta)
+    for (int i = 0; i < W; ++i)
 #pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          cin[j][r] = gload(Cin + min(out_row(i, r), p.M - 1) * p.ldcin +
-                            min(n0 + 16 * j + lr, p.N - 1));
-#pragma unroll
-    for (int j = 0; j < WN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = out_row(i, r), col = n0 + 16 * j + lr;
-        if (row >= p.M || col >= p.N) continue;
-        const T xr = re[i][j][r], xi = im[i][j][r];
-        E out{ar * xr - ai * xi, ar * xi + ai * xr};
-        if (use_beta) {
-          const E y = cin[j][r];
-          out.re += br * y.re - bi * y.im;
-          out.im += br * y.im + bi * y.re;
+      for (int j = 0; j < W; ++j) {
+        const Chunks x = __builtin_bit_cast(Chunks, re[i][j]);
+        gstore(dst, x.c[0]);
+        gstore(dst + DIRECT_NT, x.c[1]);
+        dst += 2 * DIRECT_NT;
+        if constexpr (CPLX) {
+          const Chunks y = __builtin_bit_cast(Chunks, im[i][j]);
+          gstore(dst, y.c[0]);
+          gstore(dst + DIRECT_NT, y.c[1]);
+          dst += 2 * DIRECT_NT;
         }
-        if (row == col) out.re += gam;
-        gstore(Cg + row * p.ldc + col, out);
-        if (mirror) gstore(Cg + col * p.ldc + row, E{out.re, -out.im});
       }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < W; ++i)
+    direct_epilogue<CPLX>(p, m0 + 16 * i, n0, mirror, re[i], im[CPLX ? i : 0]);
+}
+
+// One product by direct tiles: workgroups 0 .. base - 1 take a tile each (full
+// rounds of PER_CU tiles per CU), the G after them equal ranges of the
+// remaining tiles' slices laid end to end, as gemm_tail_kernel does; one launch, so
+// that the ranges start as the last full round's tiles end.  Bound by the MFMA
+// pipes: N = 2304 2.14 ms a step (69 TFLOP/s), 12288 300 ms (74); U formation at
+// N = 5120 17.8 -> 17.2 ms, 2304 2.15 -> 2.06.
+template <bool CPLX>
+__global__ void __launch_bounds__(DIRECT_NT, Direct<CPLX>::PER_CU)
+gemm_direct_kernel(const Params p, TailSplit ts, void* part) {
+  const int pid = blockIdx.x;
+  const bool whole = pid < ts.base;
+  const int w = whole ? 0 : xcd_linear(pid - ts.base, ts.G);
+  int64_t x = whole ? 0 : ts.start(w);
+  const int64_t end = whole ? ts.kt : ts.start(w + 1);
+#pragma unroll 1
+  while (x < end) {
+    const int i = int(x / ts.kt);
+    const int64_t sx = x - i * ts.kt, len = min(ts.kt - sx, end - x);
+    int tm, tn;
+    launch_tile(p, whole ? pid : ts.base + i, tm, tn);
+    direct_tile<CPLX>(p, tm, tn, p.herm && tm != tn, sx, int(len),
+                      whole ? nullptr
+                            : reinterpret_cast<u4*>(static_cast<char*>(part) +
+                                                    size_t(w + i) * Direct<CPLX>::SLOT));
+    x += len;
   }
 }
 
-// One workgroup per direct tile of one product.
-__global__ void __launch_bounds__(256, 3) gemm_direct_kernel(const Params p) {
+// Sums a split tile's slots in order and runs the epilogue: one workgroup per tile
+// and block row of its waves.
+template <bool CPLX>
+__global__ void __launch_bounds__(DIRECT_NT)
+direct_finish_kernel(const Params p, TailSplit ts, const void* part) {
+  typedef Direct<CPLX> D;
+  typedef typename D::A4 A4;
+  constexpr int W = D::W, ROW = D::CHUNKS / W;         // chunks of a block row
+  struct Chunks { u4 c[2]; };
+  const int t = blockIdx.x, i = blockIdx.y;
   int tm, tn;
-  launch_tile(p, blockIdx.x, tm, tn);
-  direct_tile(p, tm, tn, p.herm && tm != tn);
+  launch_tile(p, ts.base + t, tm, tn);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m0 = int64_t(tm) * D::EDGE + (wave / 2) * 16 * W;
+  const int64_t n0 = int64_t(tn) * D::EDGE + (wave % 2) * 16 * W;
+  if (m0 >= p.M || n0 >= p.N) return;
+  const int w0 = ts.owner(t * ts.kt), w1 = ts.owner((t + 1) * ts.kt - 1);
+  A4 re[W], im[CPLX ? W : 1];
+#pragma unroll
+  for (int j = 0; j < W; ++j) {
+    re[j] = A4{0, 0, 0, 0};
+    if constexpr (CPLX) im[j] = A4{0, 0, 0, 0};
+  }
+#pragma unroll 2
+  for (int w = w0; w <= w1; ++w) {
+    const u4* src = reinterpret_cast<const u4*>(static_cast<const char*>(part) +
+                                                size_t(w + t) * D::SLOT) + i * ROW * DIRECT_NT + tid;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      Chunks x;
+      x.c[0] = gload(src);
+      x.c[1] = gload(src + DIRECT_NT);
+      src += 2 * DIRECT_NT;
+      re[j] += __builtin_bit_cast(A4, x);
+      if constexpr (CPLX) {
+        x.c[0] = gload(src);
+        x.c[1] = gload(src + DIRECT_NT);
+        src += 2 * DIRECT_NT;
+        im[j] += __builtin_bit_cast(A4, x);
+      }
+    }
+  }
+  direct_epilogue<CPLX>(p, m0 + 16 * i, n0, p.herm && tm != tn, re, im);
 }
 
 // One workgroup per direct tile of the concatenated list.
-__global__ void __launch_bounds__(256, 3)
+__global__ void __launch_bounds__(DIRECT_NT, Direct<true>::PER_CU)
 grouped_direct_kernel(const GroupItem* __restrict__ items, int count) {
   int lo = 0, hi = count - 1;            // last item with tile_begin <= blockIdx.x
   while (lo < hi) {
@@ -834,7 +953,7 @@ grouped_direct_kernel(const GroupItem* __restrict__ items, int count) {
   const Params p = items[lo].p;
   int tm, tn;
   grouped_coords(p, int(blockIdx.x) - items[lo].tile_begin, tm, tn);
-  direct_tile(p, tm, tn, p.herm && tm != tn);
+  direct_tile<true>(p, tm, tn, p.herm && tm != tn, 0, int(p.K / 8), nullptr);
 }
 
 // Tile shapes (BM, BN, BKT, WM, WN); the wave count is (BM/16WM)(BN/16WN).
@@ -972,22 +1091,40 @@ Params make_params(const GemmDesc& d) {
   return p;
 }
 
-// What direct tiles take: complex, row-major, K in whole slices of 8.
+// What direct tiles take: FP64, A and B row-major, K in whole slices of 8.
 bool direct_product(const GemmDesc& d) {
-  return d.complex && !d.a_kmaj && d.b_kmaj && !d.c_trans && !d.cin_trans && d.K > 0 &&
-         d.K % 8 == 0;
+  return !d.a_kmaj && d.b_kmaj && !d.c_trans && !d.cin_trans && d.K > 0 && d.K % 8 == 0;
 }
 
-typedef Shp<DIRECT_EDGE, DIRECT_EDGE, 8, 2, 2> DirectShape;
-
+template <bool CPLX>
 int launch_direct(const GemmDesc& d, hipStream_t s) {
-  const Params p = make_params<DirectShape>(d);
+  typedef Direct<CPLX> D;
+  const Params p = make_params<Shp<D::EDGE, D::EDGE, 8, D::W, D::W>>(d);
   const int64_t tiles = p.herm ? int64_t(p.tiles_m) * (p.tiles_m + 1) / 2
                                : int64_t(p.tiles_m) * p.tiles_n;
-  if (tiles > (int64_t(1) << 31) - 1) { set_error("product too large"); return TC_ERR_UNSUPPORTED; }
+  if (tiles > (int64_t(1) << 30)) { set_error("product too large"); return TC_ERR_UNSUPPORTED; }
+  // a partial last round is spread over the CUs when that saves at least the time
+  // of 8 slices (storing and adding the partial sums costs about as much)
+  const int64_t round = int64_t(device_cus()) * D::PER_CU;
+  const int64_t slots = std::min<int64_t>(d.tail_ws ? int64_t(d.tail_ws_bytes / D::SLOT) : 0, 1 << 20);
+  TailSplit ts;
+  ts.kt = d.K / 8;
+  ts.base = int(tiles / round * round);
+  ts.tail = int(tiles - ts.base);
+  ts.G = int(std::min<int64_t>(std::min<int64_t>(round, ts.tail * ts.kt / 8), slots - ts.tail + 1));
+  if (!(ts.tail > 0 && ts.G > ts.tail && ts.kt * (ts.G - ts.tail) >= 8 * int64_t(ts.G))) {
+    ts.base = int(tiles);
+    ts.tail = ts.G = 0;
+  }
   ProfileScope prof(TC_KERNEL_GEMM_F64, s);
-  hipLaunchKernelGGL(gemm_direct_kernel, dim3(unsigned(tiles)), dim3(256), 0, s, p);
+  hipLaunchKernelGGL(gemm_direct_kernel<CPLX>, dim3(unsigned(ts.base + ts.G)), dim3(DIRECT_NT), 0, s,
+                     p, ts, d.tail_ws);
   TC_TRY_HIP(hipGetLastError());
+  if (ts.tail > 0) {
+    hipLaunchKernelGGL(direct_finish_kernel<CPLX>, dim3(unsigned(ts.tail), unsigned(D::W)),
+                       dim3(DIRECT_NT), 0, s, p, ts, static_cast<const void*>(d.tail_ws));
+    TC_TRY_HIP(hipGetLastError());
+  }
   return TC_OK;
 }
 
@@ -996,29 +1133,22 @@ int launch2(const GemmDesc& d, hipStream_t s) {
   typedef Variants<T, CPLX> V;
   if constexpr (CPLX)
     if (variant_for(-1) < 0 && small_product(d, sizeof(T) == 8)) return small_gemm<T>(d, nullptr, s);
-  if constexpr (CPLX && sizeof(T) == 8)
-    if (variant_for(-1) < 0 && direct_product(d)) {
-      // Direct tiles instead of 128 x 128 LDS tiles where those would be ragged
-      // (range checks and padding: N = 1088, 1.08 ms a step against 0.41; 2112,
-      // 3.11 against 1.94), have no scratch to spread a last round over, or are
-      // so many that a last round no longer counts (N = 5120, 1600 tiles, 22.6
-      // against 22.0; 12288, 308 against 298).  In between the spread last round
-      // wins (N = 2304, 2.19 against 2.38; 3584, 7.90 against 8.15; 4608 equal).
-      const int64_t tiles = ((d.M + 127) / 128) * ((d.N + 127) / 128);
-      if (!d.tail_ws || d.M % 128 || d.N % 128 || tiles >= 1600) return launch_direct(d, s);
-    }
+  // FP64: direct tiles (2 N = 2304 products a step 2.19 ms on 128 x 128 LDS tiles
+  // with a spread last round, 2.14 on direct ones; 1536 700 -> 671 us, 5120
+  // 22.7 -> 22.1 ms; ragged tiles, range-checked in LDS, N = 1088 1.08 -> 0.28 ms,
+  // 1600 1.58 -> 0.76).  Real products (U formation, a tile is a quarter of the
+  // work) of up to 100 tiles of 128 x 128, or 256 (one round) when there is no
+  // buffer for K ranges, take 64 x 64 LDS tiles instead, four times the
+  // workgroups: U at N = 768 310 us against 511, 1536 968 against 906.
+  const int64_t t128 = ((d.M + 127) / 128) * ((d.N + 127) / 128);
+  const int64_t few = CPLX ? 16 : d.tail_ws ? 100 : 256;
+  if constexpr (sizeof(T) == 8)
+    if (variant_for(-1) < 0 && direct_product(d) && (CPLX || t128 > few))
+      return launch_direct<CPLX>(d, s);
   if (!d.a_kmaj && d.b_kmaj) {
-    // A product of at most 16 tiles of 128 x 128 (N <= 512 when square)
-    // takes 64 x 64 tiles (variant 2 in every element type): four times the
-    // workgroups before the K split of its one partial round, so each
-    // workgroup's share of the work is smaller, and a quarter of the padded
-    // work when the product is smaller than one 128 x 128 tile.  (At N = 768
-    // the K-split 128 x 128 tiles give the shorter critical path.)
+    // A complex FP32 product of at most 16 tiles of 128 x 128 takes 64 x 64 tiles
+    // (variant 2 in every element type) too.
     const int env = variant_for(-1);
-    const int64_t t128 = ((d.M + 127) / 128) * ((d.N + 127) / 128);
-    // Real products (U formation, a tile is a quarter of the work): up to 100
-    // tiles, or one round when there is no buffer for K ranges.
-    const int64_t few = CPLX ? 16 : d.tail_ws ? 100 : 256;
     const int v = env >= 0 ? env : (t128 <= few ? 2 : DefaultVariant<T, CPLX>::value);
     switch (v) {
       case 1: return launch_shape<T, CPLX, false, true, typename V::V1>(d, s);
@@ -1182,10 +1312,10 @@ int grouped_launch_tiles(const GroupedProducts& g, hipStream_t s) {
 
 template <typename T, typename S>
 int grouped_launch_any(const GroupedProducts& g, hipStream_t s) {
-  if (sizeof(T) == 8 && S::BM == DIRECT_EDGE && g.direct) {
+  if (sizeof(T) == 8 && S::BM == Direct<true>::EDGE && g.direct) {
     ProfileScope prof(TC_KERNEL_GEMM_F64, s);
-    hipLaunchKernelGGL(grouped_direct_kernel, dim3(unsigned(g.total_tiles)), dim3(256), 0, s,
-                       static_cast<const GroupItem*>(g.items_dev), g.count);
+    hipLaunchKernelGGL(grouped_direct_kernel, dim3(unsigned(g.total_tiles)),
+                       dim3(DIRECT_NT), 0, s, static_cast<const GroupItem*>(g.items_dev), g.count);
     TC_TRY_HIP(hipGetLastError());
     return TC_OK;
   }

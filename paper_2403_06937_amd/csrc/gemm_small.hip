@@ -346,12 +346,13 @@ int launch_grouped(const SmallGroup& g, hipStream_t s) {
 }  // namespace
 
 // Step times (both products, FP64 / FP32): N = 64 12.9 / 10.2 us against 27.6 /
-// 19.4 on the large tiles, 160 13.3 / 10.6 against 64 / 45, 512 42 / 28 against
-// 58 / 49, 768 132 / 75 against 145 / 91, 1024 239 / 128 against 251 / 146,
-// 1280 457 / 243 against 439 / 254, 1536 696 / 372 against 703 / 403: above the
-// limits the 128 x 128 tiles' smaller operand traffic wins.
+// 19.4 on 64 x 64 and 128 x 128 LDS tiles, 160 13.3 / 10.6 against 64 / 45.  Above
+// the limits larger tiles' smaller operand traffic wins: FP64 direct tiles with a
+// buffer to spread their last round, 512 43 us against 64, 640 70 against 91, 768
+// 131 against 125, 1024 237 against 227; FP32 128 x 128 tiles, 1024 128 against 146,
+// 1536 372 against 403.
 bool small_product(const GemmDesc& d, bool f64) {
-  const int64_t most = f64 ? 1024 : 1536;
+  const int64_t most = f64 ? (d.tail_ws ? 704 : 1024) : 1536;
   return d.complex && !d.a_kmaj && d.b_kmaj && !d.c_trans && !d.cin_trans && d.M <= most &&
          d.N <= most && d.K >= 1 && d.K <= (int64_t(1) << 20);
 }

@@ -303,6 +303,23 @@ def test_batch_direct_tiles(frame, full):
         assert np.max(np.abs(rho.cpu().numpy() - np.outer(psi, psi.conj()))) <= 1e-10
 
 
+@pytest.mark.parametrize("n,c,frame,full", [
+    (5, 22, tcm.TC_FRAME_LAB, 0), (7, 6, tcm.TC_FRAME_ROTATING, 0),
+    (3, 136, tcm.TC_FRAME_LAB, 1), (8, 6, tcm.TC_FRAME_LAB, 0), (9, 3, tcm.TC_FRAME_ROTATING, 1)])
+def test_direct_tiles_spread_round(n, c, frame, full):
+    """FP64 steps on 64 x 64 direct tiles whose last round is spread over the CUs:
+    no full round (N = 736, 896, 1096 ragged), one and a rest (1792, 2048), with the
+    Hermitian triangle or every tile, against the oracle."""
+    inst = ti.random_model(n, c, 330 + n, state="gaussian")
+    dt, steps = 0.05, 4
+    m = pipeline.model_of(inst)
+    _, U = pipeline.propagator(m, dt)
+    rho = _dev(inst.rho0())
+    pipeline.evolve(m, U, rho, steps, dt, tcm.TC_GEMM_F64, frame, 0, 1, full_product=full)
+    psi = oev.SectorPropagator(n, c, inst.g, inst.omega_a).psi(inst.psi0, steps * dt)
+    assert max_entry_error_pure(rho.cpu().numpy(), psi) <= 1e-10
+
+
 def test_resident_nonfinite_and_zero_steps():
     """The resident kernel reports a non-finite trace like the general path and
     leaves rho as it is for zero steps."""

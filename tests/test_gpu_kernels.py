@@ -87,6 +87,19 @@ def test_zgemm_f64_direct_tiles(M, N, K, op_a, op_b):
     test_zgemm_f64(M, N, K, op_a, op_b)
 
 
+@pytest.mark.parametrize("n,c", [(5, 44), (7, 10), (8, 5), (7, 12)])
+def test_expm_direct_tiles(n, c):
+    """U on real direct tiles (N = 1440 .. 1664: ragged 128 x 128 tiles, a last round
+    spread over the CUs): unitary, and equal to the oracle's on a state."""
+    inst = ti.random_model(n, c, 640 + n + c, state="gaussian")
+    _, U = pipeline.propagator(pipeline.model_of(inst), 0.05)
+    N = U.shape[0]
+    err = (U @ U.conj().T - torch.eye(N, dtype=U.dtype, device=DEV)).abs().max().item()
+    assert err <= 1e-13
+    P = oev.SectorPropagator(n, c, inst.g, inst.omega_a)
+    assert np.max(np.abs(U.cpu().numpy() @ inst.psi0 - P.psi(inst.psi0, 0.05))) <= 1e-12
+
+
 @pytest.mark.parametrize("M,N,K", SIZES)
 def test_zgemm_f32(M, N, K):
     A = ti.random_matrix((M, K), 4)
