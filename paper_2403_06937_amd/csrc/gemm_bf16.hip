@@ -768,21 +768,23 @@ split_tail_kernel(const SplitParams p, int base, int S, int kc, float* __restric
   split_tile<2, 4, 4, 2, true, true>(q, tm, tn, sA, sB, acc + size_t(blockIdx.x) * TILE_ACC);
 }
 
-// Workgroup (i, h): waves 2h and 2h + 1 of tile i, whose outputs and staging are
-// their own; a quarter of a tile per workgroup spreads the slots' reads and the
-// epilogue over four times the CUs (step at N = 768 68 -> 56 us, 1280 97 -> 91).
-// Equal K ranges over all CUs, as the FP64 product takes for its last round, lost
+// Workgroup (i, h): wave h of tile i, whose outputs and staging are its own; an
+// eighth of a tile per workgroup spreads the slots' reads and the epilogue over the
+// CUs (step with whole tiles, quarters, eighths: N = 768 68, 55.9, 55.1 us, 1280 97,
+// 90.4, 89.3; quarters and eighths: 1536 131.9, 129.4, 3072 619, 611, 5120 2681,
+// 2589).  Two slots in flight at a time cost register copies: N = 768 102 us.
+// Equal K ranges over all CUs, as FP64 and FP32 products take for a last round, lost
 // here: N = 1536 158 us against 133, 2304 332 against 309, and the triangle's 136
 // tiles at N = 2048 gained nothing, since the shorter ranges share fewer operand
 // rows in L2.
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(64)
 split_tail_finish_kernel(const SplitParams p, int base, int S, const float* __restrict__ acc) {
-  __shared__ u4 stage[2 * 1024];
+  __shared__ u4 stage[1024];
   constexpr int NT = 512, WM = 4, WN = 2, WGN = 4;
   const int i = blockIdx.x;
   int tm, tn;
   launch_tile(p, base + i, tm, tn);
-  const int tid = blockIdx.y * 128 + threadIdx.x;      // thread of the tile
+  const int tid = blockIdx.y * 64 + threadIdx.x;      // thread of the tile
   const int wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
   f4 acc_re[WM][WN], acc_im[WM][WN];
@@ -806,7 +808,7 @@ split_tail_finish_kernel(const SplitParams p, int base, int S, const float* __re
   }
   const int64_t m0 = int64_t(tm) * SPLIT_BM, n0 = int64_t(tn) * SPLIT_BN;
   split_epilogue_staged(p, acc_re, acc_im, m0 + wm * WM * 16, n0 + wn * WN * 16,
-                        p.herm && tm != tn, stage + (threadIdx.x >> 6) * 1024);
+                        p.herm && tm != tn, stage);
 }
 
 // Many split products in one launch, one workgroup per tile of the
@@ -975,7 +977,7 @@ int run_split(const Planes4& A, const Planes4& B, int64_t M, int64_t N, int64_t 
       hipLaunchKernelGGL(split_tail_kernel, dim3(unsigned(tail * S)), dim3(512), 0, s, q, base, S,
                          int(kc), tail_acc);
       TC_TRY_HIP(hipGetLastError());
-      hipLaunchKernelGGL(split_tail_finish_kernel, dim3(unsigned(tail), 4), dim3(128), 0, s, q,
+      hipLaunchKernelGGL(split_tail_finish_kernel, dim3(unsigned(tail), 8), dim3(64), 0, s, q,
                          base, S, static_cast<const float*>(tail_acc));
       TC_TRY_HIP(hipGetLastError());
       return TC_OK;
