@@ -240,9 +240,10 @@ int tc_evolve_workspace_size(const tc_instance* inst, int32_t count,
  * workspace of tc_evolve_workspace_size bytes.  Synchronises the stream only
  * when a renormalisation finds a non-finite trace (then TC_ERR_NONFINITE).
  * Results are bitwise reproducible on a given device; a product whose last
- * round of tiles would leave at least half of the compute units idle has
- * those tiles' K sums split into ranges that are added in order, and how it
- * is split depends on the device's compute-unit count. */
+ * round of tiles is partial (split-BF16: would leave at least half of the
+ * compute units idle) has those tiles' K sums split into ranges that are
+ * added in order, and how it is split depends on the device's compute-unit
+ * count. */
 int tc_evolve(const tc_instance* inst, int32_t count, const tc_evolve_opts* o,
               void* ws, size_t ws_bytes, void* stream);
 
