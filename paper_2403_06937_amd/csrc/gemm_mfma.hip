@@ -873,7 +873,7 @@ __device__ __forceinline__ void direct_tile(const Params& p, int tm, int tn, boo
 // rounds of PER_CU tiles per CU), the G after them equal ranges of the
 // remaining tiles' slices laid end to end, as gemm_tail_kernel does; one launch, so
 // that the ranges start as the last full round's tiles end.  Bound by the MFMA
-// pipes: N = 2304 2.14 ms a step (69 TFLOP/s), 12288 300 ms (74); U formation at
+// pipes: N = 2304 2.14 ms a step (69 TFLOP/s), 12288 303 ms (74); U formation at
 // N = 5120 17.8 -> 17.2 ms, 2304 2.15 -> 2.06.
 template <bool CPLX>
 __global__ void __launch_bounds__(DIRECT_NT, Direct<CPLX>::PER_CU)
