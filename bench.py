@@ -390,15 +390,20 @@ def sector_flop_per_step(n, c):
     return sum(8.0 * dk * dk * (N - ok) + 8.0 * dk * dk * (ok + dk) for dk, ok in zip(d, o))
 
 
-def sector_executed_flop_per_step(n, c, q):
-    """Flops the sector-block products execute: each sector padded to D_k, a
-    multiple of the tile edge q, so the products are 8 sum_k D_k^2 (N_p + D_k)."""
+def sector_executed_flop_per_step(n, c, q, kt=None, tri=False):
+    """Flops the sector-block products execute: each sector's d_k rows and columns
+    padded to D_k, a multiple of the tile edge q, and its K to K_k, a multiple of
+    kt (q when not given): X_{k,k:} is D_k x K_k x (N_p - o_k), rho'_{:k,k}
+    o_k x K_k x D_k, and its diagonal block D_k x K_k x D_k (tri: the upper
+    triangle of its tiles)."""
     from math import comb
     d = [sum(comb(n, k - m) for m in range(min(k, c) + 1) if k - m <= n)
          for k in range(n + c + 1)]
     D = [-(-x // q) * q for x in d]
-    Np = sum(D)
-    return sum(8.0 * x * x * (Np + x) for x in D)
+    kt = kt or q
+    K = [-(-x // kt) * kt for x in d]
+    diag = [(x // q + 1) / (2.0 * (x // q)) if tri else 1.0 for x in D]
+    return sum(8.0 * x * y * (sum(D) + x * h) for x, y, h in zip(D, K, diag))
 
 
 def bench_sectors11(tcm, pipeline, ti, steps=40):
@@ -434,14 +439,11 @@ def bench_sectors11(tcm, pipeline, ti, steps=40):
         tcm.tc_profile_enable(False)
         ms = e0.elapsed_time(e1) / steps
         peak = {"fp64": PEAK_F64, "fp32": PEAK_F32, "split": PEAK_BF16}[key]
-        # tile edge the sector blocks are padded to: 128 for split-BF16 and for
-        # FP64 blocks above 1024 states, else the autotuner's table
-        from math import comb
-        maxd = max(sum(comb(inst.n, k - m) for m in range(min(k, inst.c) + 1) if k - m <= inst.n)
-                   for k in range(inst.n + inst.c + 1))
-        q = 128 if (key == "split" or (key == "fp64" and maxd > 1024)
-                    or tcm.tc_autotune_query(mode, N) == 1) else 64
-        fx = sector_executed_flop_per_step(inst.n, inst.c, q)
+        # tile edge the sector blocks are padded to: 128 for split-BF16, else the
+        # autotuner's table
+        split = key == "split"
+        q = 128 if split or tcm.tc_autotune_query(mode, N) == 1 else 64
+        fx = sector_executed_flop_per_step(inst.n, inst.c, q, 32 if split else 16, not split)
         out[key] = {"ms_per_step": ms, "steps_per_s": 1000.0 / ms,
                     "tflops": fl / (ms * 1e-3) / 1e12,
                     "tflops_executed": fx / (ms * 1e-3) / 1e12,
