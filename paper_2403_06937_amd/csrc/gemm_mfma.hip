@@ -1312,15 +1312,18 @@ int grouped_launch_tiles(const GroupedProducts& g, hipStream_t s) {
 
 template <typename T, typename S>
 int grouped_launch_any(const GroupedProducts& g, hipStream_t s) {
-  if (sizeof(T) == 8 && S::BM == Direct<true>::EDGE && g.direct) {
+  if constexpr (sizeof(T) == 8 && S::BM == Direct<true>::EDGE) {
+    // a K that direct tiles do not take is no whole K tile either
+    if (!g.direct) return grouped_launch_t<T, S, false>(g, s);
     ProfileScope prof(TC_KERNEL_GEMM_F64, s);
     hipLaunchKernelGGL(grouped_direct_kernel, dim3(unsigned(g.total_tiles)),
                        dim3(DIRECT_NT), 0, s, static_cast<const GroupItem*>(g.items_dev), g.count);
     TC_TRY_HIP(hipGetLastError());
     return TC_OK;
+  } else {
+    if (g.all_exact && !g.persistent) return grouped_launch_tiles<T, S>(g, s);
+    return g.all_exact ? grouped_launch_t<T, S, true>(g, s) : grouped_launch_t<T, S, false>(g, s);
   }
-  if (g.all_exact && !g.persistent) return grouped_launch_tiles<T, S>(g, s);
-  return g.all_exact ? grouped_launch_t<T, S, true>(g, s) : grouped_launch_t<T, S, false>(g, s);
 }
 
 int grouped_run(const GroupedProducts& g, hipStream_t s) {

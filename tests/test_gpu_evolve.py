@@ -303,6 +303,22 @@ def test_batch_direct_tiles(frame, full):
         assert np.max(np.abs(rho.cpu().numpy() - np.outer(psi, psi.conj()))) <= 1e-10
 
 
+def test_batch_ragged_k():
+    """A batch with an N that is no multiple of 8 (516, 516 and 576): its group's
+    FP64 products keep the range-checked LDS tiles, against the oracle."""
+    insts = [ti.random_model(n, c, 80 + i, state="gaussian")
+             for i, (n, c) in enumerate([(2, 128), (1, 257), (6, 8)])]
+    dt, steps = 0.05, 5
+    models = [pipeline.model_of(i) for i in insts]
+    Us = [pipeline.propagator(m, dt)[1] for m in models]
+    rhos = [_dev(i.rho0()) for i in insts]
+    opts = tcm.make_opts(steps, dt, tcm.TC_GEMM_F64, tcm.TC_C128, tcm.TC_FRAME_LAB, 0, 1, 0, 0)
+    tcm.tc_evolve([tcm.make_instance(m, U, r) for m, U, r in zip(models, Us, rhos)], opts)
+    for inst, rho in zip(insts, rhos):
+        psi = oev.SectorPropagator(inst.n, inst.c, inst.g, inst.omega_a).psi(inst.psi0, steps * dt)
+        assert np.max(np.abs(rho.cpu().numpy() - np.outer(psi, psi.conj()))) <= 1e-10
+
+
 @pytest.mark.parametrize("n,c,frame,full", [
     (5, 22, tcm.TC_FRAME_LAB, 0), (7, 6, tcm.TC_FRAME_ROTATING, 0),
     (3, 136, tcm.TC_FRAME_LAB, 1), (8, 6, tcm.TC_FRAME_LAB, 0), (9, 3, tcm.TC_FRAME_ROTATING, 1)])
