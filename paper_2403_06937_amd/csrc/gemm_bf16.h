@@ -15,6 +15,11 @@ enum { PL_RH = 0, PL_RL = 1, PL_IH = 2, PL_IL = 3 };
 // Tile of the split product kernel; padded plane dimensions are multiples of it.
 constexpr int SPLIT_BM = 128, SPLIT_BN = 128, SPLIT_BK = 32;
 
+// Kernel shape of the 128 x 128 tiles: 0 = 8 waves of 64 x 32 outputs in two
+// ping-pong groups (default), 1 = 4 waves of 64 x 64, 2 = 8 waves of 64 x 32 in
+// lockstep.  TC_SPLIT_VARIANT selects one for timing.
+int split_variant();
+
 inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 // A 4-plane operand of rows x ld bf16 per plane (K-contiguous rows, ld a
@@ -49,7 +54,7 @@ int split_state(const c64* rho, int64_t ld, int64_t N, const SplitPlanes& p, hip
 // herm: rho is Hermitian, so the second product forms its upper tile triangle
 // and mirrors it.
 // ro: records of the state before the step, read along with the first product
-// (small steps only), or NULL.
+// (only when split_small_step(N); an error otherwise), or NULL.
 struct SmallReadout;
 int step_split(c64* rho, int64_t ldr, c64* X, int64_t ldx, int64_t N, bool rotating, bool herm,
                const SplitPlanes& p, const SmallReadout* ro, hipStream_t s);

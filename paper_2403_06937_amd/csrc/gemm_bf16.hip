@@ -890,17 +890,6 @@ int split_into(const c64* src, int64_t ld, int64_t R, int64_t C, bool trans, boo
   return TC_OK;
 }
 
-// Kernel shape: 0 = 8 waves of 64 x 32 outputs in two ping-pong groups
-// (default), 1 = 4 waves of 64 x 64, 2 = 8 waves of 64 x 32 in lockstep.
-// TC_SPLIT_VARIANT selects one for timing.
-int split_variant() {
-  static const int v = [] {
-    const char* e = getenv("TC_SPLIT_VARIANT");
-    return e ? atoi(e) : 0;
-  }();
-  return v;
-}
-
 // Compute units of the current device (queried once per device).
 int device_cu_count(int* cus) {
   static std::atomic<int> cache[64];
@@ -996,6 +985,14 @@ int run_split(const Planes4& A, const Planes4& B, int64_t M, int64_t N, int64_t 
 
 }  // namespace
 
+int split_variant() {
+  static const int v = [] {
+    const char* e = getenv("TC_SPLIT_VARIANT");
+    return e ? atoi(e) : 0;
+  }();
+  return v;
+}
+
 Planes4 split_take_planes(Arena& ar, int64_t rows, int64_t ld) { return take_planes(ar, rows, ld); }
 
 int split_matrix(const c64* src, int64_t ld, int64_t R, int64_t C, bool trans, bool conj,
@@ -1080,7 +1077,7 @@ int split_state(const c64* rho, int64_t ld, int64_t N, const SplitPlanes& p, hip
 
 int step_split(c64* rho, int64_t ldr, c64* X, int64_t ldx, int64_t N, bool rotating, bool herm,
                const SplitPlanes& p, const SmallReadout* ro, hipStream_t s) {
-  if (split_small_step(N) && split_variant() == 0) {
+  if (split_small_step(N)) {
     SplitSmall g;
     g.M = g.N = N;
     g.Kp = round_up(N, SPLIT_BK);
@@ -1099,6 +1096,10 @@ int step_split(c64* rho, int64_t ldr, c64* X, int64_t ldx, int64_t N, bool rotat
     h.P = p.Rt.base; h.ldp = p.Rt.ld; h.p_trans = 1;
     h.herm = herm;
     return split_small(h, nullptr, s);
+  }
+  if (ro) {
+    set_error("split step: only a small step's product reads a record along");
+    return TC_ERR_UNSUPPORTED;
   }
   // X = op rho (+ rho): A = split(op), B = split(rho^T); planes of X row-major
   TC_RETURN_IF(run_split(p.opA, p.Rt, N, N, p.Np, 1.f, 0.f, rotating ? 1.f : 0.f, 0.f,

@@ -20,7 +20,8 @@ struct SplitSmall {
   int herm = 0;
 };
 
-// Whether an N x N step takes these products.
+// Whether an N x N step takes these products, and so can read a record along: up
+// to N = 640, unless TC_SPLIT_VARIANT asks for a shape of the 128 x 128 tiles.
 bool split_small_step(int64_t N);
 // ro: records of the state that the product multiplies, or NULL.
 int split_small(const SplitSmall& p, const SmallReadout* ro, hipStream_t s);

@@ -252,7 +252,7 @@ int launch(const SplitSmall& p, const SmallReadout* ro, hipStream_t s) {
 }  // namespace
 
 bool split_small_step(int64_t N) {
-  return N <= 640;
+  return N <= 640 && split_variant() == 0;
 }
 
 int split_small(const SplitSmall& p, const SmallReadout* ro, hipStream_t s) {

@@ -2,6 +2,9 @@
 workload sizes and on smaller ragged cases, in the three precisions and two
 frames; plus checkpoints, renormalisation errors, determinism and batching."""
 import math
+import os
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -19,6 +22,7 @@ tcm = pytest.importorskip("paper_2403_06937_amd")
 from paper_2403_06937_amd import pipeline  # noqa: E402
 
 DEV = "cuda"
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def setup_module(module):
@@ -495,6 +499,47 @@ def test_small_product_kernel(n, c, mode, frame, rdt, tol, full, graph):
     err = max_entry_error_pure(rho.cpu().numpy().astype(np.complex128),
                                P.psi(inst.psi0, steps * dt))
     assert err < tol
+
+
+SPLIT_RECORDS_RUN = """
+import numpy as np, torch
+import paper_2403_06937_amd as tcm
+from paper_2403_06937_amd import pipeline
+import tcm_inputs as ti
+out = []
+for graph in (False, True):
+    inst = ti.random_model({n}, {c}, 611, state="gaussian")
+    m = pipeline.model_of(inst)
+    _, U = pipeline.propagator(m, 0.05)
+    rho = torch.from_numpy(inst.rho0()).to("cuda").to(torch.complex64)
+    out += list(pipeline.evolve(m, U, rho, 37, 0.05, tcm.TC_GEMM_SPLIT_BF16,
+                                tcm.TC_FRAME_ROTATING, 0, 3, record_photons=True,
+                                use_graph=graph)[:2])
+    torch.cuda.synchronize()
+np.savez({path!r}, *[x.cpu().numpy() for x in out])
+"""
+
+
+@pytest.mark.parametrize("variant", [1, 2])
+def test_split_records_with_tile_variant(variant, tmp_path):
+    """TC_SPLIT_VARIANT moves a small split-BF16 step (N = 160) from the small
+    products to a timing shape of the 128 x 128 tiles: every record of both kinds,
+    eager and from captured chunks, stays within the split bar of the oracle."""
+    n, c, path = 5, 4, str(tmp_path / "records.npz")
+    env = dict(os.environ, TC_SPLIT_VARIANT=str(variant))
+    r = subprocess.run([sys.executable, "-c", SPLIT_RECORDS_RUN.format(n=n, c=c, path=path)],
+                       cwd=ROOT, env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    z = np.load(path)
+    inst = ti.random_model(n, c, 611, state="gaussian")
+    P = oev.SectorPropagator(n, c, inst.g, inst.omega_a)
+    O = excitation_op(n, c)
+    for pop, pd in ((z["arr_0"], z["arr_1"]), (z["arr_2"], z["arr_3"])):
+        assert pop.shape == (13,)
+        for k in range(13):
+            d = np.abs(P.psi(inst.psi0, k * 3 * 0.05)) ** 2
+            assert abs(pop[k] - float(np.sum(O * d))) <= 1e-5, k
+            assert np.max(np.abs(pd[k] - d.reshape(c + 1, -1).sum(1))) <= 1e-5, k
 
 
 def mid_instance(seed=0):
