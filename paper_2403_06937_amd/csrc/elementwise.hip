@@ -497,11 +497,15 @@ __global__ void damp_cavity_kernel(E* __restrict__ rho, int64_t ld, int n, int c
 // one chain of one (a, a') pair, every element is read once and written once and
 // neighbouring threads' elements are neighbours in memory.  The coefficient of
 // rho[(m+l, a), (m'+l, a')] factors into a[m][l] a[m'][l] with
-//   a[m][l] = eta^{m/2} (binom(m + l, l) (1 - eta)^l)^{1/2},
+//   a[m][l] = eta^{m/2} (binom(m + l, l) |1 - eta|^l)^{1/2},
 // L^2 numbers from the host whose index is the same for all threads of a
-// workgroup.  HBM-bound: N = 2048 FP32 11 us against 46 when each coefficient's
+// workgroup, and the sign of (1 - eta)^l: -1 for odd l when eta > 1, which is the
+// inverse channel of a run with a negative dt.  HBM-bound: N = 2048 FP32 11 us against 46 when each coefficient's
 // roots and divisions were formed per element.
-template <int L> struct CavityCoef { double a[L * L]; };
+template <int L> struct CavityCoef {
+  double a[L * L];
+  double odd;                                // sign of (1 - eta)^l for odd l
+};
 
 template <typename E, int L>
 __global__ void __launch_bounds__(TPB)
@@ -532,7 +536,7 @@ damp_cavity_reg_kernel(E* __restrict__ rho, int64_t ld, int n, int c, CavityCoef
 #pragma unroll
     for (int l = 0; j + l < L; ++l) {
       if (j + l >= len) break;
-      const double w = am[l] * ap[l];
+      const double w = (l & 1 ? k.odd : 1.0) * am[l] * ap[l];
       yr += w * xr[j + l];
       yi += w * xi[j + l];
     }
@@ -1134,10 +1138,11 @@ int launch_frame_phase_c64(const ModelArgs& m, c64* rho, int64_t ld, double t, h
 template <typename E, int L>
 int launch_cavity(const ModelArgs& m, E* rho, int64_t ld, double eta, hipStream_t s) {
   CavityCoef<L> k;
+  k.odd = eta > 1.0 ? -1.0 : 1.0;
   for (int mm = 0; mm < L; ++mm) {
     double v = std::pow(eta, 0.5 * mm);
     for (int l = 0; l < L; ++l) {
-      if (l > 0) v *= std::sqrt(double(mm + l) / double(l) * (1.0 - eta));
+      if (l > 0) v *= std::sqrt(double(mm + l) / double(l) * std::fabs(1.0 - eta));
       k.a[mm * L + l] = v;
     }
   }

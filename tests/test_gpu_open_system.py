@@ -180,6 +180,28 @@ def test_damping_alone_shapes(n, c, pad, dtype):
     assert torch.all(buf[:, N:] == 0)
 
 
+@pytest.mark.parametrize("n,c", [(3, 1), (2, 7), (3, 8), (2, 15), (2, 17)])
+@pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
+def test_damping_undone_by_negative_dt(n, c, dtype):
+    """U = I, one step by dt and one by -dt: e^{-dt L} undoes the channels (cavity
+    chains in registers of 8 and 16 levels and beyond).  The inverse's entries add
+    up to (2 / eta - 1)^c e^{gamma dt n} < 8 here, and each direction rounds an entry
+    a few times: 4e-6 of the largest entry in FP32, 1e-13 in FP64."""
+    inst = _open(n, c, 120 + c, 0.06, 0.09)
+    m = pipeline.model_of(inst)
+    U = torch.eye(m.N, dtype=torch.complex128, device="cuda")
+    rho0 = torch.from_numpy(inst.rho0()).to("cuda").to(dtype)
+    rho = rho0.clone()
+    mode = tcm.TC_GEMM_F64 if dtype == torch.complex128 else tcm.TC_GEMM_F32
+    pipeline.evolve(m, U, rho, 1, 0.7, mode, tcm.TC_FRAME_LAB, 0, 1)
+    changed = (rho - rho0).abs().max().item()
+    pipeline.evolve(m, U, rho, 1, -0.7, mode, tcm.TC_FRAME_LAB, 0, 1)
+    scale = rho0.abs().max().item()
+    assert changed > 0.02 * scale
+    err = (rho - rho0).abs().max().item()
+    assert err <= (1e-13 if dtype == torch.complex128 else 4e-6) * scale
+
+
 @pytest.mark.parametrize("mode,dtype", [(tcm.TC_GEMM_F32, torch.complex64),
                                         (tcm.TC_GEMM_F64, torch.complex128)])
 def test_batched_equals_single(mode, dtype):
