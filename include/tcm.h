@@ -237,7 +237,9 @@ int tc_evolve_workspace_size(const tc_instance* inst, int32_t count,
  * Record r (r = 0 .. steps/record_every) holds the readout after r*record_every
  * steps; record 0 is rho(0).  On return rho holds rho(steps) in the lab frame.
  * count > 1 steps uneven instances together (all share o).  ws: device
- * workspace of tc_evolve_workspace_size bytes.  Synchronises the stream only
+ * workspace of tc_evolve_workspace_size bytes (with sectors = 1 the tile shape
+ * of tc_autotune's table enters the size; a size queried before the table changed
+ * still runs, on 64 x 64 tiles).  Synchronises the stream only
  * when a renormalisation finds a non-finite trace (then TC_ERR_NONFINITE).
  * Results are bitwise reproducible on a given device; a product whose last
  * round of tiles is partial (split-BF16: would leave at least half of the

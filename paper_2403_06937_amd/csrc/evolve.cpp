@@ -111,7 +111,8 @@ void sector_sizes(int n, int c, std::vector<int64_t>& dim, std::vector<int64_t>&
   }
 }
 
-void plan_sectors(const tc_evolve_opts& o, Arena& ar, InstPlan* p) {
+// tile64: 64 x 64 tiles whatever the autotuner's table holds.
+void plan_sectors(const tc_evolve_opts& o, bool tile64, Arena& ar, InstPlan* p) {
   const int64_t N = p->N;
   const bool f64 = o.gemm_mode == TC_GEMM_F64;
   const size_t eb = f64 ? 16 : 8;
@@ -121,7 +122,7 @@ void plan_sectors(const tc_evolve_opts& o, Arena& ar, InstPlan* p) {
   p->sectors = true;
   std::vector<int64_t> off;
   sector_sizes(p->m.n, p->m.c, p->sdim, off);
-  p->svar = tile_variant_for(N, f64);
+  p->svar = tile64 ? 2 : tile_variant_for(N, f64);
   const int64_t q = split ? SPLIT_BM : (p->svar == 1 ? 128 : 64);
   const int ns = int(p->sdim.size());
   p->spo.assign(ns, 0);
@@ -193,8 +194,8 @@ void take_tail(Arena& ar, const tc_evolve_opts& o, InstPlan* plans, int count) {
   }
 }
 
-void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelArgs& m, Arena& ar,
-                   InstPlan* p) {
+void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelArgs& m, bool tile64,
+                   Arena& ar, InstPlan* p) {
   const int64_t N = in.N;
   const size_t NN = size_t(N) * size_t(N);
   p->m = m;
@@ -205,7 +206,7 @@ void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelAr
     p->counter = static_cast<int*>(ar.take(sizeof(int)));
   }
   if (o.sectors) {
-    plan_sectors(o, ar, p);
+    plan_sectors(o, tile64, ar, p);
     return;
   }
   if (p->in_sector >= 0)
@@ -1020,6 +1021,32 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   return TC_OK;
 }
 
+// One call's buffers.
+struct RunPlan {
+  std::vector<InstPlan> plans;
+  BatchBufs batch;
+};
+
+// Checks the arguments of a run and carves its buffers from ar (sizes only, when
+// ar has no memory).
+int plan_run(const tc_instance* inst, int count, const tc_evolve_opts* o, bool tile64, Arena& ar,
+             RunPlan* r) {
+  TC_CHECK_ARG(count >= 1, "count < 1");
+  TC_CHECK_ARG(inst != nullptr, "instances is NULL");
+  TC_RETURN_IF(validate_opts(o));
+  r->plans.assign(count, InstPlan());
+  for (int b = 0; b < count; ++b) {
+    ModelArgs m;
+    TC_RETURN_IF(validate_instance(&inst[b], o, &m));
+    plan_instance(inst[b], *o, m, tile64, ar, &r->plans[b]);
+  }
+  if (use_batched(count, *o))
+    plan_batch(ar, count, sector_items(inst, count, *o), &r->batch);
+  else
+    take_tail(ar, *o, r->plans.data(), count);
+  return TC_OK;
+}
+
 }  // namespace
 }  // namespace tcm
 
@@ -1031,22 +1058,9 @@ int tc_evolve_workspace_size(const tc_instance* inst, int32_t count, const tc_ev
                              size_t* bytes) {
   clear_error();
   TC_CHECK_ARG(bytes != nullptr, "bytes is NULL");
-  TC_CHECK_ARG(count >= 1, "count < 1");
-  TC_CHECK_ARG(inst != nullptr, "instances is NULL");
-  TC_RETURN_IF(validate_opts(o));
   Arena ar(nullptr, 0);
-  std::vector<InstPlan> plans(count);
-  for (int b = 0; b < count; ++b) {
-    ModelArgs m;
-    TC_RETURN_IF(validate_instance(&inst[b], o, &m));
-    plan_instance(inst[b], *o, m, ar, &plans[b]);
-  }
-  if (use_batched(count, *o)) {
-    BatchBufs bb;
-    plan_batch(ar, count, sector_items(inst, count, *o), &bb);
-  } else {
-    take_tail(ar, *o, plans.data(), count);
-  }
+  RunPlan run;
+  TC_RETURN_IF(plan_run(inst, count, o, false, ar, &run));
   *bytes = ar.used;
   return TC_OK;
 }
@@ -1054,27 +1068,27 @@ int tc_evolve_workspace_size(const tc_instance* inst, int32_t count, const tc_ev
 int tc_evolve(const tc_instance* inst, int32_t count, const tc_evolve_opts* o, void* ws,
               size_t ws_bytes, void* stream) {
   clear_error();
-  size_t need = 0;
-  TC_RETURN_IF(tc_evolve_workspace_size(inst, count, o, &need));
-  TC_CHECK_ARG(ws != nullptr || need == 0, "workspace is NULL");
-  if (ws_bytes < need) {
-    set_error("workspace too small for tc_evolve: need " + std::to_string(need) + " bytes");
-    return TC_ERR_WORKSPACE;
+  // What is checked against the workspace is the plan that runs: the autotuner's
+  // table, which chooses the tile the sector blocks are padded to, may change
+  // between the size query and this call, and on another thread during it.
+  Arena ar(ws, ws_bytes);
+  RunPlan run;
+  TC_RETURN_IF(plan_run(inst, count, o, false, ar, &run));
+  TC_CHECK_ARG(ws != nullptr || ar.used == 0, "workspace is NULL");
+  if (!ar.fits()) {
+    const size_t need = ar.used;
+    ar = Arena(ws, ws_bytes);            // 64 x 64 tiles pad least
+    TC_RETURN_IF(plan_run(inst, count, o, true, ar, &run));
+    if (!ar.fits()) {
+      set_error("workspace too small for tc_evolve: need " + std::to_string(need) + " bytes");
+      return TC_ERR_WORKSPACE;
+    }
   }
   hipStream_t s = as_stream(stream);
-  Arena ar(ws, ws_bytes);
-  std::vector<InstPlan> plans(count);
-  for (int b = 0; b < count; ++b) {
-    ModelArgs m;
-    TC_RETURN_IF(validate_instance(&inst[b], o, &m));
-    plan_instance(inst[b], *o, m, ar, &plans[b]);
-  }
+  std::vector<InstPlan>& plans = run.plans;
   if (use_batched(count, *o)) {
-    BatchBufs bb;
-    plan_batch(ar, count, sector_items(inst, count, *o), &bb);
-    TC_RETURN_IF(evolve_batched(plans, inst, count, *o, bb, s));
+    TC_RETURN_IF(evolve_batched(plans, inst, count, *o, run.batch, s));
   } else {
-    take_tail(ar, *o, plans.data(), count);
     for (int b = 0; b < count; ++b) TC_RETURN_IF(evolve_one(plans[b], inst[b], *o, s));
   }
   if (o->renorm_every > 0 && o->steps >= o->renorm_every) {
@@ -1119,7 +1133,7 @@ int tc_evolve_sector_workspace_size(const tc_instance* inst, int32_t k, const tc
   Arena ar(nullptr, 0);
   InstPlan p;
   p.in_sector = k;
-  plan_instance(*inst, *o, m, ar, &p);
+  plan_instance(*inst, *o, m, false, ar, &p);
   take_tail(ar, *o, &p, 1);
   *bytes = ar.used;
   return TC_OK;
@@ -1141,7 +1155,7 @@ int tc_evolve_sector(const tc_instance* inst, int32_t k, const tc_evolve_opts* o
   Arena ar(ws, ws_bytes);
   InstPlan p;
   p.in_sector = k;
-  plan_instance(*inst, *o, m, ar, &p);
+  plan_instance(*inst, *o, m, false, ar, &p);
   take_tail(ar, *o, &p, 1);
   TC_RETURN_IF(evolve_one(p, *inst, *o, s));
   if (o->renorm_every > 0 && o->steps >= o->renorm_every) {

@@ -3,6 +3,10 @@ GPU: against the oracle's dense evolution and against the dense GPU products,
 on ragged sizes, both frames, with records, checkpoints,
 renormalisation and the Lindblad term, in FP64, FP32 and split-BF16; plus
 the degenerate cases (no cavity photons, one atom, zero steps)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -242,3 +246,53 @@ def test_batched_sectors(mode, frame, dtype, tol):
         err = float(np.max(np.abs(a[0][k] - ref)))
         perr = float(np.max(np.abs(a[1][k] - rpop)))
         assert err < tol and perr < tol, (k, err, perr)
+
+
+TABLE_RUN = """
+import sys, torch
+import numpy as np
+import paper_2403_06937_amd as tcm
+from paper_2403_06937_amd import pipeline
+import tcm_inputs as ti
+mode, size = int(sys.argv[1]), int(sys.argv[2])
+dtype = torch.complex128 if mode == tcm.TC_GEMM_F64 else torch.complex64
+rdt = tcm.TC_C128 if mode == tcm.TC_GEMM_F64 else tcm.TC_C64
+insts = [ti.random_model(n, c, 430 + n, state="gaussian") for n, c in ((5, 2), (6, 1))]
+opts = tcm.make_opts(12, 0.05, mode, rdt, tcm.TC_FRAME_ROTATING, sectors=1)
+models = [pipeline.model_of(i) for i in insts]
+rhos = [torch.from_numpy(i.rho0()).to("cuda").to(dtype) for i in insts]
+Us = [pipeline.propagator(m, 0.05)[1] for m in models]
+inst = [tcm.make_instance(m, U, r) for m, U, r in zip(models, Us, rhos)]
+need = tcm.tc_evolve_workspace_size(inst, opts)
+print(need)
+if size:
+    assert need > size
+    tcm.tc_evolve(inst, opts, ws=torch.empty(size, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    np.savez(sys.argv[3], *[r.cpu().numpy() for r in rhos])
+"""
+
+
+@pytest.mark.parametrize("mode,tol", [(tcm.TC_GEMM_F64, 1e-10), (tcm.TC_GEMM_F32, 1e-5)])
+def test_workspace_sized_before_the_table_changed(mode, tol, tmp_path):
+    """A workspace sized while the autotuner's table held 64 x 64 tiles still runs
+    once it holds 128 x 128 (which pad the blocks further): a batch of N = 96 and
+    128 against the oracle.  Each table comes from a cache file, in a process of its
+    own."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+    def run(v, size, out):
+        path = tmp_path / f"table{v}.json"
+        path.write_text('{"f32": [%d, %d, %d, %d], "f64": [%d, %d, %d, %d]}' % ((v,) * 8))
+        r = subprocess.run([sys.executable, "-c", TABLE_RUN, str(mode), str(size), out], cwd=root,
+                           env=dict(os.environ, TC_AUTOTUNE_CACHE=str(path)),
+                           capture_output=True, text=True, timeout=100)
+        assert r.returncode == 0, r.stderr
+        return int(r.stdout)
+
+    out = str(tmp_path / "rho.npz")
+    run(1, run(2, 0, ""), out)
+    z = np.load(out)
+    for k, (n, c) in enumerate(((5, 2), (6, 1))):
+        ref, _, _ = _oracle(ti.random_model(n, c, 430 + n, state="gaussian"), 0.05, 12)
+        assert np.max(np.abs(z[f"arr_{k}"] - ref)) <= tol
