@@ -237,11 +237,14 @@ int tc_evolve_workspace_size(const tc_instance* inst, int32_t count,
  * Record r (r = 0 .. steps/record_every) holds the readout after r*record_every
  * steps; record 0 is rho(0).  On return rho holds rho(steps) in the lab frame.
  * count > 1 steps uneven instances together (all share o).  ws: device
- * workspace of tc_evolve_workspace_size bytes (with sectors = 1 the tile shape
+ * workspace of tc_evolve_workspace_size bytes.  (With sectors = 1 the tile shape
  * of tc_autotune's table enters the size; a size queried before the table changed
- * still runs, on 64 x 64 tiles).  Synchronises the stream only
+ * still runs, on 64 x 64 tiles.  Of the memory for partial sums of a large dense
+ * step, 67 MB in FP64 and 34 MB otherwise suffice; with less than the full size
+ * fewer compute units share a product's last round of tiles.)  Synchronises the stream only
  * when a renormalisation finds a non-finite trace (then TC_ERR_NONFINITE).
- * Results are bitwise reproducible on a given device; a product whose last
+ * Results are bitwise reproducible on a given device with a workspace of the same
+ * size; a product whose last
  * round of tiles is partial (split-BF16: would leave at least half of the
  * compute units idle) has those tiles' K sums split into ranges that are
  * added in order, and how it is split depends on the device's compute-unit

@@ -304,6 +304,7 @@ int tc_expm(const double* H, int64_t N, int64_t ldh, double dt, double lam_lo, d
   if (ldu == N) {
     g.tail = U;
     g.tail_bytes = size_t(N) * size_t(N) * sizeof(tc_c128);
+    g.spread = true;
   }
   double *C = nullptr, *S = nullptr;
   TC_RETURN_IF(cos_sin(L, g, cc, cs, &C, &S));

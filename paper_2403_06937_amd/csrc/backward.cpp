@@ -77,10 +77,17 @@ void bwd_layout(Arena& ar, int64_t N, const tc_evolve_opts& o, BwdLayout* L) {
   if (!L->f64) L->T = ar.take(NN * 8);
   ar.used = std::max(ar.used, sub.used);
   L->scratch = static_cast<double*>(ar.take(8 * sizeof(double)));
-  if (tail_slots(N) > 0) {
-    L->tail.bytes = size_t(tail_slots(N)) * 128 * 128 * 16;
-    L->tail.p = ar.take(L->tail.bytes);
+  // partial sums of the sweep's complex products and of the derivative's real ones
+  GemmDesc d;
+  d.M = d.N = d.K = N;
+  d.spread = true;
+  for (const bool herm : {false, true}) {
+    d.herm = herm;
+    L->tail.bytes = std::max(L->tail.bytes, gemm_tail_bytes(d, L->f64));
   }
+  d.complex = false;
+  L->tail.bytes = std::max(L->tail.bytes, gemm_tail_bytes(d, true));
+  if (L->tail.bytes > 0) L->tail.p = ar.take_at_most(&L->tail.bytes, tail_least_bytes(true));
 }
 
 // General complex product in the sweep precision: C = alpha op(A) op(B) + beta C.
@@ -88,7 +95,7 @@ int cgemm(const TailWs& tw, bool f64, int64_t N, const void* A, int64_t lda, boo
           bool conj_a, const void* B, int64_t ldb, bool b_kmaj, bool conj_b, void* C, int64_t ldc,
           double alpha_re, double beta_re, hipStream_t s) {
   GemmDesc d;
-  d.tail_ws = tw.p; d.tail_ws_bytes = tw.bytes;
+  d.tail_ws = tw.p; d.tail_ws_bytes = tw.bytes; d.spread = true;
   d.M = d.N = d.K = N;
   d.A = A; d.lda = lda; d.a_kmaj = a_kmaj; d.conj_a = conj_a;
   d.B = B; d.ldb = ldb; d.b_kmaj = b_kmaj; d.conj_b = conj_b;
@@ -104,7 +111,7 @@ int cgemm_in(const TailWs& tw, bool f64, int64_t N, const void* A, int64_t lda, 
              bool conj_a, const void* B, int64_t ldb, bool b_kmaj, bool conj_b, void* C,
              int64_t ldc, const void* Cin, hipStream_t s, bool herm = false) {
   GemmDesc d;
-  d.tail_ws = tw.p; d.tail_ws_bytes = tw.bytes;
+  d.tail_ws = tw.p; d.tail_ws_bytes = tw.bytes; d.spread = true;
   d.herm = herm;
   d.M = d.N = d.K = N;
   d.A = A; d.lda = lda; d.a_kmaj = a_kmaj; d.conj_a = conj_a;
@@ -578,12 +585,18 @@ int tc_evolve_backward(const tc_model* m, const double* H, int64_t ldh, const tc
   TC_CHECK_ARG(ldh >= N && ldu >= N, "leading dimension < N");
   TC_CHECK_ARG(std::isfinite(o->dt), "dt not finite");
   TC_CHECK_ARG(ws != nullptr, "workspace is NULL");
-  if (ws_bytes < need) {
-    set_error("workspace too small for tc_evolve_backward: need " + std::to_string(need));
-    return TC_ERR_WORKSPACE;
-  }
   ModelArgs a;
   TC_RETURN_IF(make_model_args(m, &a));
+  tc_evolve_opts oo = *o;
+  if (oo.gemm_mode == TC_GEMM_SPLIT_BF16) oo.gemm_mode = TC_GEMM_F32;
+  Arena ar(ws, ws_bytes);
+  BwdLayout L;
+  if (!oo.sectors) bwd_layout(ar, N, oo, &L);
+  if (oo.sectors ? ws_bytes < need : !ar.fits()) {
+    set_error("workspace too small for tc_evolve_backward: need at least " +
+              std::to_string(oo.sectors ? need : ar.used) + " bytes");
+    return TC_ERR_WORKSPACE;
+  }
   // Gershgorin interval of H' = H - w_c N_exc: centre sum_i (w_a,i - w_c) l_i,
   // radius of the couplings leaving the state
   double lam_lo = INFINITY, lam_hi = -INFINITY;
@@ -604,16 +617,10 @@ int tc_evolve_backward(const tc_model* m, const double* H, int64_t ldh, const tc
       lam_hi = std::max(lam_hi, centre + radius);
     }
   }
-  tc_evolve_opts oo = *o;
-  if (oo.gemm_mode == TC_GEMM_SPLIT_BF16) oo.gemm_mode = TC_GEMM_F32;
-
   hipStream_t s = as_stream(stream);
-  Arena ar(ws, ws_bytes);
   if (oo.sectors)
     return backward_by_sectors(a, H, ldh, reinterpret_cast<const c128*>(U), ldu, N, oo,
                                checkpoints, lam_lo, lam_hi, loss_out, grad_g, grad_delta, ar, s);
-  BwdLayout L;
-  bwd_layout(ar, N, oo, &L);
   const bool f64 = L.f64;
   const size_t NN = size_t(N) * size_t(N);
   const int64_t S = oo.steps, C = oo.checkpoint_every;
@@ -638,6 +645,7 @@ int tc_evolve_backward(const tc_model* m, const double* H, int64_t ldh, const tc
     g2.herm = true;   // the state after the step is Hermitian
     g1.tail_ws = g2.tail_ws = L.tail.p;
     g1.tail_ws_bytes = g2.tail_ws_bytes = L.tail.bytes;
+    g1.spread = g2.spread = true;
     TC_RETURN_IF(f64 ? gemm_f64(g1, s) : gemm_f32(g1, s));
     return f64 ? gemm_f64(g2, s) : gemm_f32(g2, s);
   };
@@ -721,6 +729,7 @@ int tc_evolve_backward(const tc_model* m, const double* H, int64_t ldh, const tc
   g.s = s;
   g.tail = L.tail.p;
   g.tail_bytes = L.tail.bytes;
+  g.spread = true;
   double *Gr = nullptr, *Gi = nullptr;
   TC_RETURN_IF(frechet(a, H, ldh, mu, dt, sc, q, L.M, L.F, g, &Gr, &Gi));
   const double ph = -mu * dt;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <algorithm>
 #include <string>
 
 #include "../../include/tcm.h"
@@ -77,6 +78,13 @@ struct Arena {
     size_t off = align_up(used, 256);
     used = off + align_up(bytes, 256);
     return base ? base + off : nullptr;
+  }
+  // Up to *bytes, as many as are left but not fewer than least; *bytes: how many.
+  void* take_at_most(size_t* bytes, size_t least) {
+    const size_t off = align_up(used, 256);
+    const size_t left = cap > off ? (cap - off) / 256 * 256 : 0;
+    if (base && left < *bytes) *bytes = std::min(*bytes, std::max(left, least));
+    return take(*bytes);
   }
   bool fits() const { return used <= cap; }
 };

@@ -161,27 +161,30 @@ void plan_sectors(const tc_evolve_opts& o, bool tile64, Arena& ar, InstPlan* p) 
   }
 }
 
-// Slots for the partial sums of a dense product's last round: one 128 x 128
-// tile of complex elements per slot (16 B in FP64, 8 B as FP32 in the FP32 and
-// split-BF16 products; at most 134 MB in FP64).  The split-BF16 product cuts
-// every tile of its last round into the same number of ranges, at most 256.
+void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDesc& g2);
+
+// Memory for the partial sums of a dense step's products, none where the small
+// kernels run (at most 101 MB in FP64, 67 in FP32).  The split-BF16 product cuts
+// every tile of its last round into the same number of ranges, at most 256, one
+// 128 x 128 tile of complex FP32 each.
 size_t tail_bytes(const InstPlan& p, const tc_evolve_opts& o) {
   if (o.sectors) return 0;
-  const size_t eb = o.gemm_mode == TC_GEMM_F64 ? 16 : 8;
-  const int64_t t = (p.N + 127) / 128;
-  const int64_t slots = o.gemm_mode == TC_GEMM_SPLIT_BF16
-                            ? (t < 2 ? 0 : std::min<int64_t>(256, 8 * t * t))
-                            : tail_slots(p.N);
-  return size_t(slots) * 128 * 128 * eb;
+  if (o.gemm_mode == TC_GEMM_SPLIT_BF16) return split_small_step(p.N) ? 0 : tail_least_bytes(false);
+  const bool f64 = o.gemm_mode == TC_GEMM_F64;
+  GemmDesc g1, g2;
+  step_descs(p, o, g1, g2);
+  return std::max(gemm_tail_bytes(g1, f64), gemm_tail_bytes(g2, f64));
 }
 
-// One region of slots for instances stepped one after another on one
-// stream (a single instance, or a batch that is not a grouped launch).
+// One region for instances stepped one after another on one stream (a single
+// instance, or a batch that is not a grouped launch).  In a workspace that does
+// not hold all of it, it is what is left, down to tail_least_bytes: the products
+// then cut their last round into fewer ranges.
 void take_tail(Arena& ar, const tc_evolve_opts& o, InstPlan* plans, int count) {
   size_t bytes = 0;
   for (int b = 0; b < count; ++b) bytes = std::max(bytes, tail_bytes(plans[b], o));
   if (bytes == 0) return;
-  void* ws = ar.take(bytes);
+  void* ws = ar.take_at_most(&bytes, tail_least_bytes(o.gemm_mode == TC_GEMM_F64));
   for (int b = 0; b < count; ++b) {
     if (tail_bytes(plans[b], o) == 0) continue;
     if (o.gemm_mode == TC_GEMM_SPLIT_BF16) {
@@ -210,7 +213,7 @@ void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelAr
     return;
   }
   if (p->in_sector >= 0)
-    p->sec_off = static_cast<int32_t*>(ar.take(std::max(size_t(m.N), size_t(m.c) + 2) * 4));
+    p->sec_off = static_cast<int32_t*>(ar.take((size_t(m.c) + 2) * 4));
   if (o.gemm_mode == TC_GEMM_F64) {
     if (o.rho_dtype == TC_C128) {
       p->rho = in.rho; p->ldr = in.ldr; p->rho_converted = false;
@@ -334,8 +337,6 @@ int renorm(InstPlan& p, const tc_evolve_opts& o, hipStream_t s) {
     TC_RETURN_IF(split_state(static_cast<const c64*>(p.rho), p.ldr, p.N, p.planes, s));
   return TC_OK;
 }
-
-void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDesc& g2);
 
 // One step of Eq. (6) for FP64 / FP32:
 //   lab:      X = U rho,          rho' = X U^dag = X conj(U)   (U symmetric)
@@ -854,7 +855,7 @@ void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDe
   g1.B = p.rho; g1.ldb = p.ldr; g1.b_kmaj = true;
   g1.C = p.X; g1.ldc = p.ldx;
   if (rot) { g1.Cin = p.rho; g1.ldcin = p.ldr; g1.beta_re = 1.0; }
-  g1.tail_ws = p.tail_ws; g1.tail_ws_bytes = p.tail_ws_bytes;
+  g1.tail_ws = p.tail_ws; g1.tail_ws_bytes = p.tail_ws_bytes; g1.spread = true;
   g2 = GemmDesc();
   g2.M = g2.N = g2.K = p.N;
   g2.A = p.X; g2.lda = p.ldx; g2.a_kmaj = false;
@@ -862,7 +863,7 @@ void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDe
   g2.C = p.rho; g2.ldc = p.ldr;
   if (rot) { g2.Cin = p.X; g2.ldcin = p.ldx; g2.beta_re = 1.0; }
   g2.herm = o.full_product == 0;
-  g2.tail_ws = p.tail_ws; g2.tail_ws_bytes = p.tail_ws_bytes;
+  g2.tail_ws = p.tail_ws; g2.tail_ws_bytes = p.tail_ws_bytes; g2.spread = true;
 }
 
 // Block products of one product phase over all instances of a batch: at most
@@ -1047,6 +1048,33 @@ int plan_run(const tc_instance* inst, int count, const tc_evolve_opts* o, bool t
   return TC_OK;
 }
 
+// The same for a run within excitation sector k.
+int plan_sector_run(const tc_instance* inst, int32_t k, const tc_evolve_opts* o, Arena& ar,
+                    InstPlan* p) {
+  TC_CHECK_ARG(inst != nullptr, "instance is NULL");
+  TC_RETURN_IF(validate_opts(o));
+  TC_CHECK_ARG(o->sectors == 0, "sectors must be 0 for a one-sector run");
+  int64_t d = 0;
+  TC_RETURN_IF(tc_sector_dim(inst->model, k, &d));
+  ModelArgs m;
+  TC_RETURN_IF(make_model_args(inst->model, &m));
+  if (m.kappa > 0.0 || m.gamma > 0.0) {
+    set_error("the damping channels lead out of an excitation sector");
+    return TC_ERR_UNSUPPORTED;
+  }
+  TC_CHECK_ARG(inst->N == d, "instance N != d_k of the sector");
+  TC_CHECK_ARG(inst->U != nullptr && inst->rho != nullptr, "U / rho is NULL");
+  TC_CHECK_ARG(inst->ldu >= d && inst->ldr >= d, "leading dimension < d_k");
+  if (inst->pop_out || inst->photon_dist_out || inst->photon_state_out)
+    TC_CHECK_ARG(o->record_every >= 1, "record_every must be >= 1 when records are requested");
+  if (inst->checkpoints)
+    TC_CHECK_ARG(o->checkpoint_every >= 1, "checkpoint_every must be >= 1 with checkpoints");
+  p->in_sector = k;
+  plan_instance(*inst, *o, m, false, ar, p);
+  take_tail(ar, *o, p, 1);
+  return TC_OK;
+}
+
 }  // namespace
 }  // namespace tcm
 
@@ -1080,7 +1108,8 @@ int tc_evolve(const tc_instance* inst, int32_t count, const tc_evolve_opts* o, v
     ar = Arena(ws, ws_bytes);            // 64 x 64 tiles pad least
     TC_RETURN_IF(plan_run(inst, count, o, true, ar, &run));
     if (!ar.fits()) {
-      set_error("workspace too small for tc_evolve: need " + std::to_string(need) + " bytes");
+      set_error("workspace too small for tc_evolve: need at least " + std::to_string(need) +
+                " bytes");
       return TC_ERR_WORKSPACE;
     }
   }
@@ -1112,29 +1141,9 @@ int tc_evolve_sector_workspace_size(const tc_instance* inst, int32_t k, const tc
                                     size_t* bytes) {
   clear_error();
   TC_CHECK_ARG(bytes != nullptr, "bytes is NULL");
-  TC_CHECK_ARG(inst != nullptr, "instance is NULL");
-  TC_RETURN_IF(validate_opts(o));
-  TC_CHECK_ARG(o->sectors == 0, "sectors must be 0 for a one-sector run");
-  int64_t d = 0;
-  TC_RETURN_IF(tc_sector_dim(inst->model, k, &d));
-  ModelArgs m;
-  TC_RETURN_IF(make_model_args(inst->model, &m));
-  if (m.kappa > 0.0 || m.gamma > 0.0) {
-    set_error("the damping channels lead out of an excitation sector");
-    return TC_ERR_UNSUPPORTED;
-  }
-  TC_CHECK_ARG(inst->N == d, "instance N != d_k of the sector");
-  TC_CHECK_ARG(inst->U != nullptr && inst->rho != nullptr, "U / rho is NULL");
-  TC_CHECK_ARG(inst->ldu >= d && inst->ldr >= d, "leading dimension < d_k");
-  if (inst->pop_out || inst->photon_dist_out || inst->photon_state_out)
-    TC_CHECK_ARG(o->record_every >= 1, "record_every must be >= 1 when records are requested");
-  if (inst->checkpoints)
-    TC_CHECK_ARG(o->checkpoint_every >= 1, "checkpoint_every must be >= 1 with checkpoints");
   Arena ar(nullptr, 0);
   InstPlan p;
-  p.in_sector = k;
-  plan_instance(*inst, *o, m, false, ar, &p);
-  take_tail(ar, *o, &p, 1);
+  TC_RETURN_IF(plan_sector_run(inst, k, o, ar, &p));
   *bytes = ar.used;
   return TC_OK;
 }
@@ -1142,21 +1151,16 @@ int tc_evolve_sector_workspace_size(const tc_instance* inst, int32_t k, const tc
 int tc_evolve_sector(const tc_instance* inst, int32_t k, const tc_evolve_opts* o, void* ws,
                      size_t ws_bytes, void* stream) {
   clear_error();
-  size_t need = 0;
-  TC_RETURN_IF(tc_evolve_sector_workspace_size(inst, k, o, &need));
-  TC_CHECK_ARG(ws != nullptr || need == 0, "workspace is NULL");
-  if (ws_bytes < need) {
-    set_error("workspace too small for tc_evolve_sector: need " + std::to_string(need) + " bytes");
+  Arena ar(ws, ws_bytes);
+  InstPlan p;
+  TC_RETURN_IF(plan_sector_run(inst, k, o, ar, &p));
+  TC_CHECK_ARG(ws != nullptr || ar.used == 0, "workspace is NULL");
+  if (!ar.fits()) {
+    set_error("workspace too small for tc_evolve_sector: need at least " +
+              std::to_string(ar.used) + " bytes");
     return TC_ERR_WORKSPACE;
   }
   hipStream_t s = as_stream(stream);
-  ModelArgs m;
-  TC_RETURN_IF(make_model_args(inst->model, &m));
-  Arena ar(ws, ws_bytes);
-  InstPlan p;
-  p.in_sector = k;
-  plan_instance(*inst, *o, m, false, ar, &p);
-  take_tail(ar, *o, &p, 1);
   TC_RETURN_IF(evolve_one(p, *inst, *o, s));
   if (o->renorm_every > 0 && o->steps >= o->renorm_every) {
     double flag = 0.0;

@@ -35,20 +35,20 @@ struct GemmDesc {
   // optional device buffer for a product's last round split over K (partial
   // sums of its tiles); nullptr: one pass per tile
   void* tail_ws = nullptr; size_t tail_ws_bytes = 0;
+  // The caller keeps such a buffer for the products that use one (gemm_tail_bytes):
+  // small products then end where larger tiles with a spread last round win.
+  bool spread = false;
 };
-
-// Slots of one 128 x 128 tile that the partial sums of an N x N product's last
-// round take: one per range and one more per tile that a range ends in (at
-// most 256 ranges, of at least 4 K tiles each, over fewer than 256 tiles); none
-// for a single tile row, whose K is too short to split.
-inline int64_t tail_slots(int64_t N) {
-  const int64_t t = (N + 127) / 128;
-  if (t < 2) return 0;
-  return t >= 8 ? 511 : (2 * t * t * t + t * t < 511 ? 2 * t * t * t + t * t : 511);
-}
 
 int gemm_f64(const GemmDesc& d, hipStream_t s);   // elements double / cplx<double>
 int gemm_f32(const GemmDesc& d, hipStream_t s);   // elements float / cplx<float>
+
+// Bytes of tail_ws that the product can use on a device of up to 256 compute units
+// (0: none; operand pointers are not read).  With fewer it runs on fewer ranges.
+size_t gemm_tail_bytes(const GemmDesc& d, bool f64);
+// What such a buffer holds at least where one is of use: 256 slots of a complex
+// 128 x 128 tile.  A workspace with room for no more runs.
+constexpr size_t tail_least_bytes(bool f64) { return size_t(256) * 128 * 128 * (f64 ? 16 : 8); }
 
 // Grouped complex products (A and B row-major, the layout of the time step):
 // every product of the group shares one tile shape and one launch.

@@ -1006,8 +1006,36 @@ template <> struct Variants<float, false> {
 
 int device_cus();
 
+// The last, partial round of `tiles` tiles of kt K tiles each, on a device that
+// runs `round` workgroups at a time, as equal ranges of at least `least` K tiles
+// (none, tail = 0 and every tile whole, unless that saves the time of `least` K
+// tiles: storing and adding the partial sums costs about as much).
+TailSplit tail_split(int64_t tiles, int64_t kt, int64_t round, int64_t least, int64_t slots) {
+  TailSplit ts;
+  ts.kt = kt;
+  ts.base = int(tiles / round * round);
+  ts.tail = int(tiles - ts.base);
+  ts.G = int(std::min<int64_t>(std::min<int64_t>(round, ts.tail * kt / least),
+                               slots - ts.tail + 1));
+  if (!(ts.tail > 0 && ts.G > ts.tail && kt * (ts.G - ts.tail) >= least * int64_t(ts.G))) {
+    ts.base = int(tiles);
+    ts.tail = ts.G = 0;
+  }
+  return ts;
+}
+
+// The slots that tail_split's ranges use (one per range and one more per tile
+// that a range ends in), for any round up to `round`.
+int64_t tail_slots(int64_t tiles, int64_t kt, int64_t round, int64_t least) {
+  if (kt <= least || tiles < 1) return 0;
+  return std::min<int64_t>(tiles, round - 1) + std::min<int64_t>(round, tiles * kt / least) - 1;
+}
+
+constexpr int64_t MAX_CUS = 256;     // of an unpartitioned MI355X
+
+// need != nullptr: only the bytes of tail_ws that the product can use.
 template <typename T, bool CPLX, bool AK, bool BK, typename S>
-int launch_shape(const GemmDesc& d, hipStream_t s) {
+int launch_shape(const GemmDesc& d, hipStream_t s, size_t* need) {
   Params p;
   p.M = d.M; p.N = d.N; p.K = d.K;
   p.A = d.A; p.lda = d.lda; p.B = d.B; p.ldb = d.ldb;
@@ -1025,21 +1053,21 @@ int launch_shape(const GemmDesc& d, hipStream_t s) {
   if (tiles > (int64_t(1) << 31) - 1) { set_error("product too large"); return TC_ERR_UNSUPPORTED; }
   const bool exact = d.M % S::BM == 0 && d.N % S::BN == 0 && d.K % S::BKT == 0 && d.K > 0;
   const dim3 grid{unsigned(tiles), 1u, 1u}, block{unsigned(S::NT), 1u, 1u};
+  // a partial last round (the whole product, when it has fewer tiles than CUs) is
+  // spread over the CUs in ranges of at least 4 K tiles (a K tile of a 128 x 128
+  // FP64 tile takes 7 us)
+  const size_t slot = size_t(S::BM) * S::BN * (CPLX ? 2 : 1) * sizeof(T);
+  const int64_t kt = d.K / S::BKT;
+  if (need) {
+    *need = exact ? size_t(tail_slots(tiles, kt, MAX_CUS, 4)) * slot : 0;
+    return TC_OK;
+  }
   ProfileScope prof(sizeof(T) == 8 ? TC_KERNEL_GEMM_F64 : TC_KERNEL_GEMM_F32, s);
   if (exact && d.tail_ws) {
-    // a partial last round (the whole product, when it has fewer tiles than
-    // CUs) is spread over the CUs, ranges of at least 4 K tiles each, when that
-    // saves at least 4 K tiles' time (about what storing and adding the partial
-    // sums costs; a K tile of a 128 x 128 FP64 tile takes 7 us)
-    const int cus = device_cus();
-    const size_t slot = size_t(S::BM) * S::BN * (CPLX ? 2 : 1) * sizeof(T);
-    TailSplit ts;
-    ts.kt = d.K / S::BKT;
-    ts.base = int(tiles / cus * cus);
-    ts.tail = int(tiles - ts.base);
-    const int64_t slots = std::min<int64_t>(int64_t(d.tail_ws_bytes / slot), 1 << 20);
-    ts.G = int(std::min<int64_t>(std::min<int64_t>(cus, ts.tail * ts.kt / 4), slots - ts.tail + 1));
-    if (ts.tail > 0 && ts.G > ts.tail && ts.kt * (ts.G - ts.tail) >= 4 * int64_t(ts.G)) {
+    const TailSplit ts =
+        tail_split(tiles, kt, device_cus(), 4,
+                   std::min<int64_t>(int64_t(d.tail_ws_bytes / slot), 1 << 20));
+    if (ts.tail > 0) {
       if (ts.base > 0) {
         hipLaunchKernelGGL((gemm_kernel<T, CPLX, AK, BK, false, S::BM, S::BN, S::BKT, S::WM,
                                         S::WN, S::PADB>),
@@ -1097,25 +1125,20 @@ bool direct_product(const GemmDesc& d) {
 }
 
 template <bool CPLX>
-int launch_direct(const GemmDesc& d, hipStream_t s) {
+int launch_direct(const GemmDesc& d, hipStream_t s, size_t* need) {
   typedef Direct<CPLX> D;
   const Params p = make_params<Shp<D::EDGE, D::EDGE, 8, D::W, D::W>>(d);
   const int64_t tiles = p.herm ? int64_t(p.tiles_m) * (p.tiles_m + 1) / 2
                                : int64_t(p.tiles_m) * p.tiles_n;
   if (tiles > (int64_t(1) << 30)) { set_error("product too large"); return TC_ERR_UNSUPPORTED; }
-  // a partial last round is spread over the CUs when that saves at least the time
-  // of 8 slices (storing and adding the partial sums costs about as much)
-  const int64_t round = int64_t(device_cus()) * D::PER_CU;
-  const int64_t slots = std::min<int64_t>(d.tail_ws ? int64_t(d.tail_ws_bytes / D::SLOT) : 0, 1 << 20);
-  TailSplit ts;
-  ts.kt = d.K / 8;
-  ts.base = int(tiles / round * round);
-  ts.tail = int(tiles - ts.base);
-  ts.G = int(std::min<int64_t>(std::min<int64_t>(round, ts.tail * ts.kt / 8), slots - ts.tail + 1));
-  if (!(ts.tail > 0 && ts.G > ts.tail && ts.kt * (ts.G - ts.tail) >= 8 * int64_t(ts.G))) {
-    ts.base = int(tiles);
-    ts.tail = ts.G = 0;
+  // a partial last round is spread over the CUs in ranges of at least 8 slices
+  if (need) {
+    *need = size_t(tail_slots(tiles, d.K / 8, MAX_CUS * D::PER_CU, 8)) * D::SLOT;
+    return TC_OK;
   }
+  const int64_t slots = std::min<int64_t>(d.tail_ws ? int64_t(d.tail_ws_bytes / D::SLOT) : 0, 1 << 20);
+  const TailSplit ts =
+      tail_split(tiles, d.K / 8, int64_t(device_cus()) * D::PER_CU, 8, slots);
   ProfileScope prof(TC_KERNEL_GEMM_F64, s);
   hipLaunchKernelGGL(gemm_direct_kernel<CPLX>, dim3(unsigned(ts.base + ts.G)), dim3(DIRECT_NT), 0, s,
                      p, ts, d.tail_ws);
@@ -1129,10 +1152,14 @@ int launch_direct(const GemmDesc& d, hipStream_t s) {
 }
 
 template <typename T, bool CPLX>
-int launch2(const GemmDesc& d, hipStream_t s) {
+int launch2(const GemmDesc& d, hipStream_t s, size_t* need) {
   typedef Variants<T, CPLX> V;
   if constexpr (CPLX)
-    if (variant_for(-1) < 0 && small_product(d, sizeof(T) == 8)) return small_gemm<T>(d, nullptr, s);
+    if (variant_for(-1) < 0 && small_product(d, sizeof(T) == 8)) {
+      if (!need) return small_gemm<T>(d, nullptr, s);
+      *need = 0;
+      return TC_OK;
+    }
   // FP64: direct tiles (2 N = 2304 products a step 2.19 ms on 128 x 128 LDS tiles
   // with a spread last round, 2.14 on direct ones; 1536 700 -> 671 us, 5120
   // 22.7 -> 22.1 ms; ragged tiles, range-checked in LDS, N = 1088 1.08 -> 0.28 ms,
@@ -1141,28 +1168,28 @@ int launch2(const GemmDesc& d, hipStream_t s) {
   // buffer for K ranges, take 64 x 64 LDS tiles instead, four times the
   // workgroups: U at N = 768 310 us against 511, 1536 968 against 906.
   const int64_t t128 = ((d.M + 127) / 128) * ((d.N + 127) / 128);
-  const int64_t few = CPLX ? 16 : d.tail_ws ? 100 : 256;
+  const int64_t few = CPLX ? 16 : d.spread ? 100 : 256;
   if constexpr (sizeof(T) == 8)
     if (variant_for(-1) < 0 && direct_product(d) && (CPLX || t128 > few))
-      return launch_direct<CPLX>(d, s);
+      return launch_direct<CPLX>(d, s, need);
   if (!d.a_kmaj && d.b_kmaj) {
     // A complex FP32 product of at most 16 tiles of 128 x 128 takes 64 x 64 tiles
     // (variant 2 in every element type) too.
     const int env = variant_for(-1);
     const int v = env >= 0 ? env : (t128 <= few ? 2 : DefaultVariant<T, CPLX>::value);
     switch (v) {
-      case 1: return launch_shape<T, CPLX, false, true, typename V::V1>(d, s);
-      case 2: return launch_shape<T, CPLX, false, true, typename V::V2>(d, s);
-      case 3: return launch_shape<T, CPLX, false, true, typename V::V3>(d, s);
-      case 4: return launch_shape<T, CPLX, false, true, typename V::V4>(d, s);
-      case 5: return launch_shape<T, CPLX, false, true, typename V::V5>(d, s);
-      case 6: return launch_shape<T, CPLX, false, true, typename V::V6>(d, s);
-      default: return launch_shape<T, CPLX, false, true, typename V::V0>(d, s);
+      case 1: return launch_shape<T, CPLX, false, true, typename V::V1>(d, s, need);
+      case 2: return launch_shape<T, CPLX, false, true, typename V::V2>(d, s, need);
+      case 3: return launch_shape<T, CPLX, false, true, typename V::V3>(d, s, need);
+      case 4: return launch_shape<T, CPLX, false, true, typename V::V4>(d, s, need);
+      case 5: return launch_shape<T, CPLX, false, true, typename V::V5>(d, s, need);
+      case 6: return launch_shape<T, CPLX, false, true, typename V::V6>(d, s, need);
+      default: return launch_shape<T, CPLX, false, true, typename V::V0>(d, s, need);
     }
   }
-  if (d.a_kmaj && d.b_kmaj) return launch_shape<T, CPLX, true, true, typename V::V0>(d, s);
-  if (d.a_kmaj && !d.b_kmaj) return launch_shape<T, CPLX, true, false, typename V::V0>(d, s);
-  return launch_shape<T, CPLX, false, false, typename V::V0>(d, s);
+  if (d.a_kmaj && d.b_kmaj) return launch_shape<T, CPLX, true, true, typename V::V0>(d, s, need);
+  if (d.a_kmaj && !d.b_kmaj) return launch_shape<T, CPLX, true, false, typename V::V0>(d, s, need);
+  return launch_shape<T, CPLX, false, false, typename V::V0>(d, s, need);
 }
 
 template <typename S>
@@ -1337,12 +1364,22 @@ int grouped_run(const GroupedProducts& g, hipStream_t s) {
 
 int gemm_f64(const GemmDesc& d, hipStream_t s) {
   if (d.M == 0 || d.N == 0) return TC_OK;
-  return d.complex ? launch2<double, true>(d, s) : launch2<double, false>(d, s);
+  return d.complex ? launch2<double, true>(d, s, nullptr) : launch2<double, false>(d, s, nullptr);
 }
 
 int gemm_f32(const GemmDesc& d, hipStream_t s) {
   if (d.M == 0 || d.N == 0) return TC_OK;
-  return d.complex ? launch2<float, true>(d, s) : launch2<float, false>(d, s);
+  return d.complex ? launch2<float, true>(d, s, nullptr) : launch2<float, false>(d, s, nullptr);
+}
+
+size_t gemm_tail_bytes(const GemmDesc& d, bool f64) {
+  if (d.M == 0 || d.N == 0) return 0;
+  size_t need = 0;
+  const int rc = f64 ? (d.complex ? launch2<double, true>(d, nullptr, &need)
+                                  : launch2<double, false>(d, nullptr, &need))
+                     : (d.complex ? launch2<float, true>(d, nullptr, &need)
+                                  : launch2<float, false>(d, nullptr, &need));
+  return rc == TC_OK ? need : 0;
 }
 
 }  // namespace tcm

@@ -352,7 +352,7 @@ int launch_grouped(const SmallGroup& g, hipStream_t s) {
 // 131 against 125, 1024 237 against 227; FP32 128 x 128 tiles, 1024 128 against 146,
 // 1536 372 against 403.
 bool small_product(const GemmDesc& d, bool f64) {
-  const int64_t most = f64 ? (d.tail_ws ? 704 : 1024) : 1536;
+  const int64_t most = f64 ? (d.spread ? 704 : 1024) : 1536;
   return d.complex && !d.a_kmaj && d.b_kmaj && !d.c_trans && !d.cin_trans && d.M <= most &&
          d.N <= most && d.K >= 1 && d.K <= (int64_t(1) << 20);
 }

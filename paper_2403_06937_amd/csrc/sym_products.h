@@ -14,6 +14,7 @@ namespace tcm {
 struct SymProducts {
   int64_t N = 0;
   void* tail = nullptr; size_t tail_bytes = 0;   // partial sums of a last round
+  bool spread = false;                           // (GemmDesc's tail_ws and spread)
   hipStream_t s = nullptr;
   // C = alpha A B + beta C + gamma I.  Either the product is symmetric, or a
   // following run adds the rest of a symmetric sum to C: the entries below the
@@ -30,7 +31,7 @@ struct SymProducts {
     d.gamma = gamma;
     d.complex = false;
     d.herm = true;
-    d.tail_ws = tail; d.tail_ws_bytes = tail_bytes;
+    d.tail_ws = tail; d.tail_ws_bytes = tail_bytes; d.spread = spread;
     return gemm_f64(d, s);
   }
 };

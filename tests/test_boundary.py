@@ -133,6 +133,29 @@ def test_workspace_sizes_scale():
     assert tcm.tc_gemm_workspace_size(64, 64, 64, tcm.TC_GEMM_SPLIT_BF16) > 0
 
 
+@pytest.mark.parametrize("n,c,mode,matrices", [
+    (6, 7, tcm.TC_GEMM_F64, 16), (8, 5, tcm.TC_GEMM_F32, 16), (7, 4, tcm.TC_GEMM_SPLIT_BF16, 48)])
+def test_small_steps_reserve_no_partial_sums(n, c, mode, matrices):
+    """N = 512 FP64, 1536 FP32 and 640 split-BF16, the largest of their kind whose
+    products run on the small kernels (FP64 up to 704): the workspace is the step's
+    matrices (bytes per entry), without slots for partial sums."""
+    class Fake:
+        def __init__(self, p, ld):
+            self.p, self.ld = p, ld
+
+        def data_ptr(self):
+            return self.p
+
+        def stride(self, i):
+            return self.ld
+
+    m = tcm.Model(n, c, [0.01] * n, [1.0] * n)
+    rdt = tcm.TC_C128 if mode == tcm.TC_GEMM_F64 else tcm.TC_C64
+    inst = tcm.make_instance(m, Fake(0x1000, m.N), Fake(0x2000, m.N))
+    ws = tcm.tc_evolve_workspace_size([inst], tcm.make_opts(10, 0.1, mode, rdt))
+    assert m.N * m.N * matrices <= ws <= m.N * m.N * matrices + 4096
+
+
 def test_dissipation_rates_checked_before_device_work():
     """Negative or non-finite kappa / gamma are argument errors; the adjoint
     rejects a model with a Lindblad term (it covers the unitary step only)."""

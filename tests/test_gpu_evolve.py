@@ -501,6 +501,58 @@ def test_small_product_kernel(n, c, mode, frame, rdt, tol, full, graph):
     assert err < tol
 
 
+@pytest.mark.parametrize("n,c,mode,dtype,tol", [
+    (8, 8, tcm.TC_GEMM_F64, torch.complex128, 1e-10),
+    (8, 4, tcm.TC_GEMM_F64, torch.complex128, 1e-10),
+    (8, 8, tcm.TC_GEMM_F32, torch.complex64, 1e-5)])
+def test_workspace_of_256_slots(n, c, mode, dtype, tol):
+    """A workspace that holds the step's matrices and 256 slots of a complex
+    128 x 128 tile, fewer than the products can use (N = 2304, 1280): the run takes
+    it, writes nothing past it and agrees with the oracle; a byte less is refused."""
+    inst = ti.random_model(n, c, 640 + c, state="gaussian")
+    m, dt, steps = pipeline.model_of(inst), 0.05, 5
+    _, U = pipeline.propagator(m, dt)
+    rho = _dev(inst.rho0(), dtype)
+    f64 = mode == tcm.TC_GEMM_F64
+    opts = tcm.make_opts(steps, dt, mode, tcm.TC_C128 if f64 else tcm.TC_C64, tcm.TC_FRAME_LAB)
+    run = [tcm.make_instance(m, U, rho)]
+    slots = 256 * 128 * 128 * (16 if f64 else 8)
+    size = m.N * m.N * 16 + 256 + slots      # X, or X and the FP32 copy of U
+    assert size < tcm.tc_evolve_workspace_size(run, opts)
+    buf = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    with pytest.raises(tcm.TcmError) as e:
+        tcm.tc_evolve(run, opts, ws=buf[:size - 1])
+    assert e.value.code == tcm.TC_ERR_WORKSPACE
+    tcm.tc_evolve(run, opts, ws=buf[:size])
+    torch.cuda.synchronize()
+    assert bool((buf[size:] == 0x5a).all())
+    psi = oev.SectorPropagator(n, c, inst.g, inst.omega_a).psi(inst.psi0, steps * dt)
+    assert max_entry_error_pure(rho.cpu().numpy().astype(np.complex128), psi) <= tol
+
+
+def test_one_sector_workspace_of_256_slots():
+    """The same for one excitation sector (n = c = k = 11, 2048 states, FP64), against
+    a run with the whole workspace."""
+    inst = ti.random_model(11, 11, 650)
+    m, k, dt, steps = pipeline.model_of(inst), 11, 0.05, 3
+    _, U = pipeline.sector_propagator(m, k, dt)
+    d = U.shape[0]
+    psi = torch.randn(d, dtype=torch.complex128, device=DEV, generator=torch.Generator(DEV).manual_seed(5))
+    psi /= psi.norm()
+    a = torch.outer(psi, psi.conj())
+    b = a.clone()
+    size = d * d * 16 + 512 + 256 * 128 * 128 * 16
+    buf = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    pipeline.evolve_sector(m, k, U, a, steps, dt)
+    pipeline.evolve_sector(m, k, U, b, steps, dt, ws=buf[:size])
+    torch.cuda.synchronize()
+    assert bool((buf[size:] == 0x5a).all())
+    assert (a - b).abs().max().item() <= 1e-13
+    with pytest.raises(tcm.TcmError) as e:
+        pipeline.evolve_sector(m, k, U, b, steps, dt, ws=buf[:size - 1])
+    assert e.value.code == tcm.TC_ERR_WORKSPACE
+
+
 SPLIT_RECORDS_RUN = """
 import numpy as np, torch
 import paper_2403_06937_amd as tcm

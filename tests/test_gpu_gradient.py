@@ -77,6 +77,36 @@ def test_adjoint_scaled_and_squared(n, c, dt):
     assert np.max(np.abs(gd - do)) <= 1e-9 * scale
 
 
+def test_adjoint_workspace_with_fewer_slots():
+    """N = 1536, FP64: a workspace 8 MB short of all the slots for partial sums (256 of
+    a complex 128 x 128 tile are left) gives the same gradient to rounding, and
+    nothing is written past it."""
+    inst = ti.random_model(8, 5, 66, state="gaussian")
+    m, dt, steps = pipeline.model_of(inst), 0.05, 3
+    H, U = pipeline.propagator(m, dt)
+    rho = torch.from_numpy(inst.rho0()).to("cuda")
+    _, _, ck = pipeline.evolve(m, U, rho, steps, dt, tcm.TC_GEMM_F64, tcm.TC_FRAME_ROTATING, 0,
+                               steps, steps)
+    opts = tcm.make_opts(steps, dt, tcm.TC_GEMM_F64, tcm.TC_C128, tcm.TC_FRAME_LAB, 0, 1, steps)
+    need = tcm.tc_evolve_backward_workspace_size(m, opts)
+    buf = torch.full((need,), 0x5a, dtype=torch.uint8, device="cuda")
+    out = []
+    for size in (need, need - (8 << 20)):
+        loss, gg, gd = (torch.zeros(k, dtype=torch.float64, device="cuda")
+                        for k in (1, inst.n, inst.n))
+        buf.fill_(0x5a)
+        tcm.tc_evolve_backward(m, H, U, opts, ck, loss, gg, gd, ws=buf[:size])
+        torch.cuda.synchronize()
+        assert bool((buf[size:] == 0x5a).all())
+        out.append(torch.cat([loss, gg, gd]).cpu().numpy())
+    scale = np.max(np.abs(out[0][1:]))
+    assert abs(out[0][0] - out[1][0]) <= 1e-12
+    assert np.max(np.abs(out[0][1:] - out[1][1:])) <= 1e-11 * scale
+    with pytest.raises(tcm.TcmError) as e:
+        tcm.tc_evolve_backward(m, H, U, opts, ck, loss, gg, gd, ws=buf[:need - (40 << 20)])
+    assert e.value.code == tcm.TC_ERR_WORKSPACE
+
+
 @pytest.mark.parametrize("sectors", [False, True])
 def test_adjoint_zero_steps(sectors):
     inst = ti.random_model(2, 2, 62, state="gaussian")
