@@ -46,8 +46,10 @@ struct InstPlan {
   int in_sector = -1;
   int32_t* sec_off = nullptr;
   bool sectors = false;
+  bool in_batch = false;             // the batch holds the descriptors of its products
   int64_t Np = 0;                    // padded dimension of the sorted order
   int svar = 2;                      // tile shape of the grouped block products (1: 128, 2: 64)
+  bool triangles = true;             // diagonal blocks of the second product as triangles
   std::vector<int64_t> sdim;         // d_k: states of sector k
   std::vector<int64_t> spo, spd;     // sector k: padded positions [spo[k], spo[k] + spd[k])
   std::vector<size_t> boff;          // element offset of block k (spd[k]^2) in blocks
@@ -111,8 +113,9 @@ void sector_sizes(int n, int c, std::vector<int64_t>& dim, std::vector<int64_t>&
   }
 }
 
-// tile64: 64 x 64 tiles whatever the autotuner's table holds.
-void plan_sectors(const tc_evolve_opts& o, bool tile64, Arena& ar, InstPlan* p) {
+// least: in as little memory as can be, on 64 x 64 tiles whatever the autotuner's
+// table holds and with one descriptor for a block of the second product.
+void plan_sectors(const tc_evolve_opts& o, bool least, Arena& ar, InstPlan* p) {
   const int64_t N = p->N;
   const bool f64 = o.gemm_mode == TC_GEMM_F64;
   const size_t eb = f64 ? 16 : 8;
@@ -122,7 +125,8 @@ void plan_sectors(const tc_evolve_opts& o, bool tile64, Arena& ar, InstPlan* p) 
   p->sectors = true;
   std::vector<int64_t> off;
   sector_sizes(p->m.n, p->m.c, p->sdim, off);
-  p->svar = tile64 ? 2 : tile_variant_for(N, f64);
+  p->svar = least ? 2 : tile_variant_for(N, f64);
+  p->triangles = !least;
   const int64_t q = split ? SPLIT_BM : (p->svar == 1 ? 128 : 64);
   const int ns = int(p->sdim.size());
   p->spo.assign(ns, 0);
@@ -145,10 +149,11 @@ void plan_sectors(const tc_evolve_opts& o, bool tile64, Arena& ar, InstPlan* p) 
   p->perm = static_cast<int32_t*>(ar.take(size_t(pos) * 4));
   p->inv = static_cast<int32_t*>(ar.take(size_t(N) * 4));
   p->secpos = static_cast<int32_t*>(ar.take(size_t(pos) * 4));
-  // one descriptor per block of the first product, two of the second (one in
-  // split-BF16)
-  p->items = static_cast<char*>(
-      ar.take(split ? 2 * split_grouped_bytes(ns) : grouped_bytes(ns) + grouped_bytes(2 * ns)));
+  // one descriptor per block of the first product, two of the second when its
+  // diagonal blocks are triangles
+  if (!p->in_batch)
+    p->items = static_cast<char*>(
+        ar.take(split ? 2 * split_grouped_bytes(ns) : grouped_bytes((p->triangles ? 3 : 2) * ns)));
   if (split) {
     p->sopA.resize(ns);
     p->sopB.resize(ns);
@@ -197,7 +202,7 @@ void take_tail(Arena& ar, const tc_evolve_opts& o, InstPlan* plans, int count) {
   }
 }
 
-void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelArgs& m, bool tile64,
+void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelArgs& m, bool least,
                    Arena& ar, InstPlan* p) {
   const int64_t N = in.N;
   const size_t NN = size_t(N) * size_t(N);
@@ -209,7 +214,7 @@ void plan_instance(const tc_instance& in, const tc_evolve_opts& o, const ModelAr
     p->counter = static_cast<int*>(ar.take(sizeof(int)));
   }
   if (o.sectors) {
-    plan_sectors(o, tile64, ar, p);
+    plan_sectors(o, least, ar, p);
     return;
   }
   if (p->in_sector >= 0)
@@ -525,13 +530,21 @@ int prepare_sectors(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o,
     g2.B = blk; g2.ldb = d; g2.b_kmaj = true; g2.conj_b = true;
     g2.C = at(p.rho, off, off, p.ldr); g2.ldc = p.ldr;
     if (rot) { g2.Cin = g2.A; g2.ldcin = p.ldx; g2.beta_re = 1.0; }
+    d1.push_back(g1);
+    if (!p.triangles) {
+      g2.M = off + d;
+      g2.A = at(p.X, 0, off, p.ldx);
+      g2.C = at(p.rho, 0, off, p.ldr);
+      if (rot) g2.Cin = g2.A;
+      d2.push_back(g2);
+      continue;
+    }
     GemmDesc g3 = g2;
     g2.herm = true;
     g3.M = off;
     g3.A = at(p.X, 0, off, p.ldx);
     g3.C = at(p.rho, 0, off, p.ldr);
     if (rot) g3.Cin = g3.A;
-    d1.push_back(g1);
     if (off > 0) d2.push_back(g3);
     d2.push_back(g2);
   }
@@ -823,28 +836,36 @@ bool batch_small(int64_t N, int64_t tiles64, bool f64) {
   return N <= 192 || (N <= 512 && (tiles64 < 256 || (!f64 && N % 64 != 0)));
 }
 
+// A batch's descriptors, one after another as a run takes them: the grouped
+// products' and the readouts' and the record index of each instance, or the
+// LDS-resident instances.
 struct BatchBufs {
-  char* items = nullptr;          // 8 groups of count GroupItem descriptors
-  char* small = nullptr;          // 2 groups of count small products
-  ReadoutItem* ritems = nullptr;  // count readout descriptors
-  ResidentItem* resident = nullptr;   // count LDS-resident instances
-  int* counter = nullptr;         // record index of each instance
+  char* items = nullptr;
+  size_t bytes = 0, used = 0;
+  // room for count objects of elem bytes (nullptr: none left)
+  char* take(size_t elem, size_t count) {
+    const size_t off = align_up(used, 16);
+    used = off + elem * count;
+    return used <= bytes ? items + off : nullptr;
+  }
 };
 
 bool use_batched(int count, const tc_evolve_opts& o) {
   return count > 1 && (o.gemm_mode != TC_GEMM_SPLIT_BF16 || o.sectors);
 }
 
-// sector_items: total block products of the batch (0 without sectors); the
-// block products of all instances share two groups per tile shape
-void plan_batch(Arena& ar, int count, int64_t sector_items, BatchBufs* b) {
-  const size_t blocks = std::max(grouped_bytes(int(sector_items)),
-                                 split_grouped_bytes(int(sector_items)));
-  b->items = static_cast<char*>(ar.take(std::max(8 * grouped_bytes(count), 4 * blocks)));
-  b->small = static_cast<char*>(ar.take(2 * small_grouped_bytes(count)));
-  b->ritems = static_cast<ReadoutItem*>(ar.take(size_t(count) * sizeof(ReadoutItem)));
-  b->counter = static_cast<int*>(ar.take(size_t(count) * sizeof(int)));
-  b->resident = static_cast<ResidentItem*>(ar.take(size_t(count) * sizeof(ResidentItem)));
+// blocks: sectors of all instances (0 without sectors).  A dense instance takes two
+// products' descriptors, a sector (at least two to an instance) at most three; the
+// rest of the 8 and 4 holds the readouts and record indexes.
+void plan_batch(Arena& ar, int count, int64_t blocks, BatchBufs* b) {
+  b->bytes = std::max(8 * grouped_bytes(count),
+                      4 * std::max(grouped_bytes(int(blocks)), split_grouped_bytes(int(blocks))));
+  b->items = static_cast<char*>(ar.take(b->bytes));
+}
+
+int no_room() {
+  set_error("batch: descriptor buffer exhausted");
+  return TC_ERR_WORKSPACE;
 }
 
 void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDesc& g2) {
@@ -866,18 +887,17 @@ void step_descs(const InstPlan& p, const tc_evolve_opts& o, GemmDesc& g1, GemmDe
   g2.tail_ws = p.tail_ws; g2.tail_ws_bytes = p.tail_ws_bytes; g2.spread = true;
 }
 
-// Block products of one product phase over all instances of a batch: at most
-// two per sector (0 without sectors).
-int64_t sector_items(const tc_instance* inst, int count, const tc_evolve_opts& o) {
+// Sectors of all instances of a batch (0 without sectors).
+int64_t sector_blocks(const tc_instance* inst, int count, const tc_evolve_opts& o) {
   if (!o.sectors) return 0;
   int64_t t = 0;
   for (int b = 0; b < count; ++b)
-    t += 2 * (inst[b].model->n_atoms + inst[b].model->photon_cutoff + 1);
+    t += inst[b].model->n_atoms + inst[b].model->photon_cutoff + 1;
   return t;
 }
 
 int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int count,
-                   const tc_evolve_opts& o, const BatchBufs& bb, hipStream_t s) {
+                   const tc_evolve_opts& o, BatchBufs bb, hipStream_t s) {
   const bool f64 = o.gemm_mode == TC_GEMM_F64;
   // a batch of nothing but LDS-resident instances: one workgroup each, all steps
   // in one launch (30 of N = 32: per-step launches took 23 us a step).  With
@@ -892,10 +912,13 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
       items[b] = resident_item(plans[b], inst[b]);
       maxN = std::max(maxN, items[b].N);
     }
-    TC_TRY_HIP(hipMemcpyAsync(bb.resident, items.data(), items.size() * sizeof(ResidentItem),
+    char* dev = bb.take(sizeof(ResidentItem), count);
+    if (!dev) return no_room();
+    TC_TRY_HIP(hipMemcpyAsync(dev, items.data(), items.size() * sizeof(ResidentItem),
                               hipMemcpyHostToDevice, s));
     TC_TRY_HIP(hipStreamSynchronize(s));   // items is host memory of this call
-    return launch_resident(f64, maxN, nullptr, bb.resident, count, resident_run(o), s);
+    return launch_resident(f64, maxN, nullptr, reinterpret_cast<ResidentItem*>(dev), count,
+                           resident_run(o), s);
   }
   const bool sec = o.sectors != 0, split = o.gemm_mode == TC_GEMM_SPLIT_BF16;
   for (int b = 0; b < count; ++b)
@@ -945,28 +968,33 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   std::stable_sort(sp2.begin(), sp2.end(), by_kp);
   GroupedProducts G1[3][2], G2[3][2];
   SplitGrouped S1, S2;
-  char* it = bb.items;
-  const size_t gstep = sec ? std::max(grouped_bytes(int(d2[1][0].size() + d2[2][0].size())),
-                                      split_grouped_bytes(int(sp1.size())))
-                           : grouped_bytes(count);
-  if (sec && split) {
-    TC_RETURN_IF(split_grouped_build(sp1, it, &S1, s));
-    it += gstep;
-    TC_RETURN_IF(split_grouped_build(sp2, it, &S2, s));
-    it += gstep;
-  }
+  auto build = [&](const std::vector<GemmDesc>& ds, int v, GroupedProducts* g) -> int {
+    char* it = bb.take(grouped_bytes(1), ds.size());
+    return it ? grouped_build(ds, f64, v, it, g, s) : no_room();
+  };
+  auto build_small = [&](const std::vector<GemmDesc>& ds, SmallGroup* g) -> int {
+    char* it = bb.take(small_grouped_bytes(1), ds.size());
+    return it ? small_grouped_build(ds, f64, it, g, s) : no_room();
+  };
+  auto build_split = [&](const std::vector<SplitProduct>& ps, SplitGrouped* g) -> int {
+    char* it = bb.take(split_grouped_bytes(1), ps.size());
+    return it ? split_grouped_build(ps, it, g, s) : no_room();
+  };
+  int* counter = reinterpret_cast<int*>(bb.take(sizeof(int), count));
+  ReadoutItem* ritems = reinterpret_cast<ReadoutItem*>(bb.take(sizeof(ReadoutItem), count));
+  if (!counter || !ritems) return no_room();
+  TC_RETURN_IF(build_split(sp1, &S1));
+  TC_RETURN_IF(build_split(sp2, &S2));
   SmallGroup T1, T2;
-  TC_RETURN_IF(small_grouped_build(s1, f64, bb.small, &T1, s));
-  TC_RETURN_IF(small_grouped_build(s2, f64, bb.small + small_grouped_bytes(count), &T2, s));
+  TC_RETURN_IF(build_small(s1, &T1));
+  TC_RETURN_IF(build_small(s2, &T2));
   for (int v = 1; v <= 2; ++v)
     for (int e = 0; e < 2; ++e) {
       if (d1[v][e].empty()) continue;
       std::stable_sort(d1[v][e].begin(), d1[v][e].end(), by_k);
       std::stable_sort(d2[v][e].begin(), d2[v][e].end(), by_k);
-      TC_RETURN_IF(grouped_build(d1[v][e], f64, v, it, &G1[v][e], s));
-      it += gstep;
-      TC_RETURN_IF(grouped_build(d2[v][e], f64, v, it, &G2[v][e], s));
-      it += gstep;
+      TC_RETURN_IF(build(d1[v][e], v, &G1[v][e]));
+      TC_RETURN_IF(build(d2[v][e], v, &G2[v][e]));
       G1[v][e].persistent = G2[v][e].persistent = e == 1;
     }
   bool rec = false, ckpt = false;
@@ -984,12 +1012,12 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     rec = rec || inst[b].pop_out || inst[b].photon_dist_out || inst[b].photon_state_out;
     ckpt = ckpt || inst[b].checkpoints;
   }
-  TC_TRY_HIP(hipMemcpyAsync(bb.ritems, ri.data(), ri.size() * sizeof(ReadoutItem),
+  TC_TRY_HIP(hipMemcpyAsync(ritems, ri.data(), ri.size() * sizeof(ReadoutItem),
                             hipMemcpyHostToDevice, s));
-  TC_TRY_HIP(hipMemsetAsync(bb.counter, 0, size_t(count) * sizeof(int), s));
+  TC_TRY_HIP(hipMemsetAsync(counter, 0, size_t(count) * sizeof(int), s));
   TC_TRY_HIP(hipStreamSynchronize(s));   // ri is host memory of this call
   const bool c128s = f64;
-  if (rec) TC_RETURN_IF(launch_grouped_readout(bb.ritems, count, c128s, bb.counter, s));
+  if (rec) TC_RETURN_IF(launch_grouped_readout(ritems, count, c128s, counter, s));
   for (int b = 0; b < count; ++b)
     if (inst[b].checkpoints) TC_RETURN_IF(copy_checkpoint(plans[b], inst[b], o, 0, 0.0, s));
 
@@ -1006,7 +1034,7 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     if (o.renorm_every > 0 && st % o.renorm_every == 0)
       for (int b = 0; b < count; ++b) TC_RETURN_IF(renorm(plans[b], o, q));
     if (rec && st % o.record_every == 0)
-      TC_RETURN_IF(launch_grouped_readout(bb.ritems, count, c128s, bb.counter, q));
+      TC_RETURN_IF(launch_grouped_readout(ritems, count, c128s, counter, q));
     if (ckpt && o.checkpoint_every > 0 && st % o.checkpoint_every == 0)
       for (int b = 0; b < count; ++b)
         if (inst[b].checkpoints)
@@ -1030,7 +1058,7 @@ struct RunPlan {
 
 // Checks the arguments of a run and carves its buffers from ar (sizes only, when
 // ar has no memory).
-int plan_run(const tc_instance* inst, int count, const tc_evolve_opts* o, bool tile64, Arena& ar,
+int plan_run(const tc_instance* inst, int count, const tc_evolve_opts* o, bool least, Arena& ar,
              RunPlan* r) {
   TC_CHECK_ARG(count >= 1, "count < 1");
   TC_CHECK_ARG(inst != nullptr, "instances is NULL");
@@ -1039,10 +1067,11 @@ int plan_run(const tc_instance* inst, int count, const tc_evolve_opts* o, bool t
   for (int b = 0; b < count; ++b) {
     ModelArgs m;
     TC_RETURN_IF(validate_instance(&inst[b], o, &m));
-    plan_instance(inst[b], *o, m, tile64, ar, &r->plans[b]);
+    r->plans[b].in_batch = use_batched(count, *o);
+    plan_instance(inst[b], *o, m, least, ar, &r->plans[b]);
   }
   if (use_batched(count, *o))
-    plan_batch(ar, count, sector_items(inst, count, *o), &r->batch);
+    plan_batch(ar, count, sector_blocks(inst, count, *o), &r->batch);
   else
     take_tail(ar, *o, r->plans.data(), count);
   return TC_OK;
@@ -1105,7 +1134,7 @@ int tc_evolve(const tc_instance* inst, int32_t count, const tc_evolve_opts* o, v
   TC_CHECK_ARG(ws != nullptr || ar.used == 0, "workspace is NULL");
   if (!ar.fits()) {
     const size_t need = ar.used;
-    ar = Arena(ws, ws_bytes);            // 64 x 64 tiles pad least
+    ar = Arena(ws, ws_bytes);
     TC_RETURN_IF(plan_run(inst, count, o, true, ar, &run));
     if (!ar.fits()) {
       set_error("workspace too small for tc_evolve: need at least " + std::to_string(need) +

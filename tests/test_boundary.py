@@ -156,6 +156,31 @@ def test_small_steps_reserve_no_partial_sums(n, c, mode, matrices):
     assert m.N * m.N * matrices <= ws <= m.N * m.N * matrices + 4096
 
 
+@pytest.mark.parametrize("shapes,mode,sectors,most", [
+    ([(3, 3)] * 30, tcm.TC_GEMM_F64, 0, 541696), ([(5, 4)] * 16, tcm.TC_GEMM_F32, 0, 6580480),
+    ([(5, 4), (7, 7)], tcm.TC_GEMM_F64, 1, 79608576),
+    ([(5, 4), (7, 7)], tcm.TC_GEMM_SPLIT_BF16, 1, 180280064)])
+def test_batch_workspace_sizes_hold(shapes, mode, sectors, most):
+    """A batch asks for no more than when it had grouped tiles only: the small
+    products, resident instances and record indexes share their descriptors' memory."""
+    class Fake:
+        def __init__(self, p, ld):
+            self.p, self.ld = p, ld
+
+        def data_ptr(self):
+            return self.p
+
+        def stride(self, i):
+            return self.ld
+
+    ms = [tcm.Model(n, c, [0.01] * n, [1.0] * n) for n, c in shapes]
+    rdt = tcm.TC_C128 if mode == tcm.TC_GEMM_F64 else tcm.TC_C64
+    ws = tcm.tc_evolve_workspace_size([tcm.make_instance(m, Fake(0x1000, m.N), Fake(0x2000, m.N))
+                                       for m in ms], tcm.make_opts(10, 0.1, mode, rdt,
+                                                                   sectors=sectors))
+    assert ws <= most
+
+
 def test_dissipation_rates_checked_before_device_work():
     """Negative or non-finite kappa / gamma are argument errors; the adjoint
     rejects a model with a Lindblad term (it covers the unitary step only)."""

@@ -248,6 +248,33 @@ def test_batched_sectors(mode, frame, dtype, tol):
         assert err < tol and perr < tol, (k, err, perr)
 
 
+@pytest.mark.parametrize("mode,frame,dtype,tol", MODES[:4])
+def test_workspace_without_triangle_descriptors(mode, frame, dtype, tol):
+    """A workspace without the seven descriptors (1024 bytes, in steps of 256) that
+    split the second product's blocks into a triangle and the rest: the blocks run
+    whole, nothing is written past it, and the result is the oracle's; a byte less
+    is refused."""
+    inst = ti.random_model(3, 3, 440, state="gaussian")
+    m, dt, steps = pipeline.model_of(inst), 0.05, 20
+    _, U = pipeline.propagator(m, dt)
+    rho = torch.from_numpy(inst.rho0()).to("cuda").to(dtype)
+    pop = torch.zeros(steps + 1, dtype=torch.float64, device="cuda")
+    rdt = tcm.TC_C128 if dtype == torch.complex128 else tcm.TC_C64
+    opts = tcm.make_opts(steps, dt, mode, rdt, frame, 5, 1, sectors=1)
+    run = [tcm.make_instance(m, U, rho, pop)]
+    size = tcm.tc_evolve_workspace_size(run, opts) - 1024
+    buf = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    with pytest.raises(tcm.TcmError) as e:
+        tcm.tc_evolve(run, opts, ws=buf[:size - 1])
+    assert e.value.code == tcm.TC_ERR_WORKSPACE
+    tcm.tc_evolve(run, opts, ws=buf[:size])
+    torch.cuda.synchronize()
+    assert bool((buf[size:] == 0x5a).all())
+    ref, rpop, _ = _oracle(inst, dt, steps)
+    assert np.max(np.abs(rho.cpu().numpy() - ref)) <= tol
+    assert np.max(np.abs(pop.cpu().numpy() - rpop)) <= tol
+
+
 TABLE_RUN = """
 import sys, torch
 import numpy as np
