@@ -47,15 +47,17 @@ int make_model_args(const tc_model* m, ModelArgs* out) {
 // ----------------------------------------------------------------- expm
 namespace {
 
-// Six N x N matrices.
+// Six N x N matrices, two of them (not aligned apart) in the place of one complex.
 struct ExpmLayout {
   double *B, *X, *X2, *X3, *T, *W;
 };
 
 void expm_layout(Arena& ar, int64_t N, ExpmLayout* L) {
   const size_t rb = size_t(N) * size_t(N) * sizeof(double);
-  double** m[6] = {&L->B, &L->X, &L->X2, &L->X3, &L->T, &L->W};
+  double** m[4] = {&L->B, &L->X, &L->T, &L->W};
   for (auto p : m) *p = static_cast<double*>(ar.take(rb));
+  L->X2 = static_cast<double*>(ar.take(2 * rb));
+  L->X3 = L->X2 ? L->X2 + size_t(N) * size_t(N) : nullptr;
 }
 
 // cos and sin of B from their Taylor polynomials in X = B^2 (coefficients cc,

@@ -78,6 +78,8 @@ void bwd_layout(Arena& ar, int64_t N, const tc_evolve_opts& o, BwdLayout* L) {
   ar.used = std::max(ar.used, sub.used);
   L->scratch = static_cast<double*>(ar.take(8 * sizeof(double)));
   // partial sums of the sweep's complex products and of the derivative's real ones
+  // (none for a single 128 x 128 tile)
+  if (N <= 128) return;
   GemmDesc d;
   d.M = d.N = d.K = N;
   d.spread = true;

@@ -181,6 +181,18 @@ def test_batch_workspace_sizes_hold(shapes, mode, sectors, most):
     assert ws <= most
 
 
+def test_expm_and_adjoint_workspace_sizes_hold():
+    """tc_expm asks for no more than four matrices and a complex one, each on a
+    256-byte boundary; the adjoint at N = 128 (complex FP32, a checkpoint every step)
+    for no more than when it held the block-triangular exponential."""
+    for N in list(range(1, 70)) + [100, 333, 512]:
+        up = lambda b: -(-b // 256) * 256
+        assert tcm.tc_expm_workspace_size(N) <= 4 * up(8 * N * N) + up(16 * N * N)
+    m = tcm.Model(5, 3, [0.01] * 5, [1.0] * 5)
+    opts = tcm.make_opts(10, 0.1, tcm.TC_GEMM_F32, tcm.TC_C64, checkpoint_every=1)
+    assert tcm.tc_evolve_backward_workspace_size(m, opts) <= 2359552
+
+
 def test_dissipation_rates_checked_before_device_work():
     """Negative or non-finite kappa / gamma are argument errors; the adjoint
     rejects a model with a Lindblad term (it covers the unitary step only)."""
