@@ -92,34 +92,19 @@ void bwd_layout(Arena& ar, int64_t N, const tc_evolve_opts& o, BwdLayout* L) {
   if (L->tail.bytes > 0) L->tail.p = ar.take_at_most(&L->tail.bytes, tail_least_bytes(true));
 }
 
-// General complex product in the sweep precision: C = alpha op(A) op(B) + beta C.
-int cgemm(const TailWs& tw, bool f64, int64_t N, const void* A, int64_t lda, bool a_kmaj,
-          bool conj_a, const void* B, int64_t ldb, bool b_kmaj, bool conj_b, void* C, int64_t ldc,
-          double alpha_re, double beta_re, hipStream_t s) {
-  GemmDesc d;
-  d.tail_ws = tw.p; d.tail_ws_bytes = tw.bytes; d.spread = true;
-  d.M = d.N = d.K = N;
-  d.A = A; d.lda = lda; d.a_kmaj = a_kmaj; d.conj_a = conj_a;
-  d.B = B; d.ldb = ldb; d.b_kmaj = b_kmaj; d.conj_b = conj_b;
-  d.C = C; d.ldc = ldc;
-  d.alpha_re = alpha_re;
-  if (beta_re != 0.0) { d.Cin = C; d.ldcin = ldc; d.beta_re = beta_re; }
-  return f64 ? gemm_f64(d, s) : gemm_f32(d, s);
-}
-
-// C = op(A) op(B) + Cin in the sweep precision (Cin must not alias C); herm:
-// C is Hermitian, so only its upper tile triangle is multiplied and mirrored.
-int cgemm_in(const TailWs& tw, bool f64, int64_t N, const void* A, int64_t lda, bool a_kmaj,
-             bool conj_a, const void* B, int64_t ldb, bool b_kmaj, bool conj_b, void* C,
-             int64_t ldc, const void* Cin, hipStream_t s, bool herm = false) {
+// Complex product in the sweep precision: C = A B + Cin, A conjugated if conj_a (all
+// N x N, row-major, ld N).  Cin: NULL, C itself, or apart from C.  herm: C is
+// Hermitian, so only its upper tile triangle is multiplied and mirrored.
+int cgemm(const TailWs& tw, bool f64, int64_t N, const void* A, bool conj_a, const void* B, void* C,
+          const void* Cin, bool herm, hipStream_t s) {
   GemmDesc d;
   d.tail_ws = tw.p; d.tail_ws_bytes = tw.bytes; d.spread = true;
   d.herm = herm;
   d.M = d.N = d.K = N;
-  d.A = A; d.lda = lda; d.a_kmaj = a_kmaj; d.conj_a = conj_a;
-  d.B = B; d.ldb = ldb; d.b_kmaj = b_kmaj; d.conj_b = conj_b;
-  d.C = C; d.ldc = ldc;
-  d.Cin = Cin; d.ldcin = N; d.beta_re = 1.0;
+  d.A = A; d.lda = N; d.a_kmaj = false; d.conj_a = conj_a;
+  d.B = B; d.ldb = N; d.b_kmaj = true;
+  d.C = C; d.ldc = N;
+  if (Cin) { d.Cin = Cin; d.ldcin = N; d.beta_re = 1.0; }
   return f64 ? gemm_f64(d, s) : gemm_f32(d, s);
 }
 
@@ -700,17 +685,16 @@ int tc_evolve_backward(const tc_model* m, const double* H, int64_t ldh, const tc
       const void* rho_prev = state_at(L, N, st - 1 - s0);
       // Y = U~^dag O_s = O_s + D^dag O_s (D is symmetric: D^dag = conj(D), read
       // along rows)
-      TC_RETURN_IF(cgemm_in(L.tail, f64, N, L.D, N, false, true, L.O, N, true, false, L.Y, N, L.O, s));
+      TC_RETURN_IF(cgemm(L.tail, f64, N, L.D, true, L.O, L.Y, L.O, false, s));
       // M += rho_{s-1} Y
       if (f64) {
-        TC_RETURN_IF(cgemm(L.tail, true, N, rho_prev, N, false, false, L.Y, N, true, false, L.M, N, 1.0, 1.0, s));
+        TC_RETURN_IF(cgemm(L.tail, true, N, rho_prev, false, L.Y, L.M, L.M, false, s));
       } else {
-        TC_RETURN_IF(cgemm(L.tail, false, N, rho_prev, N, false, false, L.Y, N, true, false, L.T, N, 1.0, 0.0, s));
+        TC_RETURN_IF(cgemm(L.tail, false, N, rho_prev, false, L.Y, L.T, nullptr, false, s));
         TC_RETURN_IF(launch_accumulate_c64(static_cast<const c64*>(L.T), N, L.M, N, N, s));
       }
       // O_{s-1} = Y U~ = Y + Y D, Hermitian (= U~^dag O_s U~)
-      TC_RETURN_IF(cgemm_in(L.tail, f64, N, L.Y, N, false, false, L.D, N, true, false, L.O, N, L.Y, s,
-                            true));
+      TC_RETURN_IF(cgemm(L.tail, f64, N, L.Y, false, L.D, L.O, L.Y, true, s));
     }
   }
   if (S == 0 && loss_out) {

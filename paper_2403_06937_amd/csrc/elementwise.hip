@@ -1168,21 +1168,17 @@ int launch_dissipation_t(const ModelArgs& m, E* rho, int64_t ld, double dt, hipS
     TC_TRY_HIP(hipGetLastError());
     if constexpr (std::is_same<E, c64>::value) {
       for (; b + 3 <= m.n; b += 3) {
-        // column window of the coalesced pass: 512 columns, or the 2^n of a
-        // photon block if fewer (so it divides N); it must hold whole column
-        // groups of 8 2^b.  Wider groups (b >= 7, whose window would need more
-        // than the default 64 KB of dynamic LDS) and row strides that break
-        // 16-byte alignment take the per-block kernel.
-        const int64_t per = int64_t(1) << m.n;
-        const int64_t W = std::min<int64_t>(512, per);
-        if ((int64_t(8) << b) <= W && ld % 2 == 0 &&
-            (reinterpret_cast<uintptr_t>(rho) & 15) == 0) {
+        // Bits 6 .. 8 take the coalesced pass: its 512-column windows hold their
+        // column groups of 8 2^6 exactly.  The groups of higher bits need wider
+        // windows than LDS has room for, and an odd row stride breaks the 16-byte
+        // alignment: those take the per-block kernel.
+        if (b == 6 && ld % 2 == 0 && (reinterpret_cast<uintptr_t>(rho) & 15) == 0) {
+          constexpr int W = 512;
           const size_t lds = size_t(8) * size_t(W + W / 8 + 2) * sizeof(float2);
           const int64_t groups = m.N >> 3;
           hipLaunchKernelGGL(damp_atoms3_lds_c64_kernel,
                              dim3(unsigned(m.N / W), unsigned(groups < 4096 ? groups : 4096)),
-                             dim3(unsigned(W / 4)), lds, s, rho, ld, m.N, b, int(W), float(p),
-                             float(f));
+                             dim3(unsigned(W / 4)), lds, s, rho, ld, m.N, b, W, float(p), float(f));
         } else {
           const int64_t R = m.N >> 3;            // two lanes per 8 x 8 block
           hipLaunchKernelGGL(damp_atoms3_c64_kernel, grid2(2 * R, R), dim3(TPB), 0, s, rho, ld,

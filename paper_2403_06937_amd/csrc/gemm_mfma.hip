@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 
 namespace tcm {
 namespace {
@@ -1033,6 +1034,16 @@ int64_t tail_slots(int64_t tiles, int64_t kt, int64_t round, int64_t least) {
 
 constexpr int64_t MAX_CUS = 256;     // of an unpartitioned MI355X
 
+// The LDS shapes whose last round may be spread: those that products with a buffer
+// take, row-major complex FP32 on 128 x 128 tiles and real FP64 on 64 x 64.
+template <typename T, bool CPLX, bool AK, bool BK, typename S>
+constexpr bool lds_spreads() {
+  typedef Variants<T, CPLX> V;
+  return !AK && BK &&
+         (sizeof(T) == 8 ? !CPLX && std::is_same<S, typename V::V2>::value
+                         : CPLX && std::is_same<S, typename V::V1>::value);
+}
+
 // need != nullptr: only the bytes of tail_ws that the product can use.
 template <typename T, bool CPLX, bool AK, bool BK, typename S>
 int launch_shape(const GemmDesc& d, hipStream_t s, size_t* need) {
@@ -1056,17 +1067,19 @@ int launch_shape(const GemmDesc& d, hipStream_t s, size_t* need) {
   // a partial last round (the whole product, when it has fewer tiles than CUs) is
   // spread over the CUs in ranges of at least 4 K tiles (a K tile of a 128 x 128
   // FP64 tile takes 7 us)
+  constexpr bool SPREADS = lds_spreads<T, CPLX, AK, BK, S>();
   const size_t slot = size_t(S::BM) * S::BN * (CPLX ? 2 : 1) * sizeof(T);
   const int64_t kt = d.K / S::BKT;
   if (need) {
-    *need = exact ? size_t(tail_slots(tiles, kt, MAX_CUS, 4)) * slot : 0;
+    *need = SPREADS && exact ? size_t(tail_slots(tiles, kt, MAX_CUS, 4)) * slot : 0;
     return TC_OK;
   }
   ProfileScope prof(sizeof(T) == 8 ? TC_KERNEL_GEMM_F64 : TC_KERNEL_GEMM_F32, s);
-  if (exact && d.tail_ws) {
-    const TailSplit ts =
-        tail_split(tiles, kt, device_cus(), 4,
-                   std::min<int64_t>(int64_t(d.tail_ws_bytes / slot), 1 << 20));
+  if constexpr (SPREADS) {
+    TailSplit ts{};
+    if (exact && d.tail_ws)
+      ts = tail_split(tiles, kt, device_cus(), 4,
+                      std::min<int64_t>(int64_t(d.tail_ws_bytes / slot), 1 << 20));
     if (ts.tail > 0) {
       if (ts.base > 0) {
         hipLaunchKernelGGL((gemm_kernel<T, CPLX, AK, BK, false, S::BM, S::BN, S::BKT, S::WM,
