@@ -553,6 +553,49 @@ def test_one_sector_workspace_of_256_slots():
     assert e.value.code == tcm.TC_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("n,c", [(8, 6), (8, 8), (9, 5)])
+@pytest.mark.parametrize("full", [False, True])
+def test_fp32_partial_round_above_small_products(n, c, full):
+    """Complex FP32 on 128 x 128 LDS tiles with a spread last round: no full round
+    before it (N = 1792: 196 tiles, or 105 of the triangle), one (2304: 324; its
+    triangle, 171, has none) and two or one (3072: 576 and 300), against the oracle."""
+    inst = ti.random_model(n, c, 470 + c, state="haar2")
+    dt, steps = 0.05, 10
+    rho, pop, _ = run_gpu(inst, dt, steps, tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, renorm=5,
+                          rho_dtype=torch.complex64, full=full)
+    P = oev.SectorPropagator(n, c, inst.g, inst.omega_a)
+    O = excitation_op(n, c)
+    for k in (0, steps):
+        ref = float(np.sum(O * np.abs(P.psi(inst.psi0, k * dt)) ** 2))
+        assert abs(pop[k] - ref) <= 1e-5
+    assert max_entry_error_pure(rho, P.psi(inst.psi0, steps * dt)) <= 1e-5
+
+
+@pytest.mark.parametrize("n,c", [(1, 1), (3, 1), (4, 2), (4, 4), (5, 4), (4, 20)])
+@pytest.mark.parametrize("full,graph", [(False, False), (True, True)])
+def test_small_split_products_on_a_used_workspace(n, c, full, graph):
+    """N = 4, 16, 48 and 80, where the 16 x 16 tiles end inside a 32-deep K slice of the
+    planes, 160 and 336 (32 x 32 tiles): the workspace holds NaN patterns beforehand,
+    so nothing may rest on memory that the run has not cleared."""
+    inst = ti.random_model(n, c, 480 + n, state="gaussian")
+    m, dt, steps = pipeline.model_of(inst), 0.05, 34
+    _, U = pipeline.propagator(m, dt)
+    rho = _dev(inst.rho0(), torch.complex64)
+    pop = torch.zeros(steps + 1, dtype=torch.float64, device=DEV)
+    opts = tcm.make_opts(steps, dt, tcm.TC_GEMM_SPLIT_BF16, tcm.TC_C64, tcm.TC_FRAME_ROTATING,
+                         use_graph=int(graph), full_product=int(full))
+    run = [tcm.make_instance(m, U, rho, pop)]
+    ws = torch.full((tcm.tc_evolve_workspace_size(run, opts),), 0xff, dtype=torch.uint8, device=DEV)
+    tcm.tc_evolve(run, opts, ws=ws)
+    torch.cuda.synchronize()
+    P = oev.SectorPropagator(n, c, inst.g, inst.omega_a)
+    O = excitation_op(n, c)
+    ref = [float(np.sum(O * np.abs(P.psi(inst.psi0, k * dt)) ** 2)) for k in range(steps + 1)]
+    assert np.max(np.abs(pop.cpu().numpy() - ref)) <= 1e-5
+    got = rho.cpu().numpy().astype(np.complex128)
+    assert max_entry_error_pure(got, P.psi(inst.psi0, steps * dt)) <= 1e-5
+
+
 SPLIT_RECORDS_RUN = """
 import numpy as np, torch
 import paper_2403_06937_amd as tcm
