@@ -833,7 +833,7 @@ int evolve_one(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipS
 // per product: FP64 48 x 224 take 170 us a step against 219, 16 x 480 425
 // against 468; FP32 30 x 256 176 against 185.
 bool batch_small(int64_t N, int64_t tiles64, bool f64) {
-  return N <= 192 || (N <= 512 && (tiles64 < 256 || (!f64 && N % 64 != 0)));
+  return N <= 192 || (N <= 512 && (tiles64 < device_cus() || (!f64 && N % 64 != 0)));
 }
 
 // A batch's descriptors, one after another as a run takes them: the grouped

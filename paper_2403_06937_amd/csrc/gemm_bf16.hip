@@ -43,7 +43,6 @@
 #include "gemm_bf16_small.h"
 #include "profile.h"
 
-#include <atomic>
 #include <cstdlib>
 
 namespace tcm {
@@ -890,26 +889,6 @@ int split_into(const c64* src, int64_t ld, int64_t R, int64_t C, bool trans, boo
   return TC_OK;
 }
 
-// Compute units of the current device (queried once per device).
-int device_cu_count(int* cus) {
-  static std::atomic<int> cache[64];
-  int dev = 0;
-  TC_TRY_HIP(hipGetDevice(&dev));
-  if (dev >= 0 && dev < 64 && cache[dev].load() > 0) {
-    *cus = cache[dev].load();
-    return TC_OK;
-  }
-  int n = 0;
-  TC_TRY_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
-  if (n <= 0) {
-    set_error("the device reports no compute units");
-    return TC_ERR_HIP;
-  }
-  if (dev >= 0 && dev < 64) cache[dev].store(n);
-  *cus = n;
-  return TC_OK;
-}
-
 int run_split(const Planes4& A, const Planes4& B, int64_t M, int64_t N, int64_t Kp, float ar,
               float ai, float br, float bi, const c64* Cin, int64_t ldcin, bool cin_trans, c64* Cf,
               int64_t ldcf, const Planes4* P, bool p_trans, bool herm, hipStream_t s,
@@ -948,8 +927,7 @@ int run_split(const Planes4& A, const Planes4& B, int64_t M, int64_t N, int64_t 
     // a last round that would leave at least half of the CUs idle (the whole
     // product, when it has that few tiles): its tiles go split over K, one
     // workgroup and one slot of partial sums per K range of at least 4 K slices
-    int cus = 0;
-    TC_RETURN_IF(device_cu_count(&cus));
+    const int cus = device_cus();
     const int64_t full = tiles / cus, tail = tiles % cus, kt = Kp / SPLIT_BK;
     const int64_t slots = std::min<int64_t>(tail_slots, TAIL_SLOTS);
     int S = int(std::min<int64_t>(std::min<int64_t>(cus, slots) / std::max<int64_t>(tail, 1),

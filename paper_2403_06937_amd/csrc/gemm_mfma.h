@@ -40,6 +40,10 @@ struct GemmDesc {
   bool spread = false;
 };
 
+constexpr int MAX_CUS = 256;   // compute units of an unpartitioned MI355X
+// Compute units of the current device (asked once per device).
+int device_cus();
+
 int gemm_f64(const GemmDesc& d, hipStream_t s);   // elements double / cplx<double>
 int gemm_f32(const GemmDesc& d, hipStream_t s);   // elements float / cplx<float>
 

@@ -25,6 +25,7 @@
 #include "profile.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <type_traits>
@@ -1005,8 +1006,6 @@ template <> struct Variants<float, false> {
   typedef Shp<128, 128, 16, 4, 2, 0> V6;
 };
 
-int device_cus();
-
 // The last, partial round of `tiles` tiles of kt K tiles each, on a device that
 // runs `round` workgroups at a time, as equal ranges of at least `least` K tiles
 // (none, tail = 0 and every tile whole, unless that saves the time of `least` K
@@ -1031,8 +1030,6 @@ int64_t tail_slots(int64_t tiles, int64_t kt, int64_t round, int64_t least) {
   if (kt <= least || tiles < 1) return 0;
   return std::min<int64_t>(tiles, round - 1) + std::min<int64_t>(round, tiles * kt / least) - 1;
 }
-
-constexpr int64_t MAX_CUS = 256;     // of an unpartitioned MI355X
 
 // The LDS shapes whose last round may be spread: those that products with a buffer
 // take, row-major complex FP32 on 128 x 128 tiles and real FP64 on 64 x 64.
@@ -1227,17 +1224,18 @@ int build_items(const std::vector<GemmDesc>& ds, std::vector<GroupItem>& items, 
   return TC_OK;
 }
 
-int device_cus() {
-  static int cus = [] {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 256;
-    return n > 0 ? n : 256;
-  }();
-  return cus;
-}
-
 }  // namespace
+
+int device_cus() {
+  static std::atomic<int> cache[64];
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MAX_CUS;
+  if ((n = cache[dev].load()) > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+    return MAX_CUS;
+  cache[dev].store(n);
+  return n;
+}
 
 // Cuts the concatenated tile list into 8 ranges whose work is proportional to
 // each XCD's workgroup count (workgroup w runs on XCD w % 8); a tile's work is

@@ -315,12 +315,13 @@ SmallParams make_params(const GemmDesc& d, int edge) {
   return p;
 }
 
-// 16 x 16 or 32 x 32 tiles: a round of 256 of the smaller ones costs 7/16 of
+// 16 x 16 or 32 x 32 tiles: a round (one tile to a CU) of the smaller ones costs 7/16 of
 // one of the larger ones, not a quarter (two operand reads per MFMA more, and
 // the launch's fixed time): FP64 step at N = 320 26 and 31 us, at N = 384 39 and
 // 36 us, at N = 512 50 and 42 us.
 int choose_edge(int64_t t16, int64_t t32) {
-  return 7 * ((t16 + 255) / 256) < 16 * ((t32 + 255) / 256) ? 16 : 32;
+  const int64_t cus = device_cus();
+  return 7 * ((t16 + cus - 1) / cus) < 16 * ((t32 + cus - 1) / cus) ? 16 : 32;
 }
 
 template <typename T, int TM, int TN, int DEPTH>
