@@ -41,6 +41,7 @@
 // for the next product.
 #include "gemm_bf16.h"
 #include "gemm_bf16_small.h"
+#include "mfma.h"
 #include "profile.h"
 
 #include <cstdlib>
@@ -48,9 +49,6 @@
 namespace tcm {
 namespace {
 
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
 // Global-memory accesses through address-space-1 pointers of scalar or vector
@@ -107,11 +105,6 @@ __device__ __forceinline__ void split2(float x, uint16_t& h, uint16_t& l) {
   l = cvt_bf16(x - __uint_as_float(uint32_t(h) << 16));
 }
 
-__device__ __forceinline__ f4 mma(const u4& a, const u4& b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a),
-                                                 __builtin_bit_cast(bf8, b), c, 0, 0, 0);
-}
-
 // LDS bank conflicts of 16-byte accesses (measured with SQ_LDS_BANK_CONFLICT
 // on gfx950): lanes are served 8 at a time over 32 banks of 4 bytes, so 8
 // lanes are conflict-free when their 16-byte addresses are distinct modulo 8.
@@ -136,16 +129,6 @@ struct SplitParams {
   int tiles_m, tiles_n;
 };
 
-constexpr int GROUP_M = 8;
-
-// Consecutive workgroup ids go round the 8 XCDs; give each XCD a contiguous
-// run of the tile order so that its tiles share operand rows in its L2.
-__device__ __forceinline__ int xcd_linear(int pid, int total) {
-  const int q = total / 8, r = total % 8;
-  const int xcd = pid % 8, local = pid / 8;
-  return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + local;
-}
-
 // Tile lists of grouped launches are sorted by decreasing K, so consecutive
 // ids have similar work.  Within each run of 256 ids (one tile per CU), XCD x
 // (id mod 8) takes the 32 consecutive list entries 32 x .. 32 x + 31, so that
@@ -156,32 +139,6 @@ __device__ __forceinline__ int round_xcd(int pid, int total) {
   const int whole = total - total % 256;
   if (pid >= whole) return pid;
   return (pid / 256) * 256 + (pid % 8) * 32 + (pid % 256) / 8;
-}
-
-// Tile lin of the upper block triangle (tm <= tn) of a T x T tile grid:
-// GROUP_M tile rows at a time, column by column within a group.
-__device__ __forceinline__ void tri_coords(int lin, int T, int& tm, int& tn) {
-  int first = 0;
-  for (;;) {
-    const int gs = min(T - first, GROUP_M);
-    const int tri = gs * (gs - 1) / 2;              // the group's leading triangle
-    const int cnt = gs * (T - first) - tri;
-    if (lin < cnt) {
-      if (lin < tri) {
-        int c = 0;
-        while ((c + 1) * (c + 2) / 2 <= lin) ++c;
-        tn = first + c;
-        tm = first + lin - c * (c + 1) / 2;
-      } else {
-        const int q = lin - tri;
-        tn = first + gs - 1 + q / gs;
-        tm = first + q % gs;
-      }
-      return;
-    }
-    lin -= cnt;
-    first += gs;
-  }
 }
 
 // Tile order of a full product whose tile grid is a multiple of 16 x 16:

@@ -21,20 +21,12 @@
 
 #include <algorithm>
 
+#include "mfma.h"
 #include "profile.h"
 #include "readout.h"
 
 namespace tcm {
 namespace {
-
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f4 mma(const u4& a, const u4& b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a),
-                                                 __builtin_bit_cast(bf8, b), c, 0, 0, 0);
-}
 
 // hi = RNE_bf16(x), or lo = RNE_bf16(x - hi), as bits (the hardware conversion).
 __device__ __forceinline__ uint16_t bits(float x) {
@@ -43,12 +35,6 @@ __device__ __forceinline__ uint16_t bits(float x) {
 __device__ __forceinline__ uint16_t part(float x, bool lo) {
   const uint16_t h = bits(x);
   return lo ? bits(x - __uint_as_float(uint32_t(h) << 16)) : h;
-}
-
-__device__ __forceinline__ int xcd_linear(int pid, int total) {
-  const int q = total / 8, r = total % 8;
-  const int xcd = pid % 8, local = pid / 8;
-  return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + local;
 }
 
 constexpr int NW = 8, DEPTH = 2;           // waves; register sets of operand slices
@@ -73,12 +59,8 @@ split_small_kernel(const SplitSmall p, int tiles_n, int tiles, const SmallReadou
   }
   const int lin = xcd_linear(blockIdx.x, tiles);
   int tm, tn;
-  if (p.herm) {                            // upper tile triangle, column by column
-    int j = int((__builtin_sqrtf(8.f * float(lin) + 1.f) - 1.f) * 0.5f);
-    while (j * (j + 1) / 2 > lin) --j;
-    while ((j + 1) * (j + 2) / 2 <= lin) ++j;
-    tn = j;
-    tm = lin - j * (j + 1) / 2;
+  if (p.herm) {
+    tri_columns(lin, tm, tn);
   } else {
     tm = lin / tiles_n;
     tn = lin - tm * tiles_n;

@@ -22,6 +22,7 @@
 //     tiles that share A rows / B columns share that XCD's L2.
 #include "gemm_mfma.h"
 #include "gemm_small.h"
+#include "mfma.h"
 #include "profile.h"
 
 #include <algorithm>
@@ -32,28 +33,6 @@
 
 namespace tcm {
 namespace {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-template <typename T> struct acc_t;
-template <> struct acc_t<double> { typedef d4 type; };
-template <> struct acc_t<float> { typedef f4 type; };
-
-__device__ __forceinline__ d4 mma(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-// -a * b + c via the FP64 MFMA negation modifier (neg:[1,0,0]).
-__device__ __forceinline__ d4 mma_nega(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
-}
-__device__ __forceinline__ f4 mma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f4 mma_nega(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(-a, b, c, 0, 0, 0);
-}
 
 template <typename T, bool CPLX> struct elem;
 template <typename T> struct elem<T, true> {
@@ -79,8 +58,6 @@ struct Params {
   int tiles_m, tiles_n;
 };
 
-constexpr int GROUP_M = 8;
-
 // Default tile variant per element type for the step / exponential layout,
 // chosen by timing every variant at N = 12288 on gfx950:
 //   complex FP64: 128x128 tiles, 8 waves, K tile 16 (231 ms per full product;
@@ -91,40 +68,6 @@ constexpr int GROUP_M = 8;
 //   complex FP32: 128x128 tiles, 8 waves (112 ms; 128x64: 118 ms)
 template <typename T, bool CPLX> struct DefaultVariant { static constexpr int value = 1; };
 template <> struct DefaultVariant<double, true> { static constexpr int value = 6; };
-
-// Consecutive workgroup ids go round the 8 XCDs; give each XCD a contiguous
-// run of the tile order so that its tiles share operand rows in its L2.
-__device__ __forceinline__ int xcd_linear(int pid, int total) {
-  const int q = total / 8, r = total % 8;
-  const int xcd = pid % 8, local = pid / 8;
-  return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + local;
-}
-
-// Tile lin of the upper block triangle (tm <= tn) of a T x T tile grid:
-// GROUP_M tile rows at a time, column by column within a group.
-__device__ __forceinline__ void tri_coords(int lin, int T, int& tm, int& tn) {
-  int first = 0;
-  for (;;) {
-    const int gs = min(T - first, GROUP_M);
-    const int tri = gs * (gs - 1) / 2;              // the group's leading triangle
-    const int cnt = gs * (T - first) - tri;
-    if (lin < cnt) {
-      if (lin < tri) {
-        int c = 0;
-        while ((c + 1) * (c + 2) / 2 <= lin) ++c;
-        tn = first + c;
-        tm = first + lin - c * (c + 1) / 2;
-      } else {
-        const int q = lin - tri;
-        tn = first + gs - 1 + q / gs;
-        tm = first + q % gs;
-      }
-      return;
-    }
-    lin -= cnt;
-    first += gs;
-  }
-}
 
 // Publishes this wave's LDS writes to the workgroup: waits for them, then a
 // barrier.  Outstanding global loads are not waited for (__syncthreads would

@@ -24,32 +24,12 @@
 
 #include <algorithm>
 
+#include "mfma.h"
 #include "profile.h"
 #include "readout.h"
 
 namespace tcm {
 namespace {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-// 16 x 16 x 4 MFMA: output r of lane l is row l/16 + 4r (FP64) or 4(l/16) + r
-// (FP32) of column l%16.  mma_nega: c - a b.
-__device__ __forceinline__ d4 mma(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ d4 mma_nega(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
-}
-__device__ __forceinline__ f4 mma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f4 mma_nega(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(-a, b, c, 0, 0, 0);
-}
-template <typename T> struct acc_t;
-template <> struct acc_t<double> { typedef d4 type; };
-template <> struct acc_t<float> { typedef f4 type; };
 
 struct SmallParams {
   int M, N, K;
@@ -61,14 +41,6 @@ struct SmallParams {
   int conj_a, conj_b, herm;
   int tiles_n, tiles;
 };
-
-// Consecutive workgroup ids go round the 8 XCDs; give each XCD a contiguous
-// run of the tile order so that its tiles share operand rows in its L2.
-__device__ __forceinline__ int xcd_linear(int pid, int total) {
-  const int q = total / 8, r = total % 8;
-  const int xcd = pid % 8, local = pid / 8;
-  return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + local;
-}
 
 constexpr int NW = 8, NT = 64 * NW;
 static_assert(NT == READOUT_NT, "the last workgroup of a launch may read the records");
@@ -99,12 +71,8 @@ __device__ __forceinline__ void small_tile_body(const SmallParams& p, int lin, c
   typedef typename pair_t<T>::type v2;
   constexpr int NB = TM * TN;
   int tm, tn;
-  if (p.herm) {                            // upper tile triangle, column by column
-    int j = int((__builtin_sqrtf(8.f * float(lin) + 1.f) - 1.f) * 0.5f);
-    while (j * (j + 1) / 2 > lin) --j;
-    while ((j + 1) * (j + 2) / 2 <= lin) ++j;
-    tn = j;
-    tm = lin - j * (j + 1) / 2;
+  if (p.herm) {
+    tri_columns(lin, tm, tn);
   } else {
     tm = lin / p.tiles_n;
     tn = lin - tm * p.tiles_n;

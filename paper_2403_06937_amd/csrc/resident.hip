@@ -32,6 +32,7 @@
 #include <cmath>
 
 #include "kernels.h"
+#include "mfma.h"
 
 namespace tcm {
 namespace {
@@ -51,24 +52,6 @@ __device__ __forceinline__ void sync_lds() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-// 16 x 16 x 4 MFMA in the storage precision: lane l supplies A[l%16][l/16]
-// and B[l/16][l%16]; output r of lane l is row l/16 + 4r (FP64) or
-// 4(l/16) + r (FP32) of column l%16.  mma_nega: c - a b.
-__device__ __forceinline__ d4 mma(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ d4 mma_nega(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
-}
-__device__ __forceinline__ f4 mma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f4 mma_nega(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(-a, b, c, 0, 0, 0);
-}
 template <typename T> struct Acc;
 template <> struct Acc<double> {
   typedef d4 type;
