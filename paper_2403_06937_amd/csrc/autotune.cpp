@@ -29,13 +29,15 @@ const int64_t kBucketRep[NB] = {256, 1024, 4096, 7168};
 
 std::mutex g_mu;
 bool g_loaded = false;
-// Defaults from timing on gfx950: 64 x 64 tiles for groups of any size.  One FP32
-// product prefers 128 x 128 tiles from N = 1024 (12288: 158 ms a step against
-// 167), but a group gains more from the finer tiles' smaller padding and shorter
-// last round: 24 instances of N = 32 .. 3072 7.14 -> 6.79 ms a step, by sectors
-// N = 1536 153 -> 79 us, 2304 184 -> 130, 5120 998 -> 871, 12288 15.1 -> 14.9 ms.
+// Defaults from timing on gfx950: 64 x 64 tiles.  One FP32 product prefers 128 x 128
+// tiles from N = 1024 (12288: 158 ms a step against 167), but the blocks of a sector
+// run gain more from the finer tiles' smaller padding and shorter last round (N = 1536
+// 153 -> 79 us a step, 2304 184 -> 130, 5120 998 -> 871, 12288 15.1 -> 14.9 ms); so do
+// most dense batches (24 instances of N = 32 .. 3072 7.14 -> 6.79 ms), for which the
+// batch itself decides until the table is set.
 int g_table[2][NB] = {{2, 2, 2, 2},    // FP32
                       {2, 2, 2, 2}};   // FP64
+bool g_set[2] = {false, false};
 
 int bucket_of(int64_t N) {
   for (int b = 0; b < NB; ++b)
@@ -76,6 +78,7 @@ void load_cache_locked() {
       bool ok = true;
       for (int b = 0; b < NB; ++b) ok = ok && (vals[b] == 1 || vals[b] == 2);
       if (ok) for (int b = 0; b < NB; ++b) g_table[prec][b] = vals[b];
+      g_set[prec] = g_set[prec] || ok;
     }
   }
 }
@@ -96,6 +99,12 @@ int tile_variant_for(int64_t N, bool f64) {
   std::lock_guard<std::mutex> lk(g_mu);
   load_cache_locked();
   return g_table[f64 ? 1 : 0][bucket_of(N)];
+}
+
+bool tile_table_set(bool f64) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  load_cache_locked();
+  return g_set[f64 ? 1 : 0];
 }
 
 }  // namespace tcm
@@ -174,6 +183,7 @@ int tc_autotune(int32_t gemm_mode, int64_t max_N, void* ws, size_t ws_bytes, voi
   std::lock_guard<std::mutex> lk(g_mu);
   g_loaded = true;
   for (int b = 0; b < NB; ++b) g_table[f64 ? 1 : 0][b] = chosen[b];
+  g_set[f64 ? 1 : 0] = true;
   save_cache_locked();
   return TC_OK;
 }

@@ -825,15 +825,96 @@ int evolve_one(InstPlan& p, const tc_instance& in, const tc_evolve_opts& o, hipS
 // tiles, the readout is one launch for all instances (record index kept in a
 // device counter), and with use_graph the launches of a chunk of steps are
 // captured once in a hipGraph and replayed.
-// Dense instances of a batch that take the small product kernel, as they do on
-// their own: always up to N = 192 (16 instances of N = 160: 82 -> 47 us a step
-// in FP64, 62 -> 36 in FP32, N = 64: 44 -> 24), and up to N = 512 where there are
-// fewer 64 x 64 tiles than CUs (4 x 256 in FP64 36 us against 92) or, in FP32,
-// ragged ones (the persistent kernel).  A chip full of 64 x 64 tiles reads less
-// per product: FP64 48 x 224 take 170 us a step against 219, 16 x 480 425
-// against 468; FP32 30 x 256 176 against 185.
-bool batch_small(int64_t N, int64_t tiles64, bool f64) {
-  return N <= 192 || (N <= 512 && (tiles64 < device_cus() || (!f64 && N % 64 != 0)));
+int64_t tile_count(int64_t N, int edge, bool triangle) {
+  const int64_t t = (N + edge - 1) / edge;
+  return triangle ? t * (t + 1) / 2 : t * t;
+}
+
+// Whether a batch's members of N <= 192 (Ns) take the small product kernel, as they
+// do on their own, or 64 x 64 tiles with the larger ones.  A few are far too little
+// for the chip, and the small kernel's short K loops win; many fill it, and whole
+// tiles with fewer rounds win.  The tiles' estimates are fitted like the small
+// kernel's (us a step, small / tiles: FP64 64 x N = 64 22 / 31, 128 x 64 38 / 33, 40 x 128
+// 56 / 52, 128 x 128 136 / 82, 64 x 160 132 / 130, 400 x 160 740 / 521; FP32 40 x 64 17 / 24,
+// 400 x 64 64 / 40, 100 x 96 43 / 51, 100 x 128 65 / 57, 128 x 160 130 / 154, 100 x 192
+// 179 / 129).
+bool small_members(const std::vector<int64_t>& Ns, bool f64, bool herm) {
+  const double cus = device_cus();
+  double small = 0.0, tiles = 0.0;
+  for (const bool triangle : {false, herm}) {
+    double t16 = 0, t32 = 0, t64 = 0, work32 = 0, work64 = 0, ragged = 0;
+    for (const int64_t N : Ns) {
+      const double a = double(tile_count(N, 32, triangle)), b = double(tile_count(N, 64, triangle));
+      t16 += double(tile_count(N, 16, triangle));
+      t32 += a;
+      t64 += b;
+      work32 += a * double(N);
+      work64 += b * double(N);
+      if (N % (f64 ? 8 : 64) != 0) ragged += b;       // range-checked tiles
+    }
+    small += small_group_us(t16, t32, work32 / t32, f64, nullptr);
+    const double K = work64 / t64, more = std::ceil(t64 / cus) - 1.0;   // further rounds
+    const bool checked = 2.0 * ragged > t64;
+    if (f64) tiles += (checked ? 6.5 : 4.0) + K * (0.15 + 0.115 * more);
+    else tiles += checked ? 3.5 + K * (0.115 + 0.092 * more) : 3.0 + K * (0.1 + 0.068 * more);
+  }
+  return small < tiles;
+}
+
+// Members of 192 < N <= 512 take the small kernel where there are fewer 64 x 64
+// tiles than CUs (4 x 256 in FP64 36 us against 92) or, in FP32, ragged ones (the
+// persistent kernel).  A chip full of 64 x 64 tiles reads less per product: FP64
+// 48 x 224 take 170 us a step against 219, 16 x 480 425 against 468; FP32 30 x 256 176
+// against 185.
+bool small_member(int64_t N, int64_t tiles64, bool f64) {
+  return N <= 512 && (tiles64 < device_cus() || (!f64 && N % 64 != 0));
+}
+
+// Time of one product phase over members Ns on tiles of one edge, in units of a
+// 64 x 64 FP32 tile's K step: full rounds and the unfilled part of the last one (where
+// sizes differ, half a mean tile's time or more in a few rounds, a quarter in many).
+// Work on 64 x 64 tiles takes 1.06 of its time on 128 x 128, range-checked tiles 1.22.
+double tile_rounds(const std::vector<int64_t>& Ns, int edge, bool triangle) {
+  const double cus = device_cus(), unit = edge == 128 ? 4.0 : 1.06;
+  double total = 0.0;
+  for (const bool ragged : {false, true}) {
+    double tiles = 0.0, work = 0.0;
+    bool equal = true;
+    int64_t first = 0;
+    for (const int64_t N : Ns) {
+      if ((N % edge != 0) != ragged) continue;
+      const double t = double(tile_count(N, edge, triangle));
+      tiles += t;
+      work += t * double(N);
+      if (first == 0) first = N;
+      equal = equal && N == first;
+    }
+    if (tiles == 0.0) continue;
+    const double rounds = tiles / cus;
+    double part = std::ceil(rounds) - rounds;
+    if (!equal) part = rounds < 4.0 ? std::max(part, 0.5) : 0.25;
+    total += (ragged ? 1.22 : 1.0) * unit * (rounds + part) * work / tiles;
+  }
+  return total;
+}
+
+// Tile shape of an FP32 batch's members above N = 1024 when no tuning has set the
+// table: 128 x 128 tiles where their rounds fill the chip (us a step, 128 x 128 / 64 x 64,
+// every tile: 8 x N = 2048 7893 / 8358, 16 x 3072 52719 / 55950, 2 x 6144 52627 / 55923),
+// 64 x 64 with the smaller members where those leave much of a last round idle
+// (2 x 1536 1508 / 1032, 4 x 2304 6675 / 6171, triangles of 2 x 2560 3750 / 3317).  The
+// estimate of members that differ in size is coarser: it has to win by 3 %.
+int fp32_variant(const std::vector<int64_t>& Ns, bool herm) {
+  std::vector<int64_t> large, rest;
+  for (const int64_t N : Ns) (N > 1024 ? large : rest).push_back(N);
+  bool equal = rest.empty();
+  for (const int64_t N : large) equal = equal && N == large[0];
+  double fine = 0.0, coarse = 0.0;
+  for (const bool triangle : {false, herm}) {
+    fine += tile_rounds(Ns, 64, triangle);
+    coarse += tile_rounds(large, 128, triangle) + tile_rounds(rest, 64, triangle);
+  }
+  return coarse < (equal ? 1.0 : 0.97) * fine ? 1 : 2;
 }
 
 // A batch's descriptors, one after another as a run takes them: the grouped
@@ -926,20 +1007,34 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
                      : prepare(plans[b], inst[b], o, s));
   // group the products by tile shape (autotuner table per dimension bucket)
   // and by whether N is a multiple of the tile: those run one workgroup per
-  // tile with the unchecked tile (fewer registers), the rest persistently.
+  // tile with the unchecked tile (fewer registers), the rest persistently (FP64
+  // direct tiles: one workgroup per tile too, so an N that is no multiple of 8,
+  // which they do not take, is a group of its own).
   // By sectors, the block products of every instance (whole tiles of the
   // instance's padding) go into one group per tile shape.  Every group runs its
   // largest K first, so that its last round is of the shortest tiles (24 instances
   // of N = 32 .. 3072 in FP32 7.47 -> 7.14 ms a step).
-  // Small dense instances (batch_small) go into one group of small products
-  // per product phase.
-  std::vector<GemmDesc> d1[3][2], d2[3][2], s1, s2;
+  // Small dense instances (small_members, small_member) go into one group of
+  // small products per product phase.
+  std::vector<GemmDesc> d1[3][3], d2[3][3], s1, s2;
   std::vector<SplitProduct> sp1, sp2;
   int64_t tiles64 = 0;
-  for (int b = 0; b < count; ++b)
-    if (plans[b].N <= 512) tiles64 += ((plans[b].N + 63) / 64) * ((plans[b].N + 63) / 64);
+  std::vector<int64_t> least, tiled;
+  const bool herm = o.full_product == 0;
   for (int b = 0; b < count; ++b) {
-    const int v = sec ? plans[b].svar : tile_variant_for(plans[b].N, f64);
+    if (plans[b].N <= 512) tiles64 += tile_count(plans[b].N, 64, false);
+    if (plans[b].N <= 192) least.push_back(plans[b].N);
+  }
+  const bool least_small = !sec && !least.empty() && small_members(least, f64, herm);
+  auto takes_small = [&](int64_t N) {
+    return N <= 192 ? least_small : small_member(N, tiles64, f64);
+  };
+  for (int b = 0; b < count; ++b)
+    if (!takes_small(plans[b].N)) tiled.push_back(plans[b].N);
+  const int large = sec || f64 || tile_table_set(false) ? 0 : fp32_variant(tiled, herm);
+  for (int b = 0; b < count; ++b) {
+    const int v = sec ? plans[b].svar
+                      : large && plans[b].N > 1024 ? large : tile_variant_for(plans[b].N, f64);
     if (sec && split) {
       sp1.insert(sp1.end(), plans[b].ssd1.begin(), plans[b].ssd1.end());
       sp2.insert(sp2.end(), plans[b].ssd2.begin(), plans[b].ssd2.end());
@@ -949,13 +1044,13 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
     } else {
       GemmDesc g1, g2;
       step_descs(plans[b], o, g1, g2);
-      if (batch_small(plans[b].N, tiles64, f64)) {
+      if (takes_small(plans[b].N)) {
         s1.push_back(g1);
         s2.push_back(g2);
         continue;
       }
       const int edge = v == 1 ? 128 : 64;
-      const int e = plans[b].N % edge == 0 ? 0 : 1;
+      const int e = plans[b].N % edge == 0 ? 0 : f64 && plans[b].N % 8 != 0 ? 2 : 1;
       d1[v][e].push_back(g1);
       d2[v][e].push_back(g2);
     }
@@ -966,7 +1061,7 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   std::stable_sort(s2.begin(), s2.end(), by_k);
   std::stable_sort(sp1.begin(), sp1.end(), by_kp);
   std::stable_sort(sp2.begin(), sp2.end(), by_kp);
-  GroupedProducts G1[3][2], G2[3][2];
+  GroupedProducts G1[3][3], G2[3][3];
   SplitGrouped S1, S2;
   auto build = [&](const std::vector<GemmDesc>& ds, int v, GroupedProducts* g) -> int {
     char* it = bb.take(grouped_bytes(1), ds.size());
@@ -989,13 +1084,13 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   TC_RETURN_IF(build_small(s1, &T1));
   TC_RETURN_IF(build_small(s2, &T2));
   for (int v = 1; v <= 2; ++v)
-    for (int e = 0; e < 2; ++e) {
+    for (int e = 0; e < 3; ++e) {
       if (d1[v][e].empty()) continue;
       std::stable_sort(d1[v][e].begin(), d1[v][e].end(), by_k);
       std::stable_sort(d2[v][e].begin(), d2[v][e].end(), by_k);
       TC_RETURN_IF(build(d1[v][e], v, &G1[v][e]));
       TC_RETURN_IF(build(d2[v][e], v, &G2[v][e]));
-      G1[v][e].persistent = G2[v][e].persistent = e == 1;
+      G1[v][e].persistent = G2[v][e].persistent = e != 0;
     }
   bool rec = false, ckpt = false;
   std::vector<ReadoutItem> ri(count);
@@ -1024,11 +1119,11 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   auto one_step = [&](int64_t st, hipStream_t q) -> int {
     TC_RETURN_IF(split_grouped_run(S1, q));
     for (int v = 1; v <= 2; ++v)
-      for (int e = 0; e < 2; ++e) TC_RETURN_IF(grouped_run(G1[v][e], q));
+      for (int e = 0; e < 3; ++e) TC_RETURN_IF(grouped_run(G1[v][e], q));
     TC_RETURN_IF(small_grouped_run(T1, q));
     TC_RETURN_IF(split_grouped_run(S2, q));
     for (int v = 1; v <= 2; ++v)
-      for (int e = 0; e < 2; ++e) TC_RETURN_IF(grouped_run(G2[v][e], q));
+      for (int e = 0; e < 3; ++e) TC_RETURN_IF(grouped_run(G2[v][e], q));
     TC_RETURN_IF(small_grouped_run(T2, q));
     for (int b = 0; b < count; ++b) TC_RETURN_IF(dissipate(plans[b], o, q));
     if (o.renorm_every > 0 && st % o.renorm_every == 0)

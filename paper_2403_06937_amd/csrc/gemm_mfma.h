@@ -86,5 +86,7 @@ void xcd_split(const std::vector<int64_t>& begins, const std::vector<int64_t>& t
 // Tile variant for an N x N x N complex product, from the autotuner's table
 // (or its defaults when no tuning ran and no cache file is set).
 int tile_variant_for(int64_t N, bool f64);
+// Whether tuning or a cache file has set that table.
+bool tile_table_set(bool f64);
 
 }  // namespace tcm

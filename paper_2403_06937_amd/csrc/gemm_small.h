@@ -23,6 +23,10 @@ bool small_product(const GemmDesc& d, bool f64);
 template <typename T>
 int small_gemm(const GemmDesc& d, const SmallReadout* ro, hipStream_t s);
 
+// Estimated us of one group of small products with t16 tiles of 16 x 16, or t32 of
+// 32 x 32, and mean K, on the better edge (*edge, may be NULL).
+double small_group_us(double t16, double t32, double K, bool f64, int* edge);
+
 // Small products of many instances in one launch.
 struct SmallGroup {
   bool f64 = false;

@@ -23,6 +23,7 @@
 #include "gemm_small.h"
 
 #include <algorithm>
+#include <cmath>
 
 #include "mfma.h"
 #include "profile.h"
@@ -283,7 +284,7 @@ SmallParams make_params(const GemmDesc& d, int edge) {
   return p;
 }
 
-// 16 x 16 or 32 x 32 tiles: a round (one tile to a CU) of the smaller ones costs 7/16 of
+// One product on 16 x 16 or 32 x 32 tiles: a round (one tile to a CU) of the smaller ones costs 7/16 of
 // one of the larger ones, not a quarter (two operand reads per MFMA more, and
 // the launch's fixed time): FP64 step at N = 320 26 and 31 us, at N = 384 39 and
 // 36 us, at N = 512 50 and 42 us.
@@ -291,6 +292,31 @@ int choose_edge(int64_t t16, int64_t t32) {
   const int64_t cus = device_cus();
   return 7 * ((t16 + cus - 1) / cus) < 16 * ((t32 + cus - 1) / cus) ? 16 : 32;
 }
+
+}  // namespace
+
+// A group's tiles run in rounds of one workgroup per CU (FP32 32 x 32 tiles two to a
+// CU), and a round of small tiles costs what its 8 waves' load, reduction and
+// dispatch take, whatever K: fitted to groups of 4 to 400 instances of N = 8 .. 192
+// (us a step of two products, 16 x 16 / 32 x 32: FP64 4 x N = 112 17 / 20, 40 x 44 19 / 18,
+// 100 x 64 68 / 36, 40 x 160 133 / 81; FP32 16 x 48 14.2 / 14.5, 40 x 64 33 / 17, 100 x 128
+// 201 / 65).
+double small_group_us(double t16, double t32, double K, bool f64, int* edge) {
+  const double cus = device_cus(), r16 = std::ceil(t16 / cus), r32 = t32 / cus;
+  const double us16 = r16 * (std::min(4.8, 1.5 + 0.05 * K) + 0.004 * std::max(0.0, K - 160.0));
+  double us32;
+  if (f64)
+    us32 = std::ceil(r32) * (K < 60.0 ? 2.5 + 0.078 * K : std::max(5.7 + 0.023 * K, 0.04 * K));
+  else
+    us32 = r32 <= 1.0 ? 2.5 + 0.03 * K
+                      : std::min(3.0, 0.04 * K) +
+                            (K < 60.0 ? 1.6 + 0.04 * K : std::max(3.75, 0.031 * K)) * r32;
+  const bool fine = us16 < us32 || t16 <= t32;
+  if (edge) *edge = fine ? 16 : 32;
+  return fine ? us16 : us32;
+}
+
+namespace {
 
 template <typename T, int TM, int TN, int DEPTH>
 int launch_small(const SmallParams& p, const SmallReadout* ro, hipStream_t s) {
@@ -343,6 +369,7 @@ size_t small_grouped_bytes(int count) { return size_t(count) * sizeof(SmallItem)
 int small_grouped_build(const std::vector<GemmDesc>& ds, bool f64, void* items_dev, SmallGroup* g,
                         hipStream_t s) {
   int64_t t16 = 0, t32 = 0, t = 0;
+  double work = 0.0;
   for (const GemmDesc& d : ds) {
     if (!small_product(d, f64)) {
       set_error("grouped small products: a product is not a small one");
@@ -350,8 +377,9 @@ int small_grouped_build(const std::vector<GemmDesc>& ds, bool f64, void* items_d
     }
     t16 += tile_count(d.M, d.N, d.herm, 16);
     t32 += tile_count(d.M, d.N, d.herm, 32);
+    work += double(tile_count(d.M, d.N, d.herm, 32)) * double(d.K);
   }
-  g->edge = choose_edge(t16, t32);
+  small_group_us(double(t16), double(t32), ds.empty() ? 0.0 : work / double(t32), f64, &g->edge);
   std::vector<SmallItem> items;
   for (const GemmDesc& d : ds) {
     SmallItem it;

@@ -87,6 +87,59 @@ def test_record_every_and_graph_chunks():
             assert abs(pops[k][r] - ref) < 1e-12
 
 
+@pytest.mark.parametrize("mode,frame,dtype,tol", [
+    (tcm.TC_GEMM_F64, tcm.TC_FRAME_LAB, torch.complex128, 1e-10),
+    (tcm.TC_GEMM_F32, tcm.TC_FRAME_ROTATING, torch.complex64, 1e-5)])
+@pytest.mark.parametrize("shapes", [
+    [(2, 2), (4, 2), (4, 3)] * 100,                        # N = 12, 48, 64: 300 tiles of 64 x 64
+    [(5, 3)] * 80,                                         # 128: 320
+    [(5, 4)] * 12 + [(2, 10)] * 6,                         # 160 and 44: small products
+    [(2, 2)] * 260 + [(5, 18), (2, 128)]])                 # with 608 and 516: tiles of each kind
+def test_batches_of_many_small_instances(shapes, mode, frame, dtype, tol):
+    """Batches that fill the chip with 64 x 64 tiles and ones that do not, with
+    triangles and with every tile: each instance against the oracle."""
+    dt, steps = 0.05, 8
+    kinds = sorted(set(shapes))
+    models, refs = {}, {}
+    for n, c in kinds:
+        inst = ti.random_model(n, c, 330 + n + c, state="gaussian")
+        models[n, c] = inst
+        psi = oev.SectorPropagator(n, c, inst.g, inst.omega_a).psi(inst.psi0, steps * dt)
+        refs[n, c] = np.outer(psi, psi.conj())
+    Us = {k: pipeline.propagator(pipeline.model_of(i), dt)[1] for k, i in models.items()}
+    rdt = tcm.TC_C128 if dtype == torch.complex128 else tcm.TC_C64
+    for full in (0, 1):
+        rhos = [torch.from_numpy(models[k].rho0()).to("cuda").to(dtype) for k in shapes]
+        ms = [pipeline.model_of(models[k]) for k in shapes]
+        opts = tcm.make_opts(steps, dt, mode, rdt, frame, 0, 1, 0, 0, full, no_resident=1)
+        tcm.tc_evolve([tcm.make_instance(m, Us[k], r) for m, k, r in zip(ms, shapes, rhos)], opts)
+        torch.cuda.synchronize()
+        for k, r in zip(shapes, rhos):
+            assert np.max(np.abs(r.cpu().numpy() - refs[k])) <= tol, (k, full)
+
+
+@pytest.mark.parametrize("n,c,count,full", [(9, 3, 2, 1), (8, 5, 4, 0), (7, 8, 6, 1)])
+def test_batches_of_large_fp32_instances(n, c, count, full):
+    """Complex FP32 members above N = 1024 on 128 x 128 tiles (2 x 2048 and 6 x 1152 with
+    every tile) or 64 x 64 (triangles of 4 x 1536), chosen by their rounds, against the
+    oracle."""
+    inst = ti.random_model(n, c, 340 + n, state="haar2")
+    dt, steps = 0.05, 4
+    m = pipeline.model_of(inst)
+    _, U = pipeline.propagator(m, dt)
+    rho0 = torch.from_numpy(inst.rho0()).to("cuda").to(torch.complex64)
+    rhos = [rho0.clone() for _ in range(count)]
+    opts = tcm.make_opts(steps, dt, tcm.TC_GEMM_F32, tcm.TC_C64, tcm.TC_FRAME_ROTATING, 0, 1, 0, 0,
+                         full)
+    tcm.tc_evolve([tcm.make_instance(m, U, r) for r in rhos], opts)
+    torch.cuda.synchronize()
+    psi = oev.SectorPropagator(n, c, inst.g, inst.omega_a).psi(inst.psi0, steps * dt)
+    got = rhos[0].cpu().numpy()
+    assert np.max(np.abs(got - np.outer(psi, psi.conj()))) <= 1e-5
+    for r in rhos[1:]:
+        assert torch.equal(r, rhos[0])
+
+
 def test_autotune_table_and_cache(tmp_path):
     path = tmp_path / "tune.json"
     os.environ["TC_AUTOTUNE_CACHE"] = str(path)
