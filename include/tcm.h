@@ -357,9 +357,12 @@ int tc_split_bf16(const float* x, int64_t count, uint16_t* hi, uint16_t* lo, voi
 /* ------------------------------------------------- a8: tile autotuner */
 
 /* tc_evolve with count > 1 and FP64 / FP32 products runs each product phase
- * of a step as one persistent launch per tile shape over the tiles of every
- * instance; the shape of each instance comes from a table indexed by its
- * dimension bucket (N <= 256, <= 1024, <= 4096, larger).  tc_autotune times
+ * of a step as one launch per tile shape over the tiles of every instance; the
+ * shape of each instance comes from a table indexed by its dimension bucket
+ * (N <= 256, <= 1024, <= 4096, larger).  Small members may take the kernel of
+ * small products instead, and until tc_autotune or a cache file has set the FP32
+ * table, members above 1024 take the shape whose rounds fill the device better
+ * (tc_autotune_query returns the table's value).  tc_autotune times
  * both shapes (1: 128 x 128 tiles, 2: 64 x 64 tiles) on an N x N x N complex
  * product per bucket (N capped at max_N) with hipEvents, stores the faster
  * one in the process-wide table and, if the environment variable

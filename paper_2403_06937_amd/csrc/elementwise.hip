@@ -500,8 +500,8 @@ __global__ void damp_cavity_kernel(E* __restrict__ rho, int64_t ld, int n, int c
 //   a[m][l] = eta^{m/2} (binom(m + l, l) |1 - eta|^l)^{1/2},
 // L^2 numbers from the host whose index is the same for all threads of a
 // workgroup, and the sign of (1 - eta)^l: -1 for odd l when eta > 1, which is the
-// inverse channel of a run with a negative dt.  HBM-bound: N = 2048 FP32 11 us against 46 when each coefficient's
-// roots and divisions were formed per element.
+// inverse channel of a run with a negative dt.  HBM-bound: N = 2048 FP32 11 us
+// against 46 when each coefficient's roots and divisions were formed per element.
 template <int L> struct CavityCoef {
   double a[L * L];
   double odd;                                // sign of (1 - eta)^l for odd l
@@ -702,7 +702,7 @@ __device__ __forceinline__ void dicke_rows(int n, int mm, int64_t b, int64_t nbl
 // reduced.  The squares of the Hermiticity differences are compared and one
 // root taken at the end; values whose square leaves the normal range go through
 // hypot.
-// The whole readout (both passes): N = 5120 complex FP64 230 -> 88 us (4.8
+// The whole readout (both passes): N = 5120 complex FP64 240 -> 97 us (4.3
 // TB/s), N = 12288 962 -> 441 us (5.5 TB/s), FP32 893 -> 294 us, N = 32 22 -> 13
 // us; one workgroup reading every tile pair's sums and all outputs' diagonals in
 // turn took half of it before.

@@ -982,8 +982,9 @@ int evolve_batched(std::vector<InstPlan>& plans, const tc_instance* inst, int co
   const bool f64 = o.gemm_mode == TC_GEMM_F64;
   // a batch of nothing but LDS-resident instances: one workgroup each, all steps
   // in one launch (30 of N = 32: per-step launches took 23 us a step).  With
-  // full_product a batch keeps the per-step products, whose bits equal those of
-  // its members' own runs with no_resident.
+  // full_product a batch keeps the per-step products; their bits equal those of a
+  // member's own run with no_resident where both take the small product kernel or
+  // tiles of one shape without K ranges.
   bool all = o.full_product == 0;
   for (int b = 0; b < count; ++b) all = all && use_resident(plans[b], inst[b], o);
   if (all) {

@@ -1,10 +1,13 @@
 // MFMA matrix products in FP64 and FP32 for gfx950 (CDNA4).
 //
-// One templated kernel covers the complex products of the time step
-// (rho <- U rho U^dag, two complex N x N x N products per step) and the real
-// and complex products used to form U.  Design:
-//   * 256 threads = 4 wavefronts of 64 lanes; the wave grid is WGM x WGN and
-//     each wave owns WM x WN blocks of 16 x 16 outputs.
+// The complex products of the time step (rho <- U rho U^dag, two complex
+// N x N x N products per step) and the real products used to form U.  Small ones
+// go to the kernel of gemm_small.hip; FP64 with K a multiple of 8 takes direct
+// tiles (gemm_direct_kernel, further down: no LDS); the rest, FP32 above all,
+// takes LDS tiles (gemm_kernel).  Both renumber their workgroups for the XCDs and
+// spread a partly filled last round over the CUs (TailSplit).  LDS tiles:
+//   * the wave grid is WGM x WGN (4 or 8 wavefronts of 64 lanes) and each wave
+//     owns WM x WN blocks of 16 x 16 outputs.
 //   * v_mfma_f64_16x16x4_f64 / v_mfma_f32_16x16x4_f32: lane l supplies
 //     A[l%16][l/16] and B[l/16][l%16] of a 16x4 / 4x16 slice.  Output r of
 //     lane l is D[4*(l/16)+r][l%16] for FP32 but D[l/16+4r][l%16] for FP64
@@ -58,13 +61,14 @@ struct Params {
   int tiles_m, tiles_n;
 };
 
-// Default tile variant per element type for the step / exponential layout,
-// chosen by timing every variant at N = 12288 on gfx950:
+// Default LDS tile variant per element type for the step / exponential layout,
+// chosen by timing every variant at N = 12288 on gfx950 (FP64 takes it only for K
+// that is no multiple of 8, or with TC_GEMM_VARIANT; the times are those of the LDS
+// tiles when they were compared):
 //   complex FP64: 128x128 tiles, 8 waves, K tile 16 (231 ms per full product;
 //                 64x64: 285 ms; 128x128 with K tile 8: 294 ms; 128x64: 438 ms;
-//                 LDS row padding of 0, 16 or 32 bytes: no difference), for K
-//                 that direct tiles do not take
-//   real FP64:    128x128 tiles, 8 waves (128x64: a third slower), likewise
+//                 LDS row padding of 0, 16 or 32 bytes: no difference)
+//   real FP64:    128x128 tiles, 8 waves (128x64: a third slower)
 //   complex FP32: 128x128 tiles, 8 waves (112 ms; 128x64: 118 ms)
 template <typename T, bool CPLX> struct DefaultVariant { static constexpr int value = 1; };
 template <> struct DefaultVariant<double, true> { static constexpr int value = 6; };

@@ -47,9 +47,10 @@ int launch_frame_phase_c128(const ModelArgs& m, c128* rho, int64_t ld, double t,
 int launch_frame_phase_c64(const ModelArgs& m, c64* rho, int64_t ld, double t, hipStream_t s);
 
 // Dissipation over dt, exp(dt L) for the Lindblad term of the model (in
-// place; no-op when kappa = gamma = 0): one amplitude-damping channel per atom,
-// two atoms per pass, then the cavity channel.  Commutes with the rotating
-// frame's phase, so it applies in either frame.
+// place; no-op when kappa = gamma = 0): one amplitude-damping channel per atom
+// (atoms on the six lowest bits in one pass, the rest three (c64) or two per pass),
+// then the cavity channel.  dt < 0 undoes it.  Commutes with the rotating frame's
+// phase, so it applies in either frame.
 int launch_dissipation_c128(const ModelArgs& m, c128* rho, int64_t ld, double dt, hipStream_t s);
 int launch_dissipation_c64(const ModelArgs& m, c64* rho, int64_t ld, double dt, hipStream_t s);
 

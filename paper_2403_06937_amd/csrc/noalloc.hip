@@ -12,7 +12,9 @@ namespace tcm {
 namespace {
 
 // Partial sums of the observables' reductions: 16 MiB, enough for every N up
-// to 37 120 (3 per 32 x 32 tile pair, the diagonal, Im Tr and the Dicke pass).
+// to 37 120.  The size is 3 per 32 x 32 tile pair, 2 N and 8, of which a call uses 4
+// per workgroup of pass 1 (at most 1024, one per tile pair at most), the diagonal
+// and the Dicke rows' partial sums.
 constexpr size_t SCRATCH_BYTES = size_t(16) << 20;
 static __device__ __align__(256) double scratch[SCRATCH_BYTES / sizeof(double)];
 
